@@ -338,6 +338,26 @@ def test_active_subsets_and_duplicates():
     ctx.check()
 
 
+@pytest.mark.parametrize("n", [255 * 64, 64 * 256 + 1, 8192 * 256 - 63, 8305 * 256 - 1])
+def test_block_order_covers_every_group(n, monkeypatch):
+    """The blocks of a walk are dealt to the dies in runs of a length that
+    follows from their number: every group of 64 targets is walked once,
+    whatever number of blocks the runs leave over.  The shared cursor against
+    the independent lanes (another launch geometry), bit for bit."""
+    p = W.uniform_cube(n, 41)
+    out = []
+    for mode in ("1", "2"):
+        monkeypatch.setenv("TPM_WALK_MODE", mode)
+        ctx = _ctx(precision="fp32", eps=0.01, theta=1.5)
+        _build(ctx, p)
+        nint = torch.full((n,), -1, dtype=torch.int32, device=_dev())
+        acc = torch.full((3, n), float("nan"), dtype=torch.float32, device=_dev())
+        ctx.compute_forces(_t(np.arange(n), torch.int32), "bh", acc=acc, n_interactions=nint)
+        ctx.check()
+        out.append((acc, nint))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_sparse_sets_group_or_lanes_identical(prec):
     """Sparse active sets with a cutoff take the shared cursor or independent
