@@ -486,7 +486,7 @@ __device__ __forceinline__ void item_output(const SrvReq &R, uint32_t it) {
     }
 }
 
-// Both instances inline every walk variant (FP32: 80 VGPRs, FP64: 170, no
+// Both instances inline every walk variant (FP32: 76 VGPRs, FP64: 105, no
 // spills); each is launched with two wavefronts per SIMD.
 template <bool FP32>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FP32 ? 4 : 2))) void k_server(
@@ -724,7 +724,7 @@ int tpm_server_create(int32_t precision, double idle_ms, tpm_server **out) {
         hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, s->device) !=
             hipSuccess)
         rc = TPM_EDEVICE;
-    // Two wavefronts per SIMD each: FP32 (80 VGPRs) and FP64 (170) then fit
+    // Two wavefronts per SIMD each: FP32 (76 VGPRs) and FP64 (105) then fit
     // in a SIMD's registers beside each other (and four blocks of 32 KiB in
     // a CU's LDS); kernels of other work (builds of newly admitted systems)
     // run when the servers drain or idle.  Measured on the serving mix of 16

