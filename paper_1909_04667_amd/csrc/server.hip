@@ -172,8 +172,11 @@ __device__ __forceinline__ uint32_t phase_items(uint32_t n, uint32_t n_act, uint
     case kPhCompact: return (n + kSrvTile - 1) / kSrvTile;
     case kPhPm:
     case kPhNorm: return (nuniq + kSrvSlots - 1) / kSrvSlots;
-    default: return (variant >> 5) == kSplitWalk ? nuniq            // one target per item
-                                                 : (nuniq + 63) / 64;  // 64 per item
+    // An item walks all shares of its targets: other requests fill the chip,
+    // and a wavefront per share would repeat the upper tree's steps (burst
+    // capacity of the 16-system mix 5.2e7 against 6.2e7 evals/s).
+    default:
+        return walk_waves((Variant)(variant >> 5), nuniq, 1u);
     }
 }
 
@@ -371,18 +374,18 @@ __device__ __forceinline__ void srv_group(const WalkArgs &A, uint32_t g, uint32_
                                           WaveLds *Q) {
     if constexpr (FP32) {
         if (var == kSplitWalk)
-            walk_lanes32<PER, TPM, OPEN, false, MIXED, true>(A, g, 1u, Q->front);
+            walk_lanes32<kWhole, PER, TPM, OPEN, false, MIXED, true>(A, g, 1u, Q->front);
         else if (var == kLaneWalk)
-            walk_lanes32<PER, TPM, OPEN, false, MIXED>(A, g, 1u);
+            walk_lanes32<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, 1u, nullptr, &Q->parts);
         else
-            walk_group32<PER, TPM, OPEN, false, MIXED>(A, g);
+            walk_group32<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, &Q->parts);
     } else {
         if (var == kSplitWalk)
-            walk_lanes64<PER, TPM, OPEN, false, MIXED, true>(A, g, 1u, Q->front);
+            walk_lanes64<kWhole, PER, TPM, OPEN, false, MIXED, true>(A, g, 1u, Q->front);
         else if (var == kLaneWalk)
-            walk_lanes64<PER, TPM, OPEN, false, MIXED>(A, g, 1u);
+            walk_lanes64<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, 1u, nullptr, &Q->d.parts);
         else
-            walk_group64<PER, TPM, OPEN, false, MIXED>(A, g, &Q->q);
+            walk_group64<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, &Q->d.q, &Q->d.parts);
     }
 }
 
@@ -486,7 +489,7 @@ __device__ __forceinline__ void item_output(const SrvReq &R, uint32_t it) {
     }
 }
 
-// Both instances inline every walk variant (FP32: 76 VGPRs, FP64: 105, no
+// Both instances inline every walk variant (FP32: 77 VGPRs, FP64: 108, no
 // spills); each is launched with two wavefronts per SIMD.
 template <bool FP32>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FP32 ? 4 : 2))) void k_server(
@@ -724,8 +727,8 @@ int tpm_server_create(int32_t precision, double idle_ms, tpm_server **out) {
         hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, s->device) !=
             hipSuccess)
         rc = TPM_EDEVICE;
-    // Two wavefronts per SIMD each: FP32 (76 VGPRs) and FP64 (105) then fit
-    // in a SIMD's registers beside each other (and four blocks of 32 KiB in
+    // Two wavefronts per SIMD each: FP32 (77 VGPRs) and FP64 (108) then fit
+    // in a SIMD's registers beside each other (and four blocks of 34 KiB in
     // a CU's LDS); kernels of other work (builds of newly admitted systems)
     // run when the servers drain or idle.  Measured on the serving mix of 16
     // systems: burst capacity 6.3e7 evals/s against 5.0e7 with three FP32
@@ -846,6 +849,8 @@ int submit_impl(tpm_server *s, tpm_ctx *c, bool step, int32_t opening, int64_t n
     s->free_slots.pop_back();
     SrvReq R{};
     wk::fill_args(c, step ? (const double *)c->srv_an.p : anorm, w, R.A);
+    const wk::Variant variant = wk::walk_variant(c, n_act);
+    wk::set_shares(c, n_act, variant, R.A);
     R.A.coherent = 1u;  // later items of the request read the results in this kernel
     R.idx = idx;
     R.rank = (const int32_t *)c->rank.p;
@@ -859,7 +864,7 @@ int submit_impl(tpm_server *s, tpm_ctx *c, bool step, int32_t opening, int64_t n
     R.epoch = w.epoch;
     R.clear = w.clear ? 1u : 0u;
     R.variant = (opening == TPM_OPEN_REL ? 1u : 0u) | (c->P.pm_grid > 0 ? 2u : 0u) |
-                ((uint32_t)wk::walk_variant(c, n_act) << 5) | (c->P.periodic ? 8u : 0u) |
+                ((uint32_t)variant << 5) | (c->P.periodic ? 8u : 0u) |
                 (c->mixed ? 16u : 0u);
     R.flags = (step ? kStep : 0u) | (mesh ? kMesh : 0u);
     if (mesh) {

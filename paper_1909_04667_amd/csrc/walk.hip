@@ -30,7 +30,7 @@ using namespace wk;
 // With a cutoff held to 64 VGPRs (66 without the bound): eight wavefronts per
 // SIMD, 7.18 -> 6.64 ms for the geometric pass over 128^3 clustered particles
 // (six where potentials or individual softening need more registers).
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!TPM ? 4 : POT || MIXED ? 6 : 8))) void
 k_walk64(const WalkArgs A) {
     IQ64 *Q = nullptr;  // the interaction queue, with a cutoff
@@ -38,40 +38,44 @@ k_walk64(const WalkArgs A) {
         __shared__ IQ64 q[kBlock / 64];
         Q = &q[threadIdx.x >> 6];
     }
-    walk_group64<PER, TPM, OPEN, POT, MIXED>(A, wave_id(), Q);
+    walk_group64<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), Q);
 }
 
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk32(const WalkArgs A) {
-    walk_group32<PER, TPM, OPEN, POT, MIXED>(A, wave_id());
+    walk_group32<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id());
 }
 
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk64i(const WalkArgs A, uint32_t K) {
-    walk_lanes64<PER, TPM, OPEN, POT, MIXED>(A, wave_id(), K);
+    walk_lanes64<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), K);
 }
 
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk32i(const WalkArgs A, uint32_t K) {
-    walk_lanes32<PER, TPM, OPEN, POT, MIXED>(A, wave_id(), K);
+    walk_lanes32<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), K);
 }
 
-// Sparse active sets with a cutoff: a census counts the compact groups
-// (group_compact), then one of two launches walks every group -- with the
-// shared cursor when at least half of the groups are compact (a set of dense
-// clumps, as the deepest time bins are), with independent lanes otherwise;
-// the other launch returns at once.  The two walks give the same results.
-// Measured on the clustered 256^3 box, FP32 relative walk, against lanes for
-// every sparse set: the densest 1 % 1.17 against 1.65 ms, the densest 10 %
-// 3.81 against 4.44, random 1 % and 10 % unchanged (lanes: 1.66, 6.18).
+// Sparse active sets: a census counts the compact groups (group_compact),
+// then one of two launches walks every group -- with the shared cursor when
+// at least half of the groups are compact (a set of dense clumps, as the
+// deepest time bins are), with independent lanes otherwise; the other launch
+// returns at once.  The two walks give the same results.
+// Measured, relative walk, shared cursor against lanes (both in shares).
+// Clustered 256^3 box, FP32: the densest 1 % 0.58 against 0.93 ms, random 3 %
+// of 128^3 1.00 against 0.71.  Hernquist sphere of 2^20, FP32: the densest 10 %
+// 0.80 against 1.55, the densest 2 % 0.63 against 1.11, random 20 % 1.03
+// against 1.46, 10 % 0.97 against 1.16, 7 % 1.06 against 1.03, 5 % 0.98 against
+// 0.76; of 2^18 (eight shares) random 20 % 0.54 against 0.71, 10 % 0.63 against
+// 0.47.
 // (Choosing per group inside one kernel made its lane walk slower: 7.6
-// against 6.0 ms on the random 10 %.)
-template <bool PER>
+// against 6.0 ms on a random 10 % of the box.)
+template <bool PER, bool TPM>
 __global__ __launch_bounds__(kBlock) void k_census(const WalkArgs A, uint32_t *census) {
     const uint32_t wave = wave_id();
     if (wave * 64u >= load_count(A.nuniq))
         return;
-    if (group_compact<PER>(A, wave) && (threadIdx.x & 63) == 0)
+    if (group_compact<PER, TPM>(A, wave) && (threadIdx.x & 63) == 0)
         atomicAdd(census, 1u);
 }
 
@@ -80,43 +84,49 @@ __device__ __forceinline__ bool mostly_compact(const WalkArgs &A) {
     return 2ull * load_count(A.census) >= groups;
 }
 
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(POT || MIXED ? 6 : 8))) void
+template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!TPM ? 4 : POT || MIXED ? 6 : 8))) void
 k_walk64m(const WalkArgs A) {
-    __shared__ IQ64 q[kBlock / 64];
+    IQ64 *Q = nullptr;
+    if constexpr (TPM) {
+        __shared__ IQ64 q[kBlock / 64];
+        Q = &q[threadIdx.x >> 6];
+    }
     if (mostly_compact(A))
-        walk_group64<PER, TPM, OPEN, POT, MIXED>(A, wave_id(), &q[threadIdx.x >> 6]);
+        walk_group64<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), Q);
 }
 
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk64im(const WalkArgs A) {
     if (!mostly_compact(A))
-        walk_lanes64<PER, TPM, OPEN, POT, MIXED>(A, wave_id(), 1u);
+        walk_lanes64<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), 1u);
 }
 
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk32m(const WalkArgs A) {
     if (mostly_compact(A))
-        walk_group32<PER, TPM, OPEN, POT, MIXED>(A, wave_id());
+        walk_group32<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id());
 }
 
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk32im(const WalkArgs A) {
     if (!mostly_compact(A))
-        walk_lanes32<PER, TPM, OPEN, POT, MIXED>(A, wave_id(), 1u);
+        walk_lanes32<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), 1u);
 }
 
 // one wavefront per target (sparse active sets)
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk64s(const WalkArgs A) {
     __shared__ uint32_t front[kBlock / 64][kFrontWords];
-    walk_lanes64<PER, TPM, OPEN, POT, MIXED, true>(A, wave_id(), 1u, front[threadIdx.x >> 6]);
+    walk_lanes64<kWhole, PER, TPM, OPEN, POT, MIXED, true>(A, wave_id(), 1u,
+                                                              front[threadIdx.x >> 6]);
 }
 
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk32s(const WalkArgs A) {
     __shared__ uint32_t front[kBlock / 64][kFrontWords];
-    walk_lanes32<PER, TPM, OPEN, POT, MIXED, true>(A, wave_id(), 1u, front[threadIdx.x >> 6]);
+    walk_lanes32<kWhole, PER, TPM, OPEN, POT, MIXED, true>(A, wave_id(), 1u,
+                                                              front[threadIdx.x >> 6]);
 }
 
 // ---- active set -> slots in curve order --------------------------------------
@@ -137,8 +147,9 @@ template <typename T>
 __global__ __launch_bounds__(kBlock) void k_output(
     const int32_t *__restrict__ idx, int64_t n_act, int64_t n, const int32_t *__restrict__ rank,
     const uint32_t *__restrict__ slot, const uint32_t *__restrict__ nuniq,
-    const T *__restrict__ res, const T *__restrict__ rpot, T *__restrict__ acc,
-    T *__restrict__ pot, uint32_t *__restrict__ nint, uint32_t *__restrict__ err) {
+    const T *__restrict__ res, const T *__restrict__ rpot, uint32_t shares, uint32_t plane,
+    T *__restrict__ acc, T *__restrict__ pot, uint32_t *__restrict__ nint,
+    uint32_t *__restrict__ err) {
     int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= n_act)
         return;
@@ -160,13 +171,26 @@ __global__ __launch_bounds__(kBlock) void k_output(
     const uint32_t rk = (uint32_t)rank[i];
     const uint32_t sl = *nuniq == (uint32_t)n ? rk : slot[rk];
     const T *r = res + 4 * (size_t)sl;
-    acc[k] = r[0];
-    acc[n_act + k] = r[1];
-    acc[2 * n_act + k] = r[2];
-    if (pot)
-        pot[k] = rpot[sl];
+    T v0 = r[0], v1 = r[1], v2 = r[2];
+    uint32_t c = count_of(r[3]);
+    for (uint32_t p = 1; p < shares; p++) {  // the shares of the walk, in order
+        r = res + 4 * ((size_t)p * plane + sl);
+        v0 += r[0];
+        v1 += r[1];
+        v2 += r[2];
+        c += count_of(r[3]);
+    }
+    acc[k] = v0;
+    acc[n_act + k] = v1;
+    acc[2 * n_act + k] = v2;
+    if (pot) {
+        T v = rpot[sl];
+        for (uint32_t p = 1; p < shares; p++)
+            v += rpot[(size_t)p * plane + sl];
+        pot[k] = v;
+    }
     if (nint)
-        nint[k] = count_of(r[3]);
+        nint[k] = c;
 }
 
 template <typename T>
@@ -199,6 +223,8 @@ struct Launch {
     Variant variant;
     uint32_t K;       // slots per lane (lane-independent walk)
     unsigned blocks;
+    unsigned lane_blocks;    // kGroupOrLanes: of the lane walk
+    unsigned census_blocks;  // and of the census
 };
 
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
@@ -214,21 +240,32 @@ void launch_walk(const WalkArgs &A, const Launch &L, hipStream_t st) {
         else
             k_walk64i<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A, L.K);
     } else if (L.variant == kGroupOrLanes) {
-        if constexpr (TPM) {  // chosen only with a cutoff
-            k_census<PER><<<L.blocks, kBlock, 0, st>>>(A, (uint32_t *)A.census);
-            if (L.fp32) {
-                k_walk32m<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
-                k_walk32im<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
-            } else {
-                k_walk64m<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
-                k_walk64im<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
-            }
+        k_census<PER, TPM><<<L.census_blocks, kBlock, 0, st>>>(A, (uint32_t *)A.census);
+        if (L.fp32) {
+            if (A.shares > 1u)
+                k_walk32m<true, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+            else
+                k_walk32m<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+            k_walk32im<PER, TPM, OPEN, POT, MIXED><<<L.lane_blocks, kBlock, 0, st>>>(A);
+        } else {
+            if (A.shares > 1u)
+                k_walk64m<true, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+            else
+                k_walk64m<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+            k_walk64im<PER, TPM, OPEN, POT, MIXED><<<L.lane_blocks, kBlock, 0, st>>>(A);
         }
     } else {
-        if (L.fp32)
-            k_walk32<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
-        else
-            k_walk64<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+        if (L.fp32) {
+            if (A.shares > 1u)
+                k_walk32<true, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+            else
+                k_walk32<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+        } else {
+            if (A.shares > 1u)
+                k_walk64<true, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+            else
+                k_walk64<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+        }
     }
 }
 
@@ -283,8 +320,8 @@ int work_of_ctx(tpm_ctx *c, bool results, Work &w) {
     TPM_TRY(ensure(c, c->scan_tmp, (size_t)compaction_tiles(n) * 4));
     if (results) {
         const size_t esz = c->P.precision == TPM_FP32 ? 4 : 8;
-        TPM_TRY(ensure(c, c->res, (size_t)4 * n * esz));
-        TPM_TRY(ensure(c, c->rpot, (size_t)n * esz));
+        TPM_TRY(ensure(c, c->res, (size_t)4 * result_slots(n) * esz));
+        TPM_TRY(ensure(c, c->rpot, (size_t)result_slots(n) * esz));
     }
     w = Work{};
     w.mark = (uint32_t *)c->mark.p;
@@ -324,11 +361,9 @@ int select_active(tpm_ctx *c, int64_t n_act, const int32_t *idx) {
 }
 
 // Walk variant.  Independent lanes (results identical to the shared cursor)
-// for sparse active sets, whose groups are too spread out for a shared cursor
-// (it would visit the union of their walks), and for FP64 TreePM of isolated
-// systems (their outer groups span many cutoff radii, and the FP64
-// interaction is costly); the shared cursor otherwise (measured on the 128^3
-// box and the Hernquist sphere).  One wavefront per target for active sets
+// for sparse active sets whose groups are too spread out for a shared cursor
+// (it would visit the union of their walks); the shared cursor otherwise.
+// One wavefront per target for active sets
 // of at most 4096 targets, and of at most 65536 in trees of 2^22 particles or
 // more: with that few wavefronts a lane's serial walk (the longest, which
 // grows with the tree) is the critical path, while the frontier walk spreads
@@ -349,14 +384,39 @@ Variant wk::walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok) {
     const int64_t targets = std::min<int64_t>(n_act, c->n);
     if (targets <= 4096 || (targets <= 65536 && c->n >= (int64_t(1) << 22)))
         return kSplitWalk;
-    const bool fp64_iso_tpm =
-        c->P.precision == TPM_FP64 && c->P.pm_grid > 0 && !c->P.periodic;
-    if (fp64_iso_tpm)
-        return kLaneWalk;
     if (4 * n_act >= c->n)
         return kGroupWalk;
     // a sparse set: with a cutoff, as the census of its groups decides
-    return census_ok && c->P.pm_grid > 0 ? kGroupOrLanes : kLaneWalk;
+    return census_ok ? kGroupOrLanes : kLaneWalk;
+}
+
+// Shares of a walk over t targets (walk_device.h): with groups of 64, t
+// targets keep t / 64 of the chip's 8192 wavefront slots, each for the latency
+// of a serial walk (some 400 ns a step at one wavefront per SIMD), so small
+// sets are divided until the slots fill.  Milliseconds of the geometric and the
+// relative pass for 1, 2, 4, 8, 16 shares:
+//   Hernquist 10,000, FP64     1.00 .49 | .67 .35 | .47 .26 | .31 .20 | .26 .18
+//   Hernquist 50,000, FP64     1.33 .74 | .99 .62 | .70 .46 | .64 .47 | .76 .64
+//   clustered 40^3, FP32        .47 .66 | .33 .42 | .28 .32 | .28 .30 | .33 .35
+//   Hernquist 100,000, FP64    1.87 1.66 | 1.41 1.17 | 1.14 .84 | 1.17 .78
+//   densest 1 % of 256^3, FP32  1.17 | .73 | .62 | .62 (relative pass)
+//   clustered 64^3, FP32        .68 .92 | .63 .78 | .69 .84
+//   Hernquist 2^18, FP32       1.20 1.02 | 1.25 .80 | 1.46 .80
+//   Zel'dovich 64^3, FP32       .32 .31 | .34 .32 | .39 .37
+// Blocks of entries give each share some of a group's dense neighbourhood: 256
+// entries in a periodic box, where the cutoff bounds the neighbourhood (128
+// and 512: within 10 %), an isolated tree's entries over 128, 256 to 4096
+// (Hernquist 50,000 in FP64: blocks of 256, 512, 1024, 2048 give 1.15, 1.02,
+// .98, 1.19 ms for both passes).
+void wk::set_shares(const tpm_ctx *c, int64_t n_act, Variant v, WalkArgs &A) {
+    const int64_t t = std::min<int64_t>(n_act, c->n);
+    A.shares_log = v == kSplitWalk ? 0u : t <= 65536 ? (c->P.precision == TPM_FP32 ? 3u : 2u) : t <= 196608 ? 2u : t <= 262144 ? 1u : 0u;
+    A.shares = 1u << A.shares_log;
+    A.share_shift = 8;
+    if (!c->P.periodic)
+        while (A.share_shift < 12u && (c->E >> (A.share_shift + 7)) > 1)
+            A.share_shift++;
+    A.plane = (uint32_t)t;
 }
 
 void wk::fill_args(tpm_ctx *c, const double *anorm, const Work &w, WalkArgs &A) {
@@ -459,6 +519,7 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
     // lane-independent walks pay off where the interaction is expensive and
     // the wavefront's union of cutoff spheres is large: FP64 with TreePM
     LA.variant = walk_variant(c, n_act, true);
+    set_shares(c, n_act, LA.variant, A);
     if (LA.variant == kGroupOrLanes) {  // the census word follows the unique count
         A.census = w.nuniq + 1;
         TPM_TRY(fill_u32(c, w.nuniq + 1, 0u, 1));
@@ -470,9 +531,13 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
         while (LA.K < 8 && groups / (2 * LA.K) >= 2 * slots_per_chip)
             LA.K *= 2;
     }
-    const int64_t waves = LA.variant == kSplitWalk ? std::min<int64_t>(n_act, n)
-                                                  : (groups + LA.K - 1) / LA.K;
-    LA.blocks = (unsigned)((waves + 3) / 4);
+    const uint32_t targets = (uint32_t)std::min<int64_t>(n_act, n);
+    uint32_t waves = walk_waves(LA.variant, targets, A.shares);
+    if (LA.variant == kLaneWalk)
+        waves = (waves + LA.K - 1) / LA.K;
+    LA.blocks = (waves + 3) / 4;
+    LA.lane_blocks = (walk_waves(kLaneWalk, targets, A.shares) + 3) / 4;
+    LA.census_blocks = (unsigned)((groups + 3) / 4);
     const bool want_pot = pot != nullptr && P.want_potential;
     const int tkind = opening == TPM_OPEN_REL ? TPM_TIMER_WALK_REL : TPM_TIMER_WALK;
     if (timed)
@@ -491,12 +556,12 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
     if (fp32)
         k_output<float><<<ob, kBlock, 0, st>>>(
             idx, n_act, n, (const int32_t *)c->rank.p, w.slot, w.nuniq, (const float *)w.res,
-            (const float *)w.rpot, (float *)acc, want_pot ? (float *)pot : nullptr,
+            (const float *)w.rpot, A.shares, A.plane, (float *)acc, want_pot ? (float *)pot : nullptr,
             nint, (uint32_t *)c->err_flag.p);
     else
         k_output<double><<<ob, kBlock, 0, st>>>(
             idx, n_act, n, (const int32_t *)c->rank.p, w.slot, w.nuniq, (const double *)w.res,
-            (const double *)w.rpot, (double *)acc, want_pot ? (double *)pot : nullptr,
+            (const double *)w.rpot, A.shares, A.plane, (double *)acc, want_pot ? (double *)pot : nullptr,
             nint, (uint32_t *)c->err_flag.p);
     TPM_LAUNCHED(c, "k_output");
     return TPM_OK;
@@ -530,14 +595,18 @@ __device__ __forceinline__ void batch_group(const WalkArgs &A, uint32_t g, uint3
                                             IQ64 *Q) {
     if constexpr (FP32) {
         if (var == kLaneWalk)
-            walk_lanes32<PER, TPM, OPEN, false, MIXED>(A, g, 1u);
+            walk_lanes32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, 1u);
+        else if (A.shares > 1u)
+            walk_group32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g);
         else
-            walk_group32<PER, TPM, OPEN, false, MIXED>(A, g);
+            walk_group32<kWhole, PER, TPM, OPEN, false, MIXED>(A, g);
     } else {
         if (var == kLaneWalk)
-            walk_lanes64<PER, TPM, OPEN, false, MIXED>(A, g, 1u);
+            walk_lanes64<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, 1u);
+        else if (A.shares > 1u)
+            walk_group64<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, Q);
         else
-            walk_group64<PER, TPM, OPEN, false, MIXED>(A, g, Q);
+            walk_group64<kWhole, PER, TPM, OPEN, false, MIXED>(A, g, Q);
     }
 }
 
@@ -753,16 +822,17 @@ int tpm_batch_launch(tpm_batch *b) {
                     ((uint32_t)walk_variant(c, p.n_act) << 5) | (c->P.periodic ? 8u : 0u) |
                     (c->mixed ? 16u : 0u);
         R.first = items[which];
-        const int64_t tg = std::min<int64_t>(p.n_act, c->n);
-        const bool split = p.n_act > 0 && walk_variant(c, p.n_act) == kSplitWalk;
+        const uint32_t tg = (uint32_t)std::min<int64_t>(p.n_act, c->n);
+        const Variant variant = walk_variant(c, p.n_act);
+        set_shares(c, p.n_act, variant, R.A);
+        const bool split = p.n_act > 0 && variant == kSplitWalk;
         if (split) {  // its own launch, after the staging below
-            Launch LA{c->P.precision == TPM_FP32, kSplitWalk, 1u,
-                      (unsigned)((tg + 3) / 4)};
+            Launch LA{c->P.precision == TPM_FP32, kSplitWalk, 1u, (tg + 3) / 4, 0u, 0u};
             own.push_back({R.A, LA, p.opening, c->mixed != 0, c->P.periodic != 0,
                            c->P.pm_grid > 0});
         }
-        const int64_t groups = (p.n_act > 0 && !split) ? (tg + 63) / 64 : 0;
-        items[which] += (uint32_t)groups;
+        if (p.n_act > 0 && !split)
+            items[which] += walk_waves(variant, tg, R.A.shares);
         nreq[which]++;
     }
     BHIP(b, hipMemcpyAsync(b->dev, b->host, np * sizeof(BatchReq), hipMemcpyHostToDevice,
@@ -796,20 +866,22 @@ int tpm_batch_launch(tpm_batch *b) {
         BHIP(b, hipGetLastError());
     }
     // outputs in each request's caller order
-    for (const auto &p : b->pend) {
+    for (size_t o = 0; o < np; o++) {
+        const auto &p = b->pend[order[o]];
         if (p.n_act == 0)
             continue;
         tpm_ctx *c = p.c;
+        const uint32_t shares = b->host[o].A.shares, plane = b->host[o].A.plane;
         const unsigned ob = grid_for(p.n_act, kBlock);
         if (c->P.precision == TPM_FP32)
             k_output<float><<<ob, kBlock, 0, b->stream>>>(
                 p.idx, p.n_act, c->n, (const int32_t *)c->rank.p, (const uint32_t *)c->slot.p,
-                (const uint32_t *)c->counters.p + 40, (const float *)c->res.p, (const float *)c->rpot.p, (float *)p.acc, nullptr,
+                (const uint32_t *)c->counters.p + 40, (const float *)c->res.p, (const float *)c->rpot.p, shares, plane, (float *)p.acc, nullptr,
                 p.nint, (uint32_t *)c->err_flag.p);
         else
             k_output<double><<<ob, kBlock, 0, b->stream>>>(
                 p.idx, p.n_act, c->n, (const int32_t *)c->rank.p, (const uint32_t *)c->slot.p,
-                (const uint32_t *)c->counters.p + 40, (const double *)c->res.p, (const double *)c->rpot.p, (double *)p.acc, nullptr,
+                (const uint32_t *)c->counters.p + 40, (const double *)c->res.p, (const double *)c->rpot.p, shares, plane, (double *)p.acc, nullptr,
                 p.nint, (uint32_t *)c->err_flag.p);
         BHIP(b, hipGetLastError());
     }

@@ -52,6 +52,11 @@ struct WalkArgs {
     // set by the resident server, whose later work items read them inside
     // the same kernel; other launches store plainly (visible at kernel end)
     uint32_t coherent;
+    // Shares of a target's walk (a power of two; 1: the whole walk in one
+    // piece).  See owns() below.
+    uint32_t shares, shares_log;
+    uint32_t share_shift;  // log2 of the entries of a block
+    uint32_t plane;        // slots per share in res and rpot
 };
 
 // Wavefront masks: ballot of a lane predicate, and a mask read back as the
@@ -432,6 +437,13 @@ __device__ __forceinline__ Rec32 uniform_rec32(const Rec32 *R, uint32_t i) {
     return r;
 }
 
+// The skip pointer of record i alone.
+template <typename Rec>
+__device__ __forceinline__ uint32_t uniform_skip(const Rec *R, uint32_t i) {
+    typedef __attribute__((address_space(4))) const uint32_t cword;
+    return *(cword *)&R[i].skip;
+}
+
 template <typename T>
 __device__ __forceinline__ T uniform_at(const void *p, uint32_t i) {
     typedef __attribute__((address_space(4))) const T cval;
@@ -448,19 +460,96 @@ __device__ __forceinline__ const T *uniform_ptr(const void *p) {
     return (const T *)(((uint64_t)hi << 32) | lo);
 }
 
+// A target's walk may be divided into A.shares shares, each the work of its own
+// wavefront (group walk) or lane (lane walk), so that a set of few targets
+// fills the chip.  The tree is cut into subtrees of at most 2^share_shift
+// entries, as large as the walk meets them from the root, and a subtree
+// belongs to the share that the block of 2^share_shift entries with its
+// first entry is dealt to.  A share walks its own subtrees and steps over the
+// others; larger cubes are decided by every share, and accepted by the one
+// their own entry belongs to.  A share's sum runs in depth-first order, and the
+// target's total is share 0 + share 1 + ... whoever walked them, so group
+// and lane walks of the same set agree bit for bit.
+__device__ __forceinline__ bool owns(const WalkArgs &A, uint32_t e, uint32_t share) {
+    return ((e >> A.share_shift) & (A.shares - 1u)) == share;
+}
+
+// All ones for equal shares, none otherwise (on the scalar unit).
+__device__ __forceinline__ uint64_t equal_mask(uint32_t a, uint32_t b) {
+    const uint32_t m = (uint32_t)((int32_t)((a ^ b) - 1u) >> 31);
+    return ((uint64_t)m << 32) | m;
+}
+
+// Who walks a target's shares.
+enum Shares : int {
+    kWhole = 0,      // the walk is not divided
+    kOneShare = 1,   // each wavefront (lane) one share; the output adds them
+    kAllShares = 2,  // one wavefront (lane) all of them in one pass, each with its
+                     // own sum in LDS: the same total without the divided
+                     // walks' repeated steps (the resident server, whose other
+                     // requests fill the chip).  No potentials.
+};
+constexpr uint32_t kMaxShares32 = 8, kMaxShares64 = 4;
+
+// The shares' sums of a wavefront's lanes (kAllShares): the current share's in
+// the walk's registers, the others' here.
+template <typename T>
+struct Parts {
+    static constexpr uint32_t kMax = sizeof(T) == 4 ? kMaxShares32 : kMaxShares64;
+    T v[kMax][3][64];
+};
+template <typename T>
+__device__ __forceinline__ void parts_clear(Parts<T> *P, uint32_t shares) {
+    const int lane = threadIdx.x & 63;
+    for (uint32_t p = 0; p < shares; p++)
+        P->v[p][0][lane] = P->v[p][1][lane] = P->v[p][2][lane] = (T)0;
+}
+// From share cs's sums in a0 .. a2 to share sh's.
+template <typename T>
+__device__ __forceinline__ void parts_switch(Parts<T> *P, uint32_t &cs, uint32_t sh, T &a0, T &a1,
+                                             T &a2) {
+    const int lane = threadIdx.x & 63;
+    P->v[cs][0][lane] = a0;
+    P->v[cs][1][lane] = a1;
+    P->v[cs][2][lane] = a2;
+    a0 = P->v[sh][0][lane];
+    a1 = P->v[sh][1][lane];
+    a2 = P->v[sh][2][lane];
+    cs = sh;
+}
+// share 0 + share 1 + ...
+template <typename T>
+__device__ __forceinline__ void parts_total(Parts<T> *P, uint32_t cs, uint32_t shares, T &a0,
+                                            T &a1, T &a2) {
+    const int lane = threadIdx.x & 63;
+    parts_switch(P, cs, 0u, a0, a1, a2);
+    for (uint32_t p = 1; p < shares; p++) {
+        a0 += P->v[p][0][lane];
+        a1 += P->v[p][1][lane];
+        a2 += P->v[p][2][lane];
+    }
+}
+
 // Side of a level-`lev` cube, scaled from the root side through the exponent
 // field (exact: the root side is a normal number and lev <= 21).
 __device__ __forceinline__ double scale_level(double v, uint32_t lev) {
     return __longlong_as_double(__double_as_longlong(v) - ((long long)lev << 52));
 }
 
-// One wavefront walks group `wave` (slots 64 wave .. 64 wave + 63).  The
+// One wavefront walks one share of a group (item = group x shares + share;
+// slots 64 group .. 64 group + 63).  The
 // cursor and the entry are wavefront-uniform; each lane decides for itself
 // (as masks) and only branches on wavefront-uniform conditions are taken.
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
-__device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, IQ64 *Q) {
+template <int SHARES, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+__device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t item, IQ64 *Q,
+                                             Parts<double> *P = nullptr) {
+    constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
+    static_assert(!(ALL && POT), "");
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
+    const uint32_t it = __builtin_amdgcn_readfirstlane(item);
+    const uint32_t share = SHARED ? it & (A.shares - 1u) : 0u;
+    const uint32_t wave = SHARED ? it >> A.shares_log : it;  // the group
     if (wave * 64u >= nu)
         return;  // whole wavefront
     const uint32_t slot = wave * 64u + lane;
@@ -477,6 +566,7 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
     // to the skip pointer only when the lane accepts or discards a cube)
     uint32_t next = valid ? 0u : 0xffffffffu;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, pot = 0.0;
+    uint32_t cs = 0, sh = 0;  // kAllShares: the share in a0 .. a2, the entry's share
     uint32_t nint = 0;
     const Rec64 *__restrict__ R = uniform_ptr<Rec64>(A.rec);
 
@@ -511,7 +601,7 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
     }
 
     // queue state: pending pairs and steps, and lane j's mask of step j
-    uint32_t qn = 0, ns = 0, svl = 0, svh = 0;
+    uint32_t qn = 0, ns = 0, svl = 0, svh = 0, svs = 0;  // svs: lane j, the share of step j
     // evaluate the pending pairs, then add them to their targets
     auto flush = [&]() {
         wave_sync();
@@ -546,12 +636,22 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
             b += (uint32_t)__builtin_popcountll(m1);
             const double2 xy0 = Q->xy[i0], zm0 = Q->zm[i0], xy1 = Q->xy[i1], zm1 = Q->zm[i1];
             const double h0 = POT ? Q->h[i0] : 0.0, h1 = POT ? Q->h[i1] : 0.0;
+            if (ALL) {
+                const uint32_t s0 = __builtin_amdgcn_readlane(svs, j);
+                if (s0 != cs)
+                    parts_switch(P, cs, s0, a0, a1, a2);
+            }
             if (lane_in(m0)) {
                 a0 = fma(zm0.y, xy0.x, a0);
                 a1 = fma(zm0.y, xy0.y, a1);
                 a2 = fma(zm0.y, zm0.x, a2);
                 if (POT)
                     pot += h0;
+            }
+            if (ALL && m1) {
+                const uint32_t s1 = __builtin_amdgcn_readlane(svs, j1);
+                if (s1 != cs)
+                    parts_switch(P, cs, s1, a0, a1, a2);
             }
             if (lane_in(m1)) {
                 a0 = fma(zm1.y, xy1.x, a0);
@@ -568,6 +668,8 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
     auto push = [&](uint64_t inter, double m, double d0, double d1, double d2, double dd,
                     double hp) {
         count_lanes(nint, inter);
+        if (!TPM && ALL && sh != cs)
+            parts_switch(P, cs, sh, a0, a1, a2);
         if (!TPM) {  // evaluate at once (fma(0, d, a) == a for the other lanes)
             double fac, phi;
             factor64<TPM, POT, MIXED>(A, inter, m, dd, hp, fac, phi);
@@ -590,6 +692,8 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
             if (MIXED)
                 Q->h[p] = hp;
         }
+        if (ALL)
+            svs = writelane_u32(sh, ns, svs);
         svl = writelane_u32((uint32_t)inter, ns, svl);
         svh = writelane_u32((uint32_t)(inter >> 32), ns, svh);
         qn += k;
@@ -616,84 +720,114 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t wave, I
     // scalar operands (no moves, 117 -> 64 VGPRs, four -> eight wavefronts per
     // SIMD), wraps skipped where no lane needs one, step masks in a register
     // and the queue's sums under the lanes' mask instead of selects.
+    uint64_t own = ~0ull;  // all ones: entries are accepted here (none: another share's)
+    bool dealt = false;    // a cube larger than a block: its particles are dealt out
+    if (ALL)
+        parts_clear(P, A.shares);
     uint32_t c = 0;
     while (c < A.E) {
-        const uint32_t cu = __builtin_amdgcn_readfirstlane(c);
-        const Rec64 r = uniform_rec(R, cu);
-        const uint64_t mine = wave_mask(next <= cu);
-        if (r.meta & kParticleFlag) {
-            particle(r, cu, mine);
-            c = cu + 1u;
-            continue;
+        // the whole walk, or the next stretch of it that belongs to one share
+        uint32_t end = A.E;
+        if (SHARES != kWhole && A.shares > 1u) {
+            const uint32_t cu = __builtin_amdgcn_readfirstlane(c);
+            const uint32_t skip = uniform_skip(R, cu);
+            dealt = skip - cu > 1u << A.share_shift;
+            sh = (cu >> A.share_shift) & (A.shares - 1u);
+            if (SHARED) {
+                if (!dealt && sh != share) {
+                    c = skip;
+                    continue;
+                }
+                own = equal_mask(sh, share);
+            }
+            end = dealt ? cu + 1u : skip;
         }
-        const double he = MIXED ? uniform_at<double>(A.eh, cu) : 0.0;
-        const double hp = hi > he ? hi : he;  // the larger support
-        const uint32_t lev = r.meta & 0xffu;
-        double c0 = r.cen[0] - x0, c1 = r.cen[1] - x1, c2 = r.cen[2] - x2;
-        wrap3<PER>(c0, c1, c2, A.box, A.half);
-        uint64_t keep = mine;  // lanes here that do not discard the cube
-        if (TPM) {
-            const double hl = scale_level(A.hlr, lev);
-            const double e0 = fmax(fabs(c0) - hl, 0.0), e1 = fmax(fabs(c1) - hl, 0.0),
-                         e2 = fmax(fabs(c2) - hl, 0.0);
-            keep &= wave_mask(!(fma(e0, e0, fma(e1, e1, e2 * e2)) > A.rc2));
-            if (!keep) {  // every lane here discards the cube
-                next = lane_in(mine) ? r.skip : next;
-                c = r.skip;
+        while (c < end) {
+            const uint32_t cu = __builtin_amdgcn_readfirstlane(c);
+            const Rec64 r = uniform_rec(R, cu);
+            const uint64_t mine = wave_mask(next <= cu);
+            if (r.meta & kParticleFlag) {
+                particle(r, cu, mine);
+                c = cu + 1u;
                 continue;
             }
-        }
-        double d0 = r.com[0] - x0, d1 = r.com[1] - x1, d2 = r.com[2] - x2;
-        wrap3<PER>(d0, d1, d2, A.box, A.half);
-        const double dd = fma(d0, d0, fma(d1, d1, d2 * d2));
-        const double L2 = scale_level(scale_level(A.L2r, lev), lev);
-        uint64_t open;
-        if (OPEN == TPM_OPEN_BH)
-            open = wave_mask(L2 > A.theta2 * dd);
-        else
-            open = wave_mask((A.G * r.mass) * L2 > alpha_an * (dd * dd));
-        const double lim = scale_level(A.limr, lev);
-        open |= wave_mask(fabs(c0) < lim) & wave_mask(fabs(c1) < lim) &
-                wave_mask(fabs(c2) < lim);
-        // larger softening inside the node, target within it of the
-        // centre of mass: open (Sec. 3.2)
-        if (MIXED)
-            open |= wave_mask(hi < he) & wave_mask(dd < he * he);
-        const uint64_t desc = keep & open;
-        next = lane_in(mine & ~desc) ? r.skip : next;
-        if (keep != desc)
-            push(keep & ~open, r.mass, d0, d1, d2, dd, hp);
-        c = desc ? cu + 1u : r.skip;
-        if (TPM && desc && (r.meta & kLeafParentFlag) && prefilter) {
-            // an opened leaf parent (with the prefilter): its particle
-            // children walked here
-            const uint32_t end = r.skip;
-            for (uint32_t base = cu + 1u; base < end; base += 64u) {
-                const uint32_t k = end - base;
-                // (lanes past the run test its last particle again)
-                const double *t = R[base + min((uint32_t)lane, k - 1u)].com;
-                const double p0 = wrap64<PER>(t[0] - xr0, A.box, A.half);
-                const double p1 = wrap64<PER>(t[1] - xr1, A.box, A.half);
-                const double p2 = wrap64<PER>(t[2] - xr2, A.box, A.half);
-                const double g0 = fmax(fmax(lo0 - p0, p0 - hi0), 0.0);
-                const double g1 = fmax(fmax(lo1 - p1, p1 - hi1), 0.0);
-                const double g2 = fmax(fmax(lo2 - p2, p2 - hi2), 0.0);
-                uint64_t m = wave_mask(fma(g0, g0, fma(g1, g1, g2 * g2)) < A.pf2);
-                if (k < 64u)
-                    m &= (1ull << k) - 1u;
-                while (m) {
-                    const uint32_t e = base + (uint32_t)__builtin_ctzll(m);
-                    m &= m - 1;
-                    particle(uniform_rec(R, e), e, desc);
+            const double he = MIXED ? uniform_at<double>(A.eh, cu) : 0.0;
+            const double hp = hi > he ? hi : he;  // the larger support
+            const uint32_t lev = r.meta & 0xffu;
+            double c0 = r.cen[0] - x0, c1 = r.cen[1] - x1, c2 = r.cen[2] - x2;
+            wrap3<PER>(c0, c1, c2, A.box, A.half);
+            uint64_t keep = mine;  // lanes here that do not discard the cube
+            if (TPM) {
+                const double hl = scale_level(A.hlr, lev);
+                const double e0 = fmax(fabs(c0) - hl, 0.0), e1 = fmax(fabs(c1) - hl, 0.0),
+                             e2 = fmax(fabs(c2) - hl, 0.0);
+                keep &= wave_mask(!(fma(e0, e0, fma(e1, e1, e2 * e2)) > A.rc2));
+                if (!keep) {  // every lane here discards the cube
+                    next = lane_in(mine) ? r.skip : next;
+                    c = r.skip;
+                    continue;
                 }
             }
-            c = end;
+            double d0 = r.com[0] - x0, d1 = r.com[1] - x1, d2 = r.com[2] - x2;
+            wrap3<PER>(d0, d1, d2, A.box, A.half);
+            const double dd = fma(d0, d0, fma(d1, d1, d2 * d2));
+            const double L2 = scale_level(scale_level(A.L2r, lev), lev);
+            uint64_t open;
+            if (OPEN == TPM_OPEN_BH)
+                open = wave_mask(L2 > A.theta2 * dd);
+            else
+                open = wave_mask((A.G * r.mass) * L2 > alpha_an * (dd * dd));
+            const double lim = scale_level(A.limr, lev);
+            open |= wave_mask(fabs(c0) < lim) & wave_mask(fabs(c1) < lim) &
+                    wave_mask(fabs(c2) < lim);
+            // larger softening inside the node, target within it of the
+            // centre of mass: open (Sec. 3.2)
+            if (MIXED)
+                open |= wave_mask(hi < he) & wave_mask(dd < he * he);
+            const uint64_t desc = keep & open;
+            next = lane_in(mine & ~desc) ? r.skip : next;
+            const uint64_t inter = SHARED ? keep & ~open & own : keep & ~open;
+            if (inter)
+                push(inter, r.mass, d0, d1, d2, dd, hp);
+            c = desc ? cu + 1u : r.skip;
+            if (TPM && desc && (r.meta & kLeafParentFlag) && prefilter) {
+                // an opened leaf parent (with the prefilter): its particle
+                // children walked here
+                const uint32_t last = r.skip;
+                for (uint32_t base = cu + 1u; base < last; base += 64u) {
+                    const uint32_t k = last - base;
+                    // (lanes past the run test its last particle again)
+                    const double *t = R[base + min((uint32_t)lane, k - 1u)].com;
+                    const double p0 = wrap64<PER>(t[0] - xr0, A.box, A.half);
+                    const double p1 = wrap64<PER>(t[1] - xr1, A.box, A.half);
+                    const double p2 = wrap64<PER>(t[2] - xr2, A.box, A.half);
+                    const double g0 = fmax(fmax(lo0 - p0, p0 - hi0), 0.0);
+                    const double g1 = fmax(fmax(lo1 - p1, p1 - hi1), 0.0);
+                    const double g2 = fmax(fmax(lo2 - p2, p2 - hi2), 0.0);
+                    uint64_t m = wave_mask(fma(g0, g0, fma(g1, g1, g2 * g2)) < A.pf2);
+                    if (k < 64u)
+                        m &= (1ull << k) - 1u;
+                    if (SHARED && dealt)
+                        m &= wave_mask(owns(A, base + (uint32_t)lane, share));
+                    while (m) {
+                        const uint32_t e = base + (uint32_t)__builtin_ctzll(m);
+                        m &= m - 1;
+                        if (ALL && dealt) {
+                            sh = (e >> A.share_shift) & (A.shares - 1u);
+                        }
+                        particle(uniform_rec(R, e), e, desc);
+                    }
+                }
+                c = last;
+            }
         }
     }
     if (TPM && qn)
         flush();
+    if (ALL)
+        parts_total(P, cs, A.shares, a0, a1, a2);
     if (valid)
-        store_result<double>(A, slot, a0, a1, a2, POT, pot, nint);
+        store_result<double>(A, (SHARED ? share * A.plane : 0u) + slot, a0, a1, a2, POT, pot, nint);
 }
 
 // ---- FP32 walk ----------------------------------------------------------------
@@ -847,11 +981,17 @@ __device__ __forceinline__ float max3_abs(float a, float b, float c) {
                                          fabsf(c));
 }
 
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
-__device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t wave) {
+template <int SHARES, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+__device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t item,
+                                             Parts<float> *P = nullptr) {
+    constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
+    static_assert(!(ALL && POT), "");
     constexpr int SH = PER ? kRecShiftPer : kRecShiftIso;
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
+    const uint32_t it = __builtin_amdgcn_readfirstlane(item);
+    const uint32_t share = SHARED ? it & (A.shares - 1u) : 0u;
+    const uint32_t wave = SHARED ? it >> A.shares_log : it;  // the group
     if (wave * 64u >= nu)
         return;
     const uint32_t slot = wave * 64u + lane;
@@ -883,6 +1023,7 @@ __device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t wave) {
     // particles included, without per-entry bookkeeping.
     uint32_t next = valid ? 0u : 0xffffffffu;
     float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, pot = 0.0f;
+    uint32_t cs = 0, sh = 0;  // kAllShares: the share in a0 .. a2, the entry's share
     uint32_t nint = 0;
     const Rec32 *__restrict__ R = uniform_ptr<Rec32>(A.rec);
 
@@ -947,85 +1088,119 @@ __device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t wave) {
     // bools carried between blocks it took 71.8 k and 51.6 k, 28.7 ms against
     // 24.6 ms now (geometric pass 25.0 -> 21.5; Hernquist sphere of 2^20 3.9 ->
     // 3.5 and 1.97 -> 1.84).
+    uint64_t own = ~0ull;  // all ones: entries are accepted here (none: another share's)
+    bool dealt = false;    // a cube larger than a block: its particles are dealt out
+    if (ALL)
+        parts_clear(P, A.shares);
     uint32_t c = 0;
     while (c < A.E) {
-        const uint32_t cu = __builtin_amdgcn_readfirstlane(c);
-        const Rec32 r = uniform_rec32(R, cu);
-        const uint64_t mine = wave_mask(next <= cu);
-        const int32_t cm = r.cx_meta;
-        if (cm & kRecParticle) {
-            particle(r, cu, mine);
-            c = cu + 1u;
-            continue;
+        // the whole walk, or the next stretch of it that belongs to one share
+        uint32_t end = A.E;
+        if (SHARES != kWhole && A.shares > 1u) {
+            const uint32_t cu = __builtin_amdgcn_readfirstlane(c);
+            const uint32_t skip = uniform_skip(R, cu);
+            dealt = skip - cu > 1u << A.share_shift;
+            sh = (cu >> A.share_shift) & (A.shares - 1u);
+            if (SHARED) {
+                if (!dealt && sh != share) {
+                    c = skip;
+                    continue;
+                }
+                own = equal_mask(sh, share);
+            }
+            if (ALL && sh != cs)
+                parts_switch(P, cs, sh, a0, a1, a2);
+            end = dealt ? cu + 1u : skip;
         }
-        const float he = MIXED ? uniform_at<float>(A.eh, cu) : 0.0f;
-        const float hp = hi > he ? hi : he;
-        // target -> centre of the cube (32-bit differences wrap modulo the
-        // periodic box), and target -> centre of mass
-        const float c0 = fmaf((float)wsub(cm & -(1 << SH), G0), A.fu, -xr0);
-        const float c1 = fmaf((float)wsub(r.cy, G1), A.fu, -xr1);
-        const float c2 = fmaf((float)wsub(r.cz, G2), A.fu, -xr2);
-        const uint32_t lev = (uint32_t)cm & kRecLevel;
-        uint64_t keep = mine;  // lanes here that do not discard the cube
-        if (TPM) {
-            const float hl = scale_level32(A.fhlr, lev);
-            const float e0 = fmaxf(fabsf(c0) - hl, 0.0f);
-            const float e1 = fmaxf(fabsf(c1) - hl, 0.0f);
-            const float e2 = fmaxf(fabsf(c2) - hl, 0.0f);
-            keep &= wave_mask(!(fmaf(e0, e0, fmaf(e1, e1, e2 * e2)) > A.frc2));
-            if (!keep) {  // every lane here discards the cube
-                next = lane_in(mine) ? r.skip : next;
-                c = r.skip;
+        while (c < end) {
+            const uint32_t cu = __builtin_amdgcn_readfirstlane(c);
+            const Rec32 r = uniform_rec32(R, cu);
+            const uint64_t mine = wave_mask(next <= cu);
+            const int32_t cm = r.cx_meta;
+            if (cm & kRecParticle) {
+                particle(r, cu, mine);
+                c = cu + 1u;
                 continue;
             }
-        }
-        const float d0 = c0 + r.dx, d1 = c1 + r.dy, d2 = c2 + r.dz;
-        const float dd = fmaf(d0, d0, fmaf(d1, d1, d2 * d2));
-        const float L2 = scale_level32(scale_level32(A.fL2r, lev), lev);
-        uint64_t open;
-        if (OPEN == TPM_OPEN_BH)
-            open = wave_mask(L2 > A.ftheta2 * dd);
-        else
-            open = wave_mask(r.gm * L2 > alpha_an * (dd * dd));
-        // box rule: the largest of |c| (NaN if one is) below the limit
-        open |= wave_mask(max3_abs(c0, c1, c2) < scale_level32(A.flimr, lev));
-        if (MIXED)
-            open |= wave_mask(hi < he) & wave_mask(dd < he * he);
-        const uint64_t desc = keep & open;
-        next = lane_in(mine & ~desc) ? r.skip : next;
-        if (keep != desc)
-            interact32_wave<TPM, POT, MIXED>(A, keep & ~open, r.gm, d0, d1, d2, dd, hp, a0, a1,
-                                             a2, pot, nint);
-        c = desc ? cu + 1u : r.skip;
-        if (TPM && desc && (cm & kRecLeafParent) && prefilter) {
-            // an opened leaf parent (with the prefilter): the children
-            // cu + 1 .. skip - 1 are particles, walked here by the lanes that
-            // opened the cube, and the cursor then moves past them
-            const uint32_t end = r.skip;
-            for (uint32_t base = cu + 1u; base < end; base += 64u) {
-                const uint32_t k = end - base;
-                // (lanes past the run test its last particle again)
-                const Rec32 t = R[base + min((uint32_t)lane, k - 1u)];
-                const float p0 = fmaf((float)wsub(t.cx_meta & -(1 << SH), Gr0), A.fu, t.dx);
-                const float p1 = fmaf((float)wsub(t.cy, Gr1), A.fu, t.dy);
-                const float p2 = fmaf((float)wsub(t.cz, Gr2), A.fu, t.dz);
-                const float g0 = fmaxf(fmaxf(lo0 - p0, p0 - hi0), 0.0f);
-                const float g1 = fmaxf(fmaxf(lo1 - p1, p1 - hi1), 0.0f);
-                const float g2 = fmaxf(fmaxf(lo2 - p2, p2 - hi2), 0.0f);
-                uint64_t m = wave_mask(fmaf(g0, g0, fmaf(g1, g1, g2 * g2)) < A.fpf2);
-                if (k < 64u)
-                    m &= (1ull << k) - 1u;
-                while (m) {
-                    const uint32_t e = base + (uint32_t)__builtin_ctzll(m);
-                    m &= m - 1;
-                    particle(uniform_rec32(R, e), e, desc);
+            const float he = MIXED ? uniform_at<float>(A.eh, cu) : 0.0f;
+            const float hp = hi > he ? hi : he;
+            // target -> centre of the cube (32-bit differences wrap modulo the
+            // periodic box), and target -> centre of mass
+            const float c0 = fmaf((float)wsub(cm & -(1 << SH), G0), A.fu, -xr0);
+            const float c1 = fmaf((float)wsub(r.cy, G1), A.fu, -xr1);
+            const float c2 = fmaf((float)wsub(r.cz, G2), A.fu, -xr2);
+            const uint32_t lev = (uint32_t)cm & kRecLevel;
+            uint64_t keep = mine;  // lanes here that do not discard the cube
+            if (TPM) {
+                const float hl = scale_level32(A.fhlr, lev);
+                const float e0 = fmaxf(fabsf(c0) - hl, 0.0f);
+                const float e1 = fmaxf(fabsf(c1) - hl, 0.0f);
+                const float e2 = fmaxf(fabsf(c2) - hl, 0.0f);
+                keep &= wave_mask(!(fmaf(e0, e0, fmaf(e1, e1, e2 * e2)) > A.frc2));
+                if (!keep) {  // every lane here discards the cube
+                    next = lane_in(mine) ? r.skip : next;
+                    c = r.skip;
+                    continue;
                 }
             }
-            c = end;
+            const float d0 = c0 + r.dx, d1 = c1 + r.dy, d2 = c2 + r.dz;
+            const float dd = fmaf(d0, d0, fmaf(d1, d1, d2 * d2));
+            const float L2 = scale_level32(scale_level32(A.fL2r, lev), lev);
+            uint64_t open;
+            if (OPEN == TPM_OPEN_BH)
+                open = wave_mask(L2 > A.ftheta2 * dd);
+            else
+                open = wave_mask(r.gm * L2 > alpha_an * (dd * dd));
+            // box rule: the largest of |c| (NaN if one is) below the limit
+            open |= wave_mask(max3_abs(c0, c1, c2) < scale_level32(A.flimr, lev));
+            if (MIXED)
+                open |= wave_mask(hi < he) & wave_mask(dd < he * he);
+            const uint64_t desc = keep & open;
+            next = lane_in(mine & ~desc) ? r.skip : next;
+            const uint64_t inter = SHARED ? keep & ~open & own : keep & ~open;
+            if (inter)
+                interact32_wave<TPM, POT, MIXED>(A, inter, r.gm, d0, d1, d2, dd, hp, a0, a1,
+                                                 a2, pot, nint);
+            c = desc ? cu + 1u : r.skip;
+            if (TPM && desc && (cm & kRecLeafParent) && prefilter) {
+                // an opened leaf parent (with the prefilter): the children
+                // cu + 1 .. skip - 1 are particles, walked here by the lanes that
+                // opened the cube, and the cursor then moves past them
+                const uint32_t last = r.skip;
+                for (uint32_t base = cu + 1u; base < last; base += 64u) {
+                    const uint32_t k = last - base;
+                    // (lanes past the run test its last particle again)
+                    const Rec32 t = R[base + min((uint32_t)lane, k - 1u)];
+                    const float p0 = fmaf((float)wsub(t.cx_meta & -(1 << SH), Gr0), A.fu, t.dx);
+                    const float p1 = fmaf((float)wsub(t.cy, Gr1), A.fu, t.dy);
+                    const float p2 = fmaf((float)wsub(t.cz, Gr2), A.fu, t.dz);
+                    const float g0 = fmaxf(fmaxf(lo0 - p0, p0 - hi0), 0.0f);
+                    const float g1 = fmaxf(fmaxf(lo1 - p1, p1 - hi1), 0.0f);
+                    const float g2 = fmaxf(fmaxf(lo2 - p2, p2 - hi2), 0.0f);
+                    uint64_t m = wave_mask(fmaf(g0, g0, fmaf(g1, g1, g2 * g2)) < A.fpf2);
+                    if (k < 64u)
+                        m &= (1ull << k) - 1u;
+                    if (SHARED && dealt)
+                        m &= wave_mask(owns(A, base + (uint32_t)lane, share));
+                    while (m) {
+                        const uint32_t e = base + (uint32_t)__builtin_ctzll(m);
+                        m &= m - 1;
+                        if (ALL && dealt) {
+                            sh = (e >> A.share_shift) & (A.shares - 1u);
+                            if (sh != cs)
+                                parts_switch(P, cs, sh, a0, a1, a2);
+                        }
+                        particle(uniform_rec32(R, e), e, desc);
+                    }
+                }
+                c = last;
+            }
         }
     }
+    if (ALL)
+        parts_total(P, cs, A.shares, a0, a1, a2);
     if (valid)
-        store_result<float>(A, slot, a0, a1, a2, POT, pot, nint);
+        store_result<float>(A, (SHARED ? share * A.plane : 0u) + slot, a0, a1, a2, POT, pot, nint);
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
@@ -1087,7 +1262,11 @@ constexpr uint32_t kFrontLeaf = 128;
 // LDS of one wavefront in kernels that run either walk: the FP64 queue or
 // the FRONT walk's frontiers.
 union WaveLds {
-    IQ64 q;
+    struct {
+        IQ64 q;
+        Parts<double> parts;
+    } d;
+    Parts<float> parts;
     uint32_t front[kFrontWords];
 };
 
@@ -1204,19 +1383,24 @@ __device__ __forceinline__ void expand_front(const Rec *__restrict__ R, uint32_t
     wave_sync();
 }
 
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED, bool FRONT = false>
+template <int SHARES, bool PER, bool TPM, int OPEN, bool POT, bool MIXED, bool FRONT = false>
 __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, uint32_t K,
-                                             uint32_t *front = nullptr) {
+                                             uint32_t *front = nullptr,
+                                             Parts<double> *P = nullptr) {
+    constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
+    static_assert(!(ALL && POT), "");
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
-    const uint32_t base = FRONT ? wave : wave * 64u * K;
+    // (kOneShare: lane l takes share l mod A.shares of a target)
+    const uint32_t T = SHARED ? 64u >> A.shares_log : 64u;  // targets at a time
+    const uint32_t base = FRONT ? wave : wave * T * K;
     if (base >= nu)
         return;
-    const uint32_t chunk_end = min(nu, base + 64u * K);
+    const uint32_t chunk_end = min(nu, base + T * K);
     const Rec64 *__restrict__ R = (const Rec64 *)A.rec;
     double x0 = 0.0, x1 = 0.0, x2 = 0.0, an = 0.0, a0 = 0.0, a1 = 0.0, a2 = 0.0, pot = 0.0,
            hi = 0.0;
-    uint32_t self = 0, nint = 0;
+    uint32_t self = 0, nint = 0, cs = 0, sh = 0;
     auto start = [&](uint32_t sl) {
         const uint32_t s = coherent_ld(A.act + sl);
         x0 = A.ps[s];
@@ -1229,10 +1413,14 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, u
             hi = A.hs[s];
         a0 = a1 = a2 = pot = 0.0;
         nint = 0;
+        if (ALL) {
+            cs = sh = 0u;
+            parts_clear(P, A.shares);
+        }
     };
     // entry e for this lane's target: the decision and the interaction, as
     // in a sequential walk; true: descend into e
-    auto visit = [&](uint32_t e, const Rec64 &r) -> bool {
+    auto visit = [&](uint32_t e, const Rec64 &r, bool owned = true) -> bool {
         const double he = MIXED ? ((const double *)A.eh)[e] : 0.0;
         const double d0 = wrap64<PER>(r.com[0] - x0, A.box, A.half);
         const double d1 = wrap64<PER>(r.com[1] - x1, A.box, A.half);
@@ -1271,7 +1459,9 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, u
             step_in = open;
             inter = !discard && !open;
         }
-        if (inter) {
+        if (inter && owned) {
+            if (ALL && sh != cs)
+                parts_switch(P, cs, sh, a0, a1, a2);
             interact64<TPM, POT, MIXED>(A, r.mass, d0, d1, d2, dd, hi > he ? hi : he, a0, a1,
                                         a2, pot);
             nint++;
@@ -1279,20 +1469,40 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, u
         return step_in;
     };
     if constexpr (!FRONT) {
-        uint32_t slot = base + lane;
+        const uint32_t share = SHARED ? (uint32_t)lane & (A.shares - 1u) : 0u;
+        const uint32_t block = 1u << A.share_shift;
+        const uint32_t own0 = SHARES != kWhole && A.shares > 1u ? 0u : 0xffffffffu;
+        uint32_t slot = base + (SHARED ? (uint32_t)lane >> A.shares_log : (uint32_t)lane);
         bool live = slot < chunk_end;
-        uint32_t e = 0;
+        uint32_t e = 0, own_end = own0;
         if (live)
             start(slot);
         while (__ballot(live)) {
             if (live) {
                 const Rec64 r = R[e];
-                e = visit(e, r) ? e + 1u : r.skip;
+                bool owned = true, over = false;
+                if (e >= own_end) {  // outside this share's subtrees
+                    const bool small = r.skip - e <= block;
+                    if (SHARED) {
+                        owned = owns(A, e, share);
+                        over = small && !owned;
+                    } else {
+                        sh = (e >> A.share_shift) & (A.shares - 1u);
+                    }
+                    own_end = small && owned ? r.skip : own_end;
+                }
+                if (over)
+                    e = r.skip;
+                else
+                    e = visit(e, r, owned) ? e + 1u : r.skip;
                 if (e >= A.E) {
-                    store_result<double>(A, slot, a0, a1, a2, POT, pot, nint);
-                    slot += 64u;
+                    if (ALL)
+                        parts_total(P, cs, A.shares, a0, a1, a2);
+                    store_result<double>(A, share * A.plane + slot, a0, a1, a2, POT, pot, nint);
+                    slot += T;
                     live = slot < chunk_end;
                     e = 0;
+                    own_end = own0;
                     if (live)
                         start(slot);
                 }
@@ -1330,22 +1540,27 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, u
     }
 }
 
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED, bool FRONT = false>
+template <int SHARES, bool PER, bool TPM, int OPEN, bool POT, bool MIXED, bool FRONT = false>
 __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, uint32_t K,
-                                             uint32_t *front = nullptr) {
+                                             uint32_t *front = nullptr,
+                                             Parts<float> *P = nullptr) {
+    constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
+    static_assert(!(ALL && POT), "");
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
-    const uint32_t base = FRONT ? wave : wave * 64u * K;
+    // (kOneShare: lane l takes share l mod A.shares of a target)
+    const uint32_t T = SHARED ? 64u >> A.shares_log : 64u;  // targets at a time
+    const uint32_t base = FRONT ? wave : wave * T * K;
     if (base >= nu)
         return;
-    const uint32_t chunk_end = min(nu, base + 64u * K);
+    const uint32_t chunk_end = min(nu, base + T * K);
     const Rec32 *__restrict__ R = (const Rec32 *)A.rec;
     const double len21 = ldexp(A.L, -kMaxLevel);
     constexpr int SH = PER ? kRecShiftPer : kRecShiftIso;
     int32_t G0 = 0, G1 = 0, G2 = 0;
     float xr0 = 0.f, xr1 = 0.f, xr2 = 0.f, alpha_an = 0.f, a0 = 0.f, a1 = 0.f, a2 = 0.f,
           pot = 0.f, hi = 0.f;
-    uint32_t self = 0, nint = 0;
+    uint32_t self = 0, nint = 0, cs = 0, sh = 0;
     auto start = [&](uint32_t sl) {
         const uint32_t s = coherent_ld(A.act + sl);
         const uint64_t qq = A.qs[s];
@@ -1365,10 +1580,14 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
             hi = (float)A.hs[s];
         a0 = a1 = a2 = pot = 0.f;
         nint = 0;
+        if (ALL) {
+            cs = sh = 0u;
+            parts_clear(P, A.shares);
+        }
     };
     // entry e for this lane's target: the decision and the interaction, as
     // in a sequential walk; true: descend into e
-    auto visit = [&](uint32_t e, const Rec32 &r) -> bool {
+    auto visit = [&](uint32_t e, const Rec32 &r, bool owned = true) -> bool {
         const float he = MIXED ? ((const float *)A.eh)[e] : 0.0f;
         const int32_t cm = r.cx_meta;
         const float c0 = fmaf((float)wsub(cm & -(1 << SH), G0), A.fu, -xr0);
@@ -1397,7 +1616,9 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
         const bool soft_open = MIXED && hi < he && dd < he * he;
         const bool open = !part && !discard && (crit || box || soft_open);
         const bool inter = part ? (e != self && (!TPM || dd < A.frc2)) : (!discard && !open);
-        if (inter) {
+        if (inter && owned) {
+            if (ALL && sh != cs)
+                parts_switch(P, cs, sh, a0, a1, a2);
             interact32<TPM, POT, MIXED>(A, r.gm, d0, d1, d2, dd, hi > he ? hi : he, a0, a1, a2,
                                         pot);
             nint++;
@@ -1405,20 +1626,40 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
         return part || open;
     };
     if constexpr (!FRONT) {
-        uint32_t slot = base + lane;
+        const uint32_t share = SHARED ? (uint32_t)lane & (A.shares - 1u) : 0u;
+        const uint32_t block = 1u << A.share_shift;
+        const uint32_t own0 = SHARES != kWhole && A.shares > 1u ? 0u : 0xffffffffu;
+        uint32_t slot = base + (SHARED ? (uint32_t)lane >> A.shares_log : (uint32_t)lane);
         bool live = slot < chunk_end;
-        uint32_t e = 0;
+        uint32_t e = 0, own_end = own0;
         if (live)
             start(slot);
         while (__ballot(live)) {
             if (live) {
                 const Rec32 r = R[e];
-                e = visit(e, r) ? e + 1u : r.skip;
+                bool owned = true, over = false;
+                if (e >= own_end) {  // outside this share's subtrees
+                    const bool small = r.skip - e <= block;
+                    if (SHARED) {
+                        owned = owns(A, e, share);
+                        over = small && !owned;
+                    } else {
+                        sh = (e >> A.share_shift) & (A.shares - 1u);
+                    }
+                    own_end = small && owned ? r.skip : own_end;
+                }
+                if (over)
+                    e = r.skip;
+                else
+                    e = visit(e, r, owned) ? e + 1u : r.skip;
                 if (e >= A.E) {
-                    store_result<float>(A, slot, a0, a1, a2, POT, pot, nint);
-                    slot += 64u;
+                    if (ALL)
+                        parts_total(P, cs, A.shares, a0, a1, a2);
+                    store_result<float>(A, share * A.plane + slot, a0, a1, a2, POT, pot, nint);
+                    slot += T;
                     live = slot < chunk_end;
                     e = 0;
+                    own_end = own0;
                     if (live)
                         start(slot);
                 }
@@ -1468,15 +1709,36 @@ enum Variant : uint32_t { kGroupWalk = 0, kLaneWalk = 1, kSplitWalk = 2, kGroupO
 // be returned (single-system launches; the batch and the resident server
 // take the lanes there).
 Variant walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok = false);
+// Shares of a walk over n_act targets with that variant, into A.
+void set_shares(const tpm_ctx *c, int64_t n_act, Variant v, WalkArgs &A);
+// Wavefronts of a walk over nu unique targets.
+__host__ __device__ inline uint32_t walk_waves(Variant v, uint32_t nu, uint32_t shares) {
+    if (v == kSplitWalk)
+        return nu;
+    if (v == kLaneWalk) {
+        const uint32_t t = 64u / shares;
+        return (nu + t - 1u) / t;
+    }
+    return (nu + 63u) / 64u * shares;
+}
 
 // Whether the targets of group `wave` (its 64 slots; the caller has checked
 // that the group is not empty) lie within a box of side sqrt(A.group_ext2)
 // (nearest images in a periodic box), so that a shared cursor walks little
 // more than each target's own walk.  Wavefront-uniform.
-template <bool PER>
+// Without a cutoff: whether they lie close on the curve, at most 8 particles
+// for each target (12 where the walk has at most four shares; the measurements
+// are at k_census).
+template <bool PER, bool TPM>
 __device__ __forceinline__ bool group_compact(const WalkArgs &A, uint32_t wave) {
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
+    if constexpr (!TPM) {
+        const uint32_t first = coherent_ld(A.act + wave * 64u);
+        const uint32_t last = coherent_ld(A.act + min(wave * 64u + 63u, nu - 1u));
+        return __builtin_amdgcn_readfirstlane(
+                   (int)(last - first < (A.shares > 4u ? 512u : 768u))) != 0;
+    }
     const uint32_t slot = wave * 64u + lane;
     const uint32_t s = coherent_ld(A.act + (slot < nu ? slot : wave * 64u));
     double lo[3], hi[3];

@@ -338,6 +338,39 @@ def test_active_subsets_and_duplicates():
     ctx.check()
 
 
+@pytest.mark.parametrize("n", [4097, 65536, 65537, 196609, 262145])
+@pytest.mark.parametrize("mesh", [0, 16])
+def test_shares_of_a_walk(n, mesh, monkeypatch):
+    """Walks of small sets are divided into shares, eight to one at these
+    sizes: the shared cursor and the lanes add the same shares (bit for bit),
+    and no interaction is lost or done twice (counts of the undivided walk,
+    one wavefront per target).  700 particles share a place, so that a leaf
+    parent is larger than the blocks the shares are dealt."""
+    p = W.uniform_cube(n, 43, side=100.0)
+    for v in (p.x, p.y, p.z):
+        v[50:750] = 31.0
+    kw = dict(precision="fp32", eps=0.05, theta=1.2, want_potential=True)
+    if mesh:
+        kw.update(periodic=True, box_size=100.0, pm_grid=mesh, rcut=2.0)
+    out = []
+    for mode in ("1", "2", "3"):
+        monkeypatch.setenv("TPM_WALK_MODE", mode)
+        ctx = _ctx(**kw)
+        _build(ctx, p)
+        nint = torch.full((n,), -1, dtype=torch.int32, device=_dev())
+        acc, pot = ctx.compute_forces(_t(np.arange(n), torch.int32), "bh", n_interactions=nint)
+        ctx.check()
+        out.append((acc, pot, nint))
+    for a, b in zip(out[0], out[1]):
+        assert torch.equal(a, b)
+    assert torch.equal(out[0][2], out[2][2])
+    mag = out[0][0].double().norm(dim=0)
+    scale = mag.clamp_min(float(mag.square().mean().sqrt()))
+    err = (out[2][0].double() - out[0][0].double()).norm(dim=0) / scale
+    # rounding of two summation orders of at most n_int terms
+    assert float(err.max()) <= 64 * 2.0 ** -24 * float(out[0][2].max())
+
+
 @pytest.mark.parametrize("n", [255 * 64, 64 * 256 + 1, 8192 * 256 - 63, 8305 * 256 - 1])
 def test_block_order_covers_every_group(n, monkeypatch):
     """The blocks of a walk are dealt to the dies in runs of a length that

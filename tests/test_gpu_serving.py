@@ -181,6 +181,37 @@ def test_resident_step_equals_single_system_sequence():
         lp.close()
 
 
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("mesh", [0, 16])
+def test_resident_adds_the_same_shares(prec, mesh):
+    """The resident kernel walks all shares of its targets in one pass, the
+    single-system launch each share on its own: the same sums bit for bit, in
+    a dense set (shared cursor) and a sparse one (lanes), with a leaf parent
+    of 700 particles, larger than the blocks the shares are dealt."""
+    from paper_1909_04667_amd import binding as B
+    p = W.uniform_cube(30000, 47, side=100.0)
+    for v in (p.x, p.y, p.z):
+        v[50:750] = 31.0
+    kw = dict(periodic=True, box_size=100.0, pm_grid=mesh, rcut=2.0) if mesh else {}
+    ctx = B.Context(precision=prec, eps=0.05, **kw)
+    t = lambda a: torch.as_tensor(a, dtype=torch.float64, device=_dev())
+    ctx.build_tree(t(p.x), t(p.y), t(p.z))
+    lp = B.ResidentServer(prec)
+    for k in (30000, 6000):
+        ids = np.sort(np.random.default_rng(3).choice(p.n, k, replace=False)).astype(np.int32)
+        ix = torch.as_tensor(ids, device=_dev())
+        n_ref = torch.empty(k, dtype=torch.int32, device=_dev())
+        ref, _ = ctx.compute_forces(ix, "bh", n_interactions=n_ref)
+        torch.cuda.synchronize()
+        n = torch.zeros(k, dtype=torch.int32, device=_dev())
+        tk, acc = lp.submit(ctx, ix, "bh", n_interactions=n)
+        lp.wait(tk)
+        ctx.check()
+        assert torch.equal(acc.cpu(), ref.cpu()), k
+        assert torch.equal(n.cpu(), n_ref.cpu()), k
+    lp.close()
+
+
 def test_resident_requests_join_the_running_kernel():
     """A large request keeps the kernel busy; requests submitted meanwhile
     are taken up by the same launch, and a context rebuilt meanwhile is
