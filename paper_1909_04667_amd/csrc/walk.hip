@@ -243,7 +243,7 @@ void launch_walk(const WalkArgs &A, const Launch &L, hipStream_t st) {
         k_census<PER, TPM><<<L.census_blocks, kBlock, 0, st>>>(A, (uint32_t *)A.census);
         if (L.fp32) {
             if (A.shares > 1u)
-                k_walk32m<true, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+                k_walk32m<OPEN == TPM_OPEN_REL, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
             else
                 k_walk32m<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
             k_walk32im<PER, TPM, OPEN, POT, MIXED><<<L.lane_blocks, kBlock, 0, st>>>(A);
@@ -257,7 +257,7 @@ void launch_walk(const WalkArgs &A, const Launch &L, hipStream_t st) {
     } else {
         if (L.fp32) {
             if (A.shares > 1u)
-                k_walk32<true, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+                k_walk32<OPEN == TPM_OPEN_REL, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
             else
                 k_walk32<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
         } else {
@@ -408,9 +408,13 @@ Variant wk::walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok) {
 // and 512: within 10 %), an isolated tree's entries over 128, 256 to 4096
 // (Hernquist 50,000 in FP64: blocks of 256, 512, 1024, 2048 give 1.15, 1.02,
 // .98, 1.19 ms for both passes).
-void wk::set_shares(const tpm_ctx *c, int64_t n_act, Variant v, WalkArgs &A) {
+void wk::set_shares(const tpm_ctx *c, int64_t n_act, int opening, Variant v, WalkArgs &A) {
     const int64_t t = std::min<int64_t>(n_act, c->n);
-    A.shares_log = v == kSplitWalk ? 0u : t <= 65536 ? (c->P.precision == TPM_FP32 ? 3u : 2u) : t <= 196608 ? 2u : t <= 262144 ? 1u : 0u;
+    const bool fp32 = c->P.precision == TPM_FP32;
+    // (FP64: four, the sums that the server's LDS holds)
+    A.shares_log = t <= 65536 && fp32 ? 3u : t <= 196608 ? 2u : t <= 262144 ? 1u : 0u;
+    if (v == kSplitWalk || (fp32 && opening == TPM_OPEN_BH))
+        A.shares_log = 0u;
     A.shares = 1u << A.shares_log;
     A.share_shift = 8;
     if (!c->P.periodic)
@@ -519,7 +523,7 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
     // lane-independent walks pay off where the interaction is expensive and
     // the wavefront's union of cutoff spheres is large: FP64 with TreePM
     LA.variant = walk_variant(c, n_act, true);
-    set_shares(c, n_act, LA.variant, A);
+    set_shares(c, n_act, opening, LA.variant, A);
     if (LA.variant == kGroupOrLanes) {  // the census word follows the unique count
         A.census = w.nuniq + 1;
         TPM_TRY(fill_u32(c, w.nuniq + 1, 0u, 1));
@@ -596,7 +600,7 @@ __device__ __forceinline__ void batch_group(const WalkArgs &A, uint32_t g, uint3
     if constexpr (FP32) {
         if (var == kLaneWalk)
             walk_lanes32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, 1u);
-        else if (A.shares > 1u)
+        else if (OPEN == TPM_OPEN_REL && A.shares > 1u)
             walk_group32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g);
         else
             walk_group32<kWhole, PER, TPM, OPEN, false, MIXED>(A, g);
@@ -824,7 +828,7 @@ int tpm_batch_launch(tpm_batch *b) {
         R.first = items[which];
         const uint32_t tg = (uint32_t)std::min<int64_t>(p.n_act, c->n);
         const Variant variant = walk_variant(c, p.n_act);
-        set_shares(c, p.n_act, variant, R.A);
+        set_shares(c, p.n_act, p.opening, variant, R.A);
         const bool split = p.n_act > 0 && variant == kSplitWalk;
         if (split) {  // its own launch, after the staging below
             Launch LA{c->P.precision == TPM_FP32, kSplitWalk, 1u, (tg + 3) / 4, 0u, 0u};

@@ -480,6 +480,15 @@ __device__ __forceinline__ uint64_t equal_mask(uint32_t a, uint32_t b) {
     return ((uint64_t)m << 32) | m;
 }
 
+// The shares of an FP32 walk: the geometric pass is not divided.  Its forces
+// give the |a| by which the relative pass opens cubes; summed in another
+// order they differ in the last bits, and the few decisions that then change
+// move single forces by up to 1.7e-3 (one in five systems of 10^5 particles
+// had one above 8e-4).  In FP64 no decision changes.
+__device__ __forceinline__ uint32_t shares32(const WalkArgs &A, int opening) {
+    return opening == TPM_OPEN_BH ? 1u : A.shares;
+}
+
 // Who walks a target's shares.
 enum Shares : int {
     kWhole = 0,      // the walk is not divided
@@ -986,11 +995,12 @@ __device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t item,
                                              Parts<float> *P = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
     static_assert(!(ALL && POT), "");
+    const uint32_t shares = shares32(A, OPEN);
     constexpr int SH = PER ? kRecShiftPer : kRecShiftIso;
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
     const uint32_t it = __builtin_amdgcn_readfirstlane(item);
-    const uint32_t share = SHARED ? it & (A.shares - 1u) : 0u;
+    const uint32_t share = SHARED ? it & (shares - 1u) : 0u;
     const uint32_t wave = SHARED ? it >> A.shares_log : it;  // the group
     if (wave * 64u >= nu)
         return;
@@ -1091,16 +1101,16 @@ __device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t item,
     uint64_t own = ~0ull;  // all ones: entries are accepted here (none: another share's)
     bool dealt = false;    // a cube larger than a block: its particles are dealt out
     if (ALL)
-        parts_clear(P, A.shares);
+        parts_clear(P, shares);
     uint32_t c = 0;
     while (c < A.E) {
         // the whole walk, or the next stretch of it that belongs to one share
         uint32_t end = A.E;
-        if (SHARES != kWhole && A.shares > 1u) {
+        if (SHARES != kWhole && shares > 1u) {
             const uint32_t cu = __builtin_amdgcn_readfirstlane(c);
             const uint32_t skip = uniform_skip(R, cu);
             dealt = skip - cu > 1u << A.share_shift;
-            sh = (cu >> A.share_shift) & (A.shares - 1u);
+            sh = (cu >> A.share_shift) & (shares - 1u);
             if (SHARED) {
                 if (!dealt && sh != share) {
                     c = skip;
@@ -1186,7 +1196,7 @@ __device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t item,
                         const uint32_t e = base + (uint32_t)__builtin_ctzll(m);
                         m &= m - 1;
                         if (ALL && dealt) {
-                            sh = (e >> A.share_shift) & (A.shares - 1u);
+                            sh = (e >> A.share_shift) & (shares - 1u);
                             if (sh != cs)
                                 parts_switch(P, cs, sh, a0, a1, a2);
                         }
@@ -1198,7 +1208,7 @@ __device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t item,
         }
     }
     if (ALL)
-        parts_total(P, cs, A.shares, a0, a1, a2);
+        parts_total(P, cs, shares, a0, a1, a2);
     if (valid)
         store_result<float>(A, (SHARED ? share * A.plane : 0u) + slot, a0, a1, a2, POT, pot, nint);
 }
@@ -1546,6 +1556,7 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
                                              Parts<float> *P = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
     static_assert(!(ALL && POT), "");
+    const uint32_t shares = shares32(A, OPEN);
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
     // (kOneShare: lane l takes share l mod A.shares of a target)
@@ -1582,7 +1593,7 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
         nint = 0;
         if (ALL) {
             cs = sh = 0u;
-            parts_clear(P, A.shares);
+            parts_clear(P, shares);
         }
     };
     // entry e for this lane's target: the decision and the interaction, as
@@ -1626,9 +1637,9 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
         return part || open;
     };
     if constexpr (!FRONT) {
-        const uint32_t share = SHARED ? (uint32_t)lane & (A.shares - 1u) : 0u;
+        const uint32_t share = SHARED ? (uint32_t)lane & (shares - 1u) : 0u;
         const uint32_t block = 1u << A.share_shift;
-        const uint32_t own0 = SHARES != kWhole && A.shares > 1u ? 0u : 0xffffffffu;
+        const uint32_t own0 = SHARES != kWhole && shares > 1u ? 0u : 0xffffffffu;
         uint32_t slot = base + (SHARED ? (uint32_t)lane >> A.shares_log : (uint32_t)lane);
         bool live = slot < chunk_end;
         uint32_t e = 0, own_end = own0;
@@ -1644,7 +1655,7 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
                         owned = owns(A, e, share);
                         over = small && !owned;
                     } else {
-                        sh = (e >> A.share_shift) & (A.shares - 1u);
+                        sh = (e >> A.share_shift) & (shares - 1u);
                     }
                     own_end = small && owned ? r.skip : own_end;
                 }
@@ -1654,7 +1665,7 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
                     e = visit(e, r, owned) ? e + 1u : r.skip;
                 if (e >= A.E) {
                     if (ALL)
-                        parts_total(P, cs, A.shares, a0, a1, a2);
+                        parts_total(P, cs, shares, a0, a1, a2);
                     store_result<float>(A, share * A.plane + slot, a0, a1, a2, POT, pot, nint);
                     slot += T;
                     live = slot < chunk_end;
@@ -1709,8 +1720,9 @@ enum Variant : uint32_t { kGroupWalk = 0, kLaneWalk = 1, kSplitWalk = 2, kGroupO
 // be returned (single-system launches; the batch and the resident server
 // take the lanes there).
 Variant walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok = false);
-// Shares of a walk over n_act targets with that variant, into A.
-void set_shares(const tpm_ctx *c, int64_t n_act, Variant v, WalkArgs &A);
+// Shares of a walk over n_act targets with that criterion and variant, into A
+// (a walk of both criteria, the server's steps: those of the relative pass).
+void set_shares(const tpm_ctx *c, int64_t n_act, int opening, Variant v, WalkArgs &A);
 // Wavefronts of a walk over nu unique targets.
 __host__ __device__ inline uint32_t walk_waves(Variant v, uint32_t nu, uint32_t shares) {
     if (v == kSplitWalk)

@@ -349,7 +349,7 @@ def test_shares_of_a_walk(n, mesh, monkeypatch):
     p = W.uniform_cube(n, 43, side=100.0)
     for v in (p.x, p.y, p.z):
         v[50:750] = 31.0
-    kw = dict(precision="fp32", eps=0.05, theta=1.2, want_potential=True)
+    kw = dict(precision="fp32", eps=0.05, alpha=0.02, want_potential=True)
     if mesh:
         kw.update(periodic=True, box_size=100.0, pm_grid=mesh, rcut=2.0)
     out = []
@@ -358,7 +358,8 @@ def test_shares_of_a_walk(n, mesh, monkeypatch):
         ctx = _ctx(**kw)
         _build(ctx, p)
         nint = torch.full((n,), -1, dtype=torch.int32, device=_dev())
-        acc, pot = ctx.compute_forces(_t(np.arange(n), torch.int32), "bh", n_interactions=nint)
+        acc, pot = ctx.compute_forces(_t(np.arange(n), torch.int32), "rel", n_interactions=nint,
+                                      a_old_norm=_t(np.full(n, 1e-3)))
         ctx.check()
         out.append((acc, pot, nint))
     for a, b in zip(out[0], out[1]):

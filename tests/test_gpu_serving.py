@@ -193,22 +193,23 @@ def test_resident_adds_the_same_shares(prec, mesh):
     for v in (p.x, p.y, p.z):
         v[50:750] = 31.0
     kw = dict(periodic=True, box_size=100.0, pm_grid=mesh, rcut=2.0) if mesh else {}
-    ctx = B.Context(precision=prec, eps=0.05, **kw)
+    ctx = B.Context(precision=prec, eps=0.05, alpha=0.02, **kw)
     t = lambda a: torch.as_tensor(a, dtype=torch.float64, device=_dev())
     ctx.build_tree(t(p.x), t(p.y), t(p.z))
     lp = B.ResidentServer(prec)
-    for k in (30000, 6000):
+    an = t(np.full(p.n, 1e-3))
+    for k, opening in ((30000, "rel"), (6000, "rel"), (30000, "bh"), (6000, "bh")):
         ids = np.sort(np.random.default_rng(3).choice(p.n, k, replace=False)).astype(np.int32)
         ix = torch.as_tensor(ids, device=_dev())
         n_ref = torch.empty(k, dtype=torch.int32, device=_dev())
-        ref, _ = ctx.compute_forces(ix, "bh", n_interactions=n_ref)
+        ref, _ = ctx.compute_forces(ix, opening, a_old_norm=an, n_interactions=n_ref)
         torch.cuda.synchronize()
         n = torch.zeros(k, dtype=torch.int32, device=_dev())
-        tk, acc = lp.submit(ctx, ix, "bh", n_interactions=n)
+        tk, acc = lp.submit(ctx, ix, opening, a_old_norm=an, n_interactions=n)
         lp.wait(tk)
         ctx.check()
-        assert torch.equal(acc.cpu(), ref.cpu()), k
-        assert torch.equal(n.cpu(), n_ref.cpu()), k
+        assert torch.equal(acc.cpu(), ref.cpu()), (k, opening)
+        assert torch.equal(n.cpu(), n_ref.cpu()), (k, opening)
     lp.close()
 
 
