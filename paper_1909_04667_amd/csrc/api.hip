@@ -311,6 +311,11 @@ int tpm_create_arena(const tpm_params *p, void *hip_stream, int64_t arena_bytes,
         delete c;
         return TPM_ENOMEM;
     }
+    if (hipHostGetDevicePointer((void **)&c->hpin_dev, c->hpin, 0) != hipSuccess) {
+        free_all(c);
+        delete c;
+        return TPM_EDEVICE;
+    }
     // buffers kept across builds take the arena's top end
     visit_sizes(c, c->P, 1, 0, false, [](DBuf &b, size_t, int kind) {
         if (kind == 2)

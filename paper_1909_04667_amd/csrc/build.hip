@@ -11,6 +11,7 @@
 // subtree) come from a galloping search for the end of each prefix run.
 #include "tpm_internal.h"
 
+#include <cstring>
 #include <vector>
 
 namespace tpm {
@@ -58,6 +59,30 @@ __global__ __launch_bounds__(kBlock) void k_bbox_partial(const double *__restric
 
 // Smallest power of two >= ext (1 + 2^-20) (1 when every particle coincides);
 // the corner sits below the minimum by a fraction shift of the slack.
+__device__ __forceinline__ void make_frame(const double lo[3], const double hi[3], double s0,
+                                           double s1, double s2, Frame &F) {
+    double ext = 0.0;
+    for (int a = 0; a < 3; a++) {
+        double e = hi[a] - lo[a];
+        ext = e > ext ? e : ext;
+    }
+    double L = 1.0;
+    if (ext > 0.0) {
+        double t = ext * (1.0 + 0x1p-20);
+        int ex;
+        double m = frexp(t, &ex);
+        L = (m == 0.5) ? ldexp(1.0, ex - 1) : ldexp(1.0, ex);
+    }
+    const double shift[3] = {s0, s1, s2};
+    for (int a = 0; a < 3; a++)
+        F.x0[a] = lo[a] - shift[a] * (L - (hi[a] - lo[a]));
+    F.L = L;
+    F.S = 2097152.0 / L;
+    F.box = 0.0;
+    F.periodic = 0;
+    F.pad = 0;
+}
+
 __global__ __launch_bounds__(kBlock) void k_frame_final(const double *__restrict__ part,
                                                         int nparts, Frame *F, double s0,
                                                         double s1, double s2) {
@@ -89,26 +114,10 @@ __global__ __launch_bounds__(kBlock) void k_frame_final(const double *__restrict
         lo[a] = sh[a][0];
         hi[a] = sh[3 + a][0];
     }
-    double ext = 0.0;
-    for (int a = 0; a < 3; a++) {
-        double e = hi[a] - lo[a];
-        ext = e > ext ? e : ext;
-    }
-    double L = 1.0;
-    if (ext > 0.0) {
-        double t = ext * (1.0 + 0x1p-20);
-        int ex;
-        double m = frexp(t, &ex);
-        L = (m == 0.5) ? ldexp(1.0, ex - 1) : ldexp(1.0, ex);
-    }
-    const double shift[3] = {s0, s1, s2};
-    for (int a = 0; a < 3; a++)
-        F->x0[a] = lo[a] - shift[a] * (L - (hi[a] - lo[a]));
-    F->L = L;
-    F->S = 2097152.0 / L;
-    F->box = 0.0;
-    F->periodic = 0;
+    make_frame(lo, hi, s0, s1, s2, *F);
 }
+
+__global__ void k_set_frame(Frame h, Frame *F) { *F = h; }
 
 // ---- keys ------------------------------------------------------------------
 
@@ -283,12 +292,20 @@ __global__ __launch_bounds__(kBlock) void k_count(const uint64_t *__restrict__ k
     }
 }
 
-// Start offset of every level's node list (the scanned histogram's first
-// block) into out[0..21].
-__global__ void k_level_starts(const uint32_t *__restrict__ off, uint32_t nb,
-                               uint32_t *__restrict__ out) {
+// What the host waits for, written to its pinned memory: the start offset of
+// every level's node list (the scanned histogram's first block, 0 .. 21), the
+// entries (32) and nodes (33), the frame (64) and the softening flag (128).
+__global__ void k_sizes(const uint32_t *__restrict__ off, uint32_t nb,
+                        const uint32_t *__restrict__ totals, const Frame *__restrict__ Fp,
+                        const uint32_t *__restrict__ bad_eps, uint32_t *hpin) {
     if (threadIdx.x < kLevels)
-        out[threadIdx.x] = off[(size_t)threadIdx.x * nb];
+        hpin[threadIdx.x] = off[(size_t)threadIdx.x * nb];
+    if (threadIdx.x == 32 || threadIdx.x == 33)
+        hpin[threadIdx.x] = totals[threadIdx.x - 32];
+    if (threadIdx.x == 34)
+        *(Frame *)(hpin + 64) = *Fp;
+    if (threadIdx.x == 35)
+        hpin[128] = *bad_eps;
 }
 
 __device__ __forceinline__ uint64_t prefix_at(uint64_t k, int lev) {
@@ -311,52 +328,16 @@ __device__ __forceinline__ void rec32_centre(Rec32 &o, const uint32_t q[3], int 
     o.cz = (int32_t)((uint32_t)C[2] << sh);
 }
 
-// Emit the particle entry and the node entries a particle starts.  Skip
-// pointers and counts of nodes are filled bottom-up by k_moments: every
-// entry carries a depth (nodes: their level; a particle: the level of the
-// cell it occupies alone, one below its deepest shared prefix), and the
-// subtree of a node of level l ends at the first later entry of depth <= l.
-// FP32 contexts (out32 set): a particle's FP32 record is written here, a
-// node's by k_moments.
-__global__ __launch_bounds__(kBlock) void k_emit(
-    const uint64_t *__restrict__ key, int64_t n, const int8_t *__restrict__ dR,
-    const uint32_t *__restrict__ base, const Frame *__restrict__ Fp,
+// The entries that particle s (slot) starts, from entry b on: its nodes of
+// levels l + 1 .. r (the depths it shares with its left and right neighbours)
+// and itself.
+__device__ __forceinline__ void emit_particle(
+    int64_t s, int64_t n, int l, int r, uint32_t b, const Frame &F,
     const double *__restrict__ ps, const double *__restrict__ ms,
     const uint64_t *__restrict__ qs, Rec64 *__restrict__ rec, uint32_t *__restrict__ efirst,
-    uint32_t *__restrict__ ecount, uint32_t *__restrict__ pe,
-    const uint32_t *__restrict__ loff, uint32_t nb, uint32_t *__restrict__ lvl_list,
-    const double *__restrict__ hs, double *__restrict__ eh, double G, Rec32 *__restrict__ out32,
-    float *__restrict__ eh32) {
-    __shared__ uint32_t h[kLevels][kBlock / 64];
-    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool live = s < n;
-    const int r = live ? (int)dR[s] : -1;
-    const int l = (live && s > 0) ? (int)dR[s - 1] : -1;
-    const uint32_t b = live ? base[s] : 0u;
+    uint32_t *__restrict__ ecount, uint32_t *__restrict__ pe, const double *__restrict__ hs,
+    double *__restrict__ eh, double G, Rec32 *__restrict__ out32, float *__restrict__ eh32) {
     const int nn = r > l ? r - l : 0;
-    // level lists in particle order: block offset (scanned histogram) +
-    // preceding wavefronts of the block + preceding lanes of the wavefront
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    for (int lev = 0; lev < kLevels; lev++) {
-        const uint64_t m = __ballot(lev > l && lev <= r);
-        if (lane == 0)
-            h[lev][w] = (uint32_t)__popcll(m);
-    }
-    __syncthreads();
-    for (int lev = 0; lev < kLevels; lev++) {
-        const bool has = lev > l && lev <= r;
-        const uint64_t m = __ballot(has);
-        if (has) {
-            uint32_t at = loff[(size_t)lev * nb + blockIdx.x];
-            for (int q = 0; q < w; q++)
-                at += h[lev][q];
-            lvl_list[at + (uint32_t)__popcll(m & lt)] = b + (uint32_t)(lev - l - 1);
-        }
-    }
-    if (!live)
-        return;
-    const Frame F = *Fp;
     const uint32_t ep = b + (uint32_t)nn;
     const int sh = F.periodic ? kRecShiftPer : kRecShiftIso;
     const uint64_t qq = qs[s];
@@ -393,8 +374,6 @@ __global__ __launch_bounds__(kBlock) void k_emit(
                 eh32[ep] = (float)hs[s];
         }
     }
-    if (nn == 0)
-        return;
     for (int lev = l + 1; lev <= r; ++lev) {
         const uint32_t e = b + (uint32_t)(lev - l - 1);
         Rec64 R;
@@ -410,6 +389,90 @@ __global__ __launch_bounds__(kBlock) void k_emit(
         R.meta = (uint32_t)lev;
         rec[e] = R;
         efirst[e] = (uint32_t)s;
+    }
+}
+
+// Emit the particle entry and the node entries a particle starts.  Skip
+// pointers and counts of nodes are filled bottom-up by k_moments: every
+// entry carries a depth (nodes: their level; a particle: the level of the
+// cell it occupies alone, one below its deepest shared prefix), and the
+// subtree of a node of level l ends at the first later entry of depth <= l.
+// FP32 contexts (out32 set): a particle's FP32 record is written here, a
+// node's by k_moments.
+__global__ __launch_bounds__(kBlock) void k_emit(
+    const uint64_t *__restrict__ key, int64_t n, const int8_t *__restrict__ dR,
+    const uint32_t *__restrict__ base, const Frame *__restrict__ Fp,
+    const double *__restrict__ ps, const double *__restrict__ ms,
+    const uint64_t *__restrict__ qs, Rec64 *__restrict__ rec, uint32_t *__restrict__ efirst,
+    uint32_t *__restrict__ ecount, uint32_t *__restrict__ pe,
+    const uint32_t *__restrict__ loff, uint32_t nb, uint32_t *__restrict__ lvl_list,
+    const double *__restrict__ hs, double *__restrict__ eh, double G, Rec32 *__restrict__ out32,
+    float *__restrict__ eh32) {
+    __shared__ uint32_t h[kLevels][kBlock / 64];
+    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool live = s < n;
+    const int r = live ? (int)dR[s] : -1;
+    const int l = (live && s > 0) ? (int)dR[s - 1] : -1;
+    const uint32_t b = live ? base[s] : 0u;
+    // level lists in particle order: block offset (scanned histogram) +
+    // preceding wavefronts of the block + preceding lanes of the wavefront
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    for (int lev = 0; lev < kLevels; lev++) {
+        const uint64_t m = __ballot(lev > l && lev <= r);
+        if (lane == 0)
+            h[lev][w] = (uint32_t)__popcll(m);
+    }
+    __syncthreads();
+    for (int lev = 0; lev < kLevels; lev++) {
+        const bool has = lev > l && lev <= r;
+        const uint64_t m = __ballot(has);
+        if (has) {
+            uint32_t at = loff[(size_t)lev * nb + blockIdx.x];
+            for (int q = 0; q < w; q++)
+                at += h[lev][q];
+            lvl_list[at + (uint32_t)__popcll(m & lt)] = b + (uint32_t)(lev - l - 1);
+        }
+    }
+    if (!live)
+        return;
+    emit_particle(s, n, l, r, b, *Fp, ps, ms, qs, rec, efirst, ecount, pe, hs, eh, G, out32, eh32);
+}
+
+// Writes node e's records from its sums over the children; k: the entry
+// after its subtree, f: its first particle.
+__device__ __forceinline__ void finish_node(Rec64 *rec, uint32_t e, uint32_t k, uint32_t E,
+                                            uint32_t n, uint32_t f, uint32_t lev, Rec64 R,
+                                            double M, double X0, double X1, double X2,
+                                            double hmax, uint64_t qq, const uint32_t *efirst,
+                                            uint32_t *ecount, double *eh, double G, int sh,
+                                            Rec32 *out32, float *eh32) {
+    const uint32_t cnt = (k < E ? efirst[k] : n) - f;
+    const bool leaf_parent = k - e - 1u == cnt;  // no entry below but the particles themselves
+    R.mass = M;
+    R.com[0] = X0 / M;
+    R.com[1] = X1 / M;
+    R.com[2] = X2 / M;
+    R.skip = k;
+    R.meta |= leaf_parent ? kLeafParentFlag : 0u;
+    rec[e] = R;
+    ecount[e] = cnt;
+    if (eh)
+        eh[e] = hmax;
+    if (out32) {  // exact integer centre from the node's first particle
+        const uint32_t q[3] = {(uint32_t)(qq >> 42) & 0x1fffffu,
+                               (uint32_t)(qq >> 21) & 0x1fffffu, (uint32_t)qq & 0x1fffffu};
+        Rec32 o;
+        rec32_centre(o, q, (int)lev, sh, false);
+        o.dx = (float)(R.com[0] - R.cen[0]);
+        o.dy = (float)(R.com[1] - R.cen[1]);
+        o.dz = (float)(R.com[2] - R.cen[2]);
+        o.gm = (float)(G * M);
+        o.cx_meta |= leaf_parent ? kRecLeafParent : 0;
+        o.skip = k;
+        out32[e] = o;
+        if (eh32)
+            eh32[e] = (float)hmax;
     }
 }
 
@@ -454,35 +517,338 @@ __global__ __launch_bounds__(kBlock) void k_moments(Rec64 *__restrict__ rec, uin
         X2 = fma(mk, rec[k].com[2], X2);
         k = rec[k].skip;
     }
-    const uint32_t cnt = (k < E ? efirst[k] : n) - f;
-    const bool leaf_parent = k - e - 1u == cnt;  // no entry below but the particles themselves
-    R.mass = M;
-    R.com[0] = X0 / M;
-    R.com[1] = X1 / M;
-    R.com[2] = X2 / M;
-    R.skip = k;
-    R.meta |= leaf_parent ? kLeafParentFlag : 0u;
-    rec[e] = R;
-    ecount[e] = cnt;
-    if (eh)
-        eh[e] = hmax;
-    if (out32) {  // exact integer centre from the node's first particle
-        const uint32_t q[3] = {(uint32_t)(qq >> 42) & 0x1fffffu,
-                               (uint32_t)(qq >> 21) & 0x1fffffu, (uint32_t)qq & 0x1fffffu};
-        Rec32 o;
-        rec32_centre(o, q, (int)lev, sh, false);
-        o.dx = (float)(R.com[0] - R.cen[0]);
-        o.dy = (float)(R.com[1] - R.cen[1]);
-        o.dz = (float)(R.com[2] - R.cen[2]);
-        o.gm = (float)(G * M);
-        o.cx_meta |= leaf_parent ? kRecLeafParent : 0;
-        o.skip = k;
-        out32[e] = o;
-        if (eh32)
-            eh32[e] = (float)hmax;
+    finish_node(rec, e, k, E, n, f, lev, R, M, X0, X1, X2, hmax, qq, efirst, ecount, eh, G, sh, out32,
+                eh32);
+}
+
+
+// ---- trees of at most kSmallN particles: one workgroup ---------------------------
+//
+// Every pass of a small build is shorter than a launch and its gap: 35 launches
+// took 0.24 ms for 4096 particles.  One workgroup takes the particles from the
+// positions to the entry counts (root cube, keys, the eight digit passes of the
+// sort in LDS, gather, counts and their scan), a second one, after the sizes are
+// known on the host, emits the entries and sums the moments level by level.
+// Same operations per particle and node as the general kernels, so the same
+// tree bit for bit.  Above kSmallN the general kernels' parallel passes win.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallRounds = 8;
+constexpr int kSmallN = kSmallBlock * kSmallRounds;
+constexpr int kSmallWaves = kSmallBlock / 64;
+constexpr uint32_t kSmallE = 16384;  // entries whose skip pointers fit in LDS
+
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v, int lane) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(v, o, 64);
+        v += lane >= o ? t : 0u;
+    }
+    return v;
+}
+
+// sizes: 64 words, level starts 0 .. 21, entries (32), nodes (33), also
+// written to host memory with the frame (hpin + 64) and the softening flag (128).
+__global__ __launch_bounds__(kSmallBlock) void k_small_front(
+    const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ z,
+    const double *__restrict__ mass, const double *__restrict__ eps, int n, Frame F0, double s0,
+    double s1, double s2, Frame *__restrict__ Fp, uint64_t *__restrict__ key,
+    int32_t *__restrict__ perm, int32_t *__restrict__ rank, double *__restrict__ ps,
+    double *__restrict__ ms, uint64_t *__restrict__ qs, double *__restrict__ hs,
+    int8_t *__restrict__ dR, uint32_t *__restrict__ base, uint32_t *__restrict__ sizes,
+    uint32_t *__restrict__ bad_eps, uint32_t *hpin) {
+    __shared__ uint64_t s_k[kSmallN];
+    __shared__ uint32_t s_v[kSmallN];
+    __shared__ uint32_t s_wc[kSmallWaves][256];
+    __shared__ uint32_t s_loc[256], s_sc[kSmallWaves], s_lev[kLevels];
+    __shared__ double s_red[6][kSmallWaves];
+    __shared__ Frame s_F;
+    __shared__ uint32_t s_bad;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int rounds = (n + kSmallBlock - 1) / kSmallBlock;  // a wavefront's keys: 64 a round
+    const int wbase = w * rounds * 64;
+    if (tid == 0)
+        s_bad = 0u;
+    if (tid < kLevels)
+        s_lev[tid] = 0u;
+    // 1. root cube
+    if (!F0.periodic) {
+        double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+        const double *c[3] = {x, y, z};
+        for (int i = tid; i < n; i += kSmallBlock)
+            for (int a = 0; a < 3; a++) {
+                lo[a] = fmin(lo[a], c[a][i]);
+                hi[a] = fmax(hi[a], c[a][i]);
+            }
+        for (int a = 0; a < 3; a++) {
+            for (int o = 1; o < 64; o <<= 1) {
+                lo[a] = fmin(lo[a], __shfl_xor(lo[a], o));
+                hi[a] = fmax(hi[a], __shfl_xor(hi[a], o));
+            }
+            if (lane == 0) {
+                s_red[a][w] = lo[a];
+                s_red[3 + a][w] = hi[a];
+            }
+        }
+        __syncthreads();
+        if (tid == 0) {
+            for (int a = 0; a < 3; a++)
+                for (int q = 0; q < kSmallWaves; q++) {
+                    lo[a] = fmin(lo[a], s_red[a][q]);
+                    hi[a] = fmax(hi[a], s_red[3 + a][q]);
+                }
+            make_frame(lo, hi, s0, s1, s2, s_F);
+        }
+    } else if (tid == 0) {
+        s_F = F0;
+    }
+    __syncthreads();
+    const Frame F = s_F;
+    // 2. keys
+    uint64_t k[kSmallRounds];
+    uint32_t v[kSmallRounds], pos[kSmallRounds];
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; r++) {
+        const int i = wbase + r * 64 + lane;
+        k[r] = 0ull;
+        v[r] = 0u;
+        if (r < rounds && i < n) {
+            double p;
+            uint32_t q0, q1, q2;
+            to_frame(x[i], F.x0[0], F, p, q0);
+            to_frame(y[i], F.x0[1], F, p, q1);
+            to_frame(z[i], F.x0[2], F, p, q2);
+            k[r] = hilbert_key(q0, q1, q2);
+            v[r] = (uint32_t)i;
+        }
+    }
+    // 3. stable sort, eight 8-bit digits: the rank of a key is the number of
+    // keys with smaller digits, of its digit in earlier wavefronts, and of its
+    // digit before it in its wavefront's contiguous share
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    for (int shift = 0; shift < 64; shift += 8) {
+        for (int q = tid; q < kSmallWaves * 256; q += kSmallBlock)
+            (&s_wc[0][0])[q] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSmallRounds; r++) {
+            if (r >= rounds)
+                break;
+            const bool valid = wbase + r * 64 + lane < n;
+            const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
+            uint64_t peers = __ballot(valid);
+#pragma unroll
+            for (int b = 0; b < 8; b++) {
+                const bool bit = (d >> b) & 1u;
+                const uint64_t m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            const uint32_t before = (uint32_t)__popcll(peers & lt);
+            const uint32_t prev = s_wc[w][d];
+            pos[r] = prev + before;
+            __builtin_amdgcn_wave_barrier();
+            if (valid && before == 0)
+                s_wc[w][d] = prev + (uint32_t)__popcll(peers);
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        uint32_t cnt = 0u, inc = 0u;
+        if (tid < 256) {
+#pragma unroll
+            for (int q = 0; q < kSmallWaves; q++) {
+                const uint32_t cq = s_wc[q][tid];
+                s_wc[q][tid] = cnt;
+                cnt += cq;
+            }
+            inc = wave_scan(cnt, lane);
+            if (lane == 63)
+                s_sc[w] = inc;
+        }
+        __syncthreads();
+        if (tid < 256) {
+            uint32_t wb = 0u;
+            for (int q = 0; q < w; q++)
+                wb += s_sc[q];
+            s_loc[tid] = wb + inc - cnt;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSmallRounds; r++) {
+            if (r >= rounds)
+                break;
+            if (wbase + r * 64 + lane < n) {
+                const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
+                const uint32_t at = s_loc[d] + s_wc[w][d] + pos[r];
+                s_k[at] = k[r];
+                s_v[at] = v[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSmallRounds; r++) {
+            const int i = wbase + r * 64 + lane;
+            if (r < rounds && i < n) {
+                k[r] = s_k[i];
+                v[r] = s_v[i];
+            }
+        }
+        __syncthreads();
+    }
+    // 4. curve order; depths shared with the neighbours, entries per particle
+    uint32_t run = 0u;  // entries of this wavefront's particles so far
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; r++) {
+        if (r >= rounds)
+            break;
+        const int s = wbase + r * 64 + lane;
+        int dr = -1, dl = -1;
+        if (s < n) {
+            const uint32_t i = v[r];
+            key[s] = k[r];
+            perm[s] = (int32_t)i;
+            rank[i] = s;
+            double p0, p1, p2;
+            uint32_t q0, q1, q2;
+            to_frame(x[i], F.x0[0], F, p0, q0);
+            to_frame(y[i], F.x0[1], F, p1, q1);
+            to_frame(z[i], F.x0[2], F, p2, q2);
+            ps[s] = p0;
+            ps[(size_t)n + s] = p1;
+            ps[2 * (size_t)n + s] = p2;
+            ms[s] = mass ? mass[i] : 1.0 / (double)n;
+            qs[s] = ((uint64_t)q0 << 42) | ((uint64_t)q1 << 21) | (uint64_t)q2;
+            if (eps) {
+                const double e = eps[i];
+                if (!(e > 0.0) || !isfinite(e))
+                    s_bad = 1u;
+                hs[s] = 2.8 * e;
+            }
+            dr = s + 1 < n ? common_levels(k[r], s_k[s + 1]) : -1;
+            dl = s > 0 ? common_levels(s_k[s - 1], k[r]) : -1;
+            dR[s] = (int8_t)dr;
+        }
+        const uint32_t nn = dr > dl ? (uint32_t)(dr - dl) : 0u;
+        const uint32_t c = s < n ? nn + 1u : 0u;
+        const uint32_t in = wave_scan(c, lane);
+        pos[r] = run + in - c;
+        run += __shfl(in, 63);
+        for (int lev = 0; lev < kLevels; lev++) {
+            const uint32_t m = (uint32_t)__popcll(__ballot(lev > dl && lev <= dr));
+            if (lane == 0 && m)
+                atomicAdd(&s_lev[lev], m);
+        }
+    }
+    if (lane == 0)
+        s_sc[w] = run;
+    __syncthreads();
+    uint32_t wb = 0u, total = 0u;
+    for (int q = 0; q < kSmallWaves; q++) {
+        wb += q < w ? s_sc[q] : 0u;
+        total += s_sc[q];
+    }
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; r++) {
+        const int s = wbase + r * 64 + lane;
+        if (r < rounds && s < n)
+            base[s] = wb + pos[r];
+    }
+    if (tid == 0) {
+        uint32_t at = 0u;
+        for (int lev = 0; lev < kLevels; lev++) {
+            sizes[lev] = hpin[lev] = at;
+            at += s_lev[lev];
+        }
+        sizes[32] = hpin[32] = total;
+        sizes[33] = hpin[33] = at;
+        *Fp = F;
+        *(Frame *)(hpin + 64) = F;
+        if (s_bad)
+            *bad_eps = 1u;
+        hpin[128] = s_bad;
     }
 }
 
+__global__ __launch_bounds__(kSmallBlock) void k_small_back(
+    int n, uint32_t E, const int8_t *__restrict__ dR, const uint32_t *__restrict__ base,
+    const Frame *__restrict__ Fp, const uint32_t *__restrict__ sizes,
+    const double *__restrict__ ps, const double *__restrict__ ms,
+    const uint64_t *__restrict__ qs, Rec64 *rec, uint32_t *efirst, uint32_t *ecount, uint32_t *pe,
+    uint32_t *lvl_list, const double *__restrict__ hs, double *eh, double G, Rec32 *out32,
+    float *eh32) {
+    // per entry: the entry after its subtree, and its depth
+    __shared__ uint32_t s_skip[kSmallE];
+    __shared__ uint8_t s_dep[kSmallE];
+    __shared__ uint32_t s_cur[kLevels];
+    const int tid = threadIdx.x;
+    if (tid < kLevels)
+        s_cur[tid] = sizes[tid];
+    const Frame F = *Fp;
+    __syncthreads();
+    for (int s = tid; s < n; s += kSmallBlock) {
+        const int r = dR[s], l = s > 0 ? (int)dR[s - 1] : -1;
+        const uint32_t b = base[s];
+        emit_particle(s, n, l, r, b, F, ps, ms, qs, rec, efirst, ecount, pe, hs, eh, G, out32,
+                      eh32);
+        for (int lev = l + 1; lev <= r; lev++) {
+            const uint32_t e = b + (uint32_t)(lev - l - 1);
+            lvl_list[atomicAdd(&s_cur[lev], 1u)] = e;
+            s_dep[e] = (uint8_t)lev;
+        }
+        const uint32_t ep = b + (uint32_t)(r > l ? r - l : 0);
+        s_skip[ep] = ep + 1u;
+        s_dep[ep] = (uint8_t)((r > l ? r : l) + 1);
+    }
+    __syncthreads();
+    const int sh = F.periodic ? kRecShiftPer : kRecShiftIso;
+    for (int lev = kMaxLevel; lev >= 0; lev--) {
+        const uint32_t first = sizes[lev], last = s_cur[lev];
+        if (first == last)
+            continue;
+        for (uint32_t i = first + (uint32_t)tid; i < last; i += kSmallBlock) {
+            const uint32_t e = lvl_list[i];
+            const Rec64 R = rec[e];
+            const uint32_t f = efirst[e];
+            const uint64_t qq = out32 ? qs[f] : 0ull;
+            double M = 0.0, X0 = 0.0, X1 = 0.0, X2 = 0.0, hmax = 0.0;
+            uint32_t k = e + 1u;
+            for (;;) {  // eight children at a time: found in LDS, then loaded together
+                uint32_t kid[8];
+                int m = 0;
+#pragma unroll
+                for (int q = 0; q < 8; q++) {
+                    const bool more = k < E && s_dep[k] > lev;
+                    kid[q] = more ? k : e;
+                    m += more ? 1 : 0;
+                    k = more ? s_skip[k] : k;
+                }
+                double mk[8], c0[8], c1[8], c2[8], hk[8];
+#pragma unroll
+                for (int q = 0; q < 8; q++) {
+                    const Rec64 *c = rec + kid[q];
+                    mk[q] = c->mass;
+                    c0[q] = c->com[0];
+                    c1[q] = c->com[1];
+                    c2[q] = c->com[2];
+                    hk[q] = eh ? eh[kid[q]] : 0.0;
+                }
+#pragma unroll
+                for (int q = 0; q < 8; q++)
+                    if (q < m) {
+                        hmax = hk[q] > hmax ? hk[q] : hmax;
+                        M = M + mk[q];
+                        X0 = fma(mk[q], c0[q], X0);
+                        X1 = fma(mk[q], c1[q], X1);
+                        X2 = fma(mk[q], c2[q], X2);
+                    }
+                if (m < 8)
+                    break;
+            }
+            s_skip[e] = k;
+            finish_node(rec, e, k, E, (uint32_t)n, f, (uint32_t)lev, R, M, X0, X1, X2, hmax, qq,
+                        efirst, ecount, eh, G, sh, out32, eh32);
+        }
+        __syncthreads();
+    }
+}
 
 }  // namespace
 
@@ -517,19 +883,42 @@ int build(tpm_ctx *c, int64_t n, const double *x, const double *y, const double 
     TPM_TRY(ensure(c, c->counters, 64 * sizeof(uint32_t)));
     TPM_TRY(ensure(c, c->lvl_cursor, 32 * sizeof(uint32_t)));
     Frame *F = (Frame *)c->frame.p;
+    const uint64_t *key = (const uint64_t *)c->key[0].p;
 
-    // 1. root cube
-    TPM_TRY(timer_begin(c, TPM_TIMER_KEYS));
+    uint32_t *lvl_count = (uint32_t *)c->counters.p;  // [0..21] level starts, [32] E, [33] nodes
+    uint32_t *bad_eps = (uint32_t *)c->err_flag.p + 1;
+    const uint32_t nb = grid_for(n, kBlock);
+    uint32_t *loff = nullptr;
+    // individual softening: spline supports in curve order; a bad value
+    // sets the second error word, read back with the sizes below
+    c->mixed = eps != nullptr;
+    if (c->mixed)
+        TPM_TRY(ensure(c, c->hs, (size_t)n * 8));
+    Frame h{};
     if (P.periodic) {
-        Frame h{};
         for (int a = 0; a < 3; a++)
             h.x0[a] = -(P.shift[a] * P.box_size);
         h.L = P.box_size;
         h.S = 2097152.0 / P.box_size;
         h.box = P.box_size;
         h.periodic = 1;
-        c->frame_host = h;
-        TPM_HIP(c, hipMemcpyAsync(F, &c->frame_host, sizeof(Frame), hipMemcpyHostToDevice, st));
+    }
+    const bool small = n <= kSmallN;
+    if (small) {
+        TPM_TRY(timer_begin(c, TPM_TIMER_TOPOLOGY));
+        k_small_front<<<1, kSmallBlock, 0, st>>>(
+            x, y, z, mass, eps, (int)n, h, P.shift[0], P.shift[1], P.shift[2], F,
+            (uint64_t *)c->key[0].p, (int32_t *)c->perm.p, (int32_t *)c->rank.p,
+            (double *)c->ps.p, (double *)c->ms.p, (uint64_t *)c->qs.p, (double *)c->hs.p,
+            (int8_t *)c->dR.p, (uint32_t *)c->base.p, lvl_count, bad_eps, c->hpin_dev);
+        TPM_LAUNCHED(c, "k_small_front");
+        TPM_TRY(timer_end(c, TPM_TIMER_TOPOLOGY));
+    } else {
+    // 1. root cube
+    TPM_TRY(timer_begin(c, TPM_TIMER_KEYS));
+    if (P.periodic) {
+        k_set_frame<<<1, 1, 0, st>>>(h, F);
+        TPM_LAUNCHED(c, "k_set_frame");
     } else {
         const int nparts = (int)std::min<int64_t>(1024, (n + kBlock - 1) / kBlock);
         TPM_TRY(ensure(c, c->bbox, bbox_bytes(n)));
@@ -546,12 +935,6 @@ int build(tpm_ctx *c, int64_t n, const double *x, const double *y, const double 
     TPM_LAUNCHED(c, "k_keys");
     TPM_TRY(timer_end(c, TPM_TIMER_KEYS));
     TPM_TRY(radix_sort_pairs(c, n));
-    // individual softening: spline supports in curve order; a bad value
-    // sets the second error word, read back with the sizes below
-    c->mixed = eps != nullptr;
-    uint32_t *bad_eps = (uint32_t *)c->err_flag.p + 1;
-    if (c->mixed)
-        TPM_TRY(ensure(c, c->hs, (size_t)n * 8));
     TPM_TRY(timer_begin(c, TPM_TIMER_GATHER));
     k_gather<<<grid_for(n, kBlock), kBlock, 0, st>>>(
         (const double4 *)c->xyzm.p, n, F, (const uint32_t *)c->idx[0].p, (int32_t *)c->perm.p,
@@ -560,27 +943,20 @@ int build(tpm_ctx *c, int64_t n, const double *x, const double *y, const double 
     TPM_LAUNCHED(c, "k_gather");
     TPM_TRY(timer_end(c, TPM_TIMER_GATHER));
     // 4. topology: counts, scan, one readback of the sizes
-    const uint64_t *key = (const uint64_t *)c->key[0].p;
-    uint32_t *lvl_count = (uint32_t *)c->counters.p;  // [0..21] level starts, [32] E, [33] nodes
-    const uint32_t nb = grid_for(n, kBlock);
     TPM_TRY(ensure(c, c->hist, topology_hist_bytes(n)));
     uint32_t *lhist = (uint32_t *)c->hist.p;
-    uint32_t *loff = lhist + (size_t)kLevels * nb;
+    loff = lhist + (size_t)kLevels * nb;
     TPM_TRY(timer_begin(c, TPM_TIMER_TOPOLOGY));
     k_count<<<nb, kBlock, 0, st>>>(key, n, (int8_t *)c->dR.p, (uint32_t *)c->cnt.p, lhist, nb);
     TPM_LAUNCHED(c, "k_count");
     TPM_TRY(scan_u32(c, (const uint32_t *)c->cnt.p, (uint32_t *)c->base.p, n, lvl_count + 32));
     TPM_TRY(scan_u32(c, lhist, loff, (int64_t)kLevels * nb, lvl_count + 33));
-    k_level_starts<<<1, 64, 0, st>>>(loff, nb, lvl_count);
-    TPM_LAUNCHED(c, "k_level_starts");
+    k_sizes<<<1, 64, 0, st>>>(loff, nb, lvl_count + 32, F, bad_eps, c->hpin_dev);
+    TPM_LAUNCHED(c, "k_sizes");
     TPM_TRY(timer_end(c, TPM_TIMER_TOPOLOGY));
-    TPM_HIP(c, hipMemcpyAsync(c->hpin, lvl_count, 64 * sizeof(uint32_t), hipMemcpyDeviceToHost,
-                              st));
-    if (!P.periodic)
-        TPM_HIP(c, hipMemcpyAsync(&c->frame_host, F, sizeof(Frame), hipMemcpyDeviceToHost, st));
-    TPM_HIP(c, hipMemcpyAsync(c->hpin + 128, bad_eps, sizeof(uint32_t), hipMemcpyDeviceToHost,
-                              st));
+    }
     TPM_HIP(c, hipStreamSynchronize(st));
+    std::memcpy(&c->frame_host, c->hpin + 64, sizeof(Frame));
     if (c->hpin[128]) {
         TPM_TRY(fill_u32(c, bad_eps, 0u, 1));
         return fail(c, TPM_EINVAL, "softening lengths must be positive and finite");
@@ -620,6 +996,28 @@ int build(tpm_ctx *c, int64_t n, const double *x, const double *y, const double 
     if (c->mixed) {
         TPM_TRY(ensure(c, c->eh64, (size_t)E * 8));
         eh = (double *)c->eh64.p;
+    }
+    if (small && E <= kSmallE) {
+        TPM_TRY(timer_begin(c, TPM_TIMER_MOMENTS));
+        k_small_back<<<1, kSmallBlock, 0, st>>>(
+            (int)n, E, (const int8_t *)c->dR.p, (const uint32_t *)c->base.p, F, lvl_count,
+            (const double *)c->ps.p, (const double *)c->ms.p, (const uint64_t *)c->qs.p, rec,
+            (uint32_t *)c->efirst.p, (uint32_t *)c->ecount.p, (uint32_t *)c->pe.p,
+            (uint32_t *)c->lvl_list.p, (const double *)c->hs.p, eh, P.G, rec32, eh32);
+        TPM_LAUNCHED(c, "k_small_back");
+        TPM_TRY(timer_end(c, TPM_TIMER_MOMENTS));
+        c->n = n;
+        c->E = E;
+        return TPM_OK;
+    }
+    if (small) {  // too many entries for its LDS: the general kernels' level offsets
+        TPM_TRY(ensure(c, c->hist, topology_hist_bytes(n)));
+        uint32_t *lhist = (uint32_t *)c->hist.p;
+        loff = lhist + (size_t)kLevels * nb;
+        k_count<<<nb, kBlock, 0, st>>>(key, n, (int8_t *)c->dR.p, (uint32_t *)c->cnt.p, lhist,
+                                       nb);
+        TPM_LAUNCHED(c, "k_count");
+        TPM_TRY(scan_u32(c, lhist, loff, (int64_t)kLevels * nb, nullptr));
     }
     TPM_TRY(timer_begin(c, TPM_TIMER_TOPOLOGY));
     k_emit<<<grid_for(n, kBlock), kBlock, 0, st>>>(

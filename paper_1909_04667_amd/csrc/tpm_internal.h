@@ -85,6 +85,7 @@ struct tpm_ctx {
     uint32_t level_off[tpm::kLevels + 1] = {};
     // host pinned scratch for small readbacks
     uint32_t *hpin = nullptr;
+    uint32_t *hpin_dev = nullptr;  // the same memory, device address
     // device buffers
     tpm::DBuf frame;            // Frame
     tpm::DBuf bbox;             // per-block min/max partials
