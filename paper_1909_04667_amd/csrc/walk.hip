@@ -143,6 +143,59 @@ __global__ __launch_bounds__(kBlock) void k_mark(const int32_t *__restrict__ idx
     mark[rank[i]] = epoch;
 }
 
+// Small trees: the slots of the active set in one launch by one workgroup (marks
+// in LDS, then ranked) instead of four that are shorter than their gaps (mark,
+// count, compact and, after a build, clear: 20 us against 6).  The marks in
+// memory are cleared when the call asks for it, as later calls on the context
+// rely on.
+constexpr int kSelBlock = 1024;
+constexpr int64_t kSelN = 8192;       // particles
+constexpr int64_t kSelActive = 65536;  // entries of the active list
+__global__ __launch_bounds__(kSelBlock) void k_select_small(
+    const int32_t *__restrict__ idx, int n_act, int n, const int32_t *__restrict__ rank,
+    uint32_t *__restrict__ mark, int clear, uint32_t *__restrict__ act,
+    uint32_t *__restrict__ slot, uint32_t *__restrict__ d_total) {
+    __shared__ uint8_t s_m[kSelN];
+    __shared__ uint32_t s_w[kSelBlock / 64];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int r = tid; r < n; r += kSelBlock) {
+        s_m[r] = 0;
+        if (clear)
+            mark[r] = 0u;
+    }
+    __syncthreads();
+    for (int k = tid; k < n_act; k += kSelBlock) {
+        const int32_t i = idx[k];
+        if (i >= 0 && i < n)
+            s_m[rank[i]] = 1;  // out-of-range indices: reported by the output kernel
+    }
+    __syncthreads();
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    uint32_t pos = 0u;
+    for (int base = 0; base < n; base += kSelBlock) {
+        const int r = base + tid;
+        const bool f = r < n && s_m[r];
+        const uint64_t m = __ballot(f);
+        if (lane == 0)
+            s_w[w] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint32_t before = 0u, all = 0u;
+        for (int q = 0; q < kSelBlock / 64; q++) {
+            before += q < w ? s_w[q] : 0u;
+            all += s_w[q];
+        }
+        if (f) {
+            const uint32_t p = pos + before + (uint32_t)__popcll(m & lt);
+            act[p] = (uint32_t)r;
+            slot[r] = p;
+        }
+        pos += all;
+        __syncthreads();
+    }
+    if (tid == 0)
+        *d_total = pos;
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_output(
     const int32_t *__restrict__ idx, int64_t n_act, int64_t n, const int32_t *__restrict__ rank,
@@ -343,6 +396,13 @@ int work_of_ctx(tpm_ctx *c, bool results, Work &w) {
 int select_active_into(tpm_ctx *c, int64_t n_act, const int32_t *idx, const Work &w) {
     const int64_t n = c->n;
     hipStream_t st = c->stream;
+    if (n <= kSelN && n_act <= kSelActive) {
+        k_select_small<<<1, kSelBlock, 0, st>>>(idx, (int)n_act, (int)n,
+                                                (const int32_t *)c->rank.p, w.mark, w.clear, w.act,
+                                                w.slot, w.nuniq);
+        TPM_LAUNCHED(c, "k_select_small");
+        return TPM_OK;
+    }
     if (w.clear)
         TPM_TRY(fill_u32(c, w.mark, 0u, n));
     if (n_act > 0) {
