@@ -122,7 +122,7 @@ void visit_sizes(tpm_ctx *c, const tpm_params &P, int64_t n, int64_t E, bool mix
     if (mixed)
         f(c->hs, 8 * N, 0);
     // per particle: active sets, results, resident-server steps, selections
-    f(c->mark, 4 * N, 0);
+    f(c->mark, mark_bytes(n), 0);
     f(c->act, 4 * N, 0);
     f(c->slot, 4 * N, 0);
     f(c->res, 4 * (size_t)result_slots(n) * esz, 0);

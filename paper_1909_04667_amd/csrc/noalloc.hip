@@ -109,7 +109,7 @@ int tpm_compute_forces_noalloc(tpm_ctx *c, int32_t opening, int64_t n_act,
     TPM_HIP(c, hipSetDevice(c->device));
     unsigned char *s = (unsigned char *)base;
     Work w;
-    w.mark = (uint32_t *)(s + kOffMark);
+    w.mark = (uint8_t *)(s + kOffMark);
     w.epoch = 1;
     w.clear = true;  // the array keeps the marks of the last call of any context
     w.act = (uint32_t *)(s + kOffAct);

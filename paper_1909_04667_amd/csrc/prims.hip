@@ -333,32 +333,66 @@ __global__ void k_fill_u64(uint64_t *p, uint64_t v, int64_t n) {
         p[i] = v;
 }
 
-// Compaction of the slots r with mark[r] == epoch, in increasing r: phase 1
-// counts them per tile of kScanTile slots.
-__global__ __launch_bounds__(kScanBlock) void k_mark_count(const uint32_t *__restrict__ mark,
-                                                           int64_t n, uint32_t epoch,
+// Compaction of the slots r with mark[r] == epoch, in increasing r.  The marks
+// are bytes (a quarter of the lines that scattered marking touches and that
+// the two phases read), a thread takes kCompItems consecutive ones in 16-byte
+// loads, and tiles are large, since every workgroup reads all tiles' counts.
+// 16.8 M particles, 1 % active: both phases 14 us (72 us with 4-byte marks and
+// tiles of 2048).  Phase 1 counts the active slots per tile.
+constexpr int kCompItems = 32;
+constexpr int kCompTile = kScanBlock * kCompItems;  // 8192
+
+// 0x80 in the bytes of w that equal e's (e: the same byte four times).
+__device__ __forceinline__ uint32_t equal_bytes(uint32_t w, uint32_t e) {
+    const uint32_t x = w ^ e;
+    return ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);
+}
+
+// The thread's kCompItems marks of its tile as a bit mask (marks 32-byte
+// aligned per thread; beyond n: none).
+__device__ __forceinline__ uint32_t marked_bits(const uint8_t *__restrict__ mark, int64_t at,
+                                                int64_t n, uint32_t e4) {
+    uint32_t bits = 0u;
+    if (at + kCompItems <= n) {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const uint4 v = ((const uint4 *)(mark + at))[h];
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const uint32_t z = equal_bytes(w[q], e4) >> 7;
+                bits |= ((z | (z >> 7) | (z >> 14) | (z >> 21)) & 15u) << (16 * h + 4 * q);
+            }
+        }
+    } else {
+        for (int j = 0; j < kCompItems && at + j < n; j++)
+            bits |= (mark[at + j] == (uint8_t)e4 ? 1u : 0u) << j;
+    }
+    return bits;
+}
+
+__global__ __launch_bounds__(kScanBlock) void k_mark_count(const uint8_t *__restrict__ mark,
+                                                           int64_t n, uint32_t e4,
                                                            uint32_t *__restrict__ counts) {
     __shared__ uint32_t s_w[kScanBlock / 64];
-    const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    uint32_t t = 0;
-    for (int k = threadIdx.x; k < kScanTile; k += kScanBlock) {
-        const int64_t r = base + k;
-        t += (r < n && mark[r] == epoch) ? 1u : 0u;
-    }
+    const int64_t at = (int64_t)blockIdx.x * kCompTile + threadIdx.x * kCompItems;
     uint32_t excl;
-    const uint32_t tot = block_excl_scan(t, s_w, excl);
+    const uint32_t tot = block_excl_scan((uint32_t)__popc(marked_bits(mark, at, n, e4)), s_w, excl);
     if (threadIdx.x == 0)
         counts[blockIdx.x] = tot;
 }
 
 // Phase 2: a tile's offset is the sum of the earlier tiles' counts (read
 // here, a few per thread); the tile's own slots are ranked with a block scan.
-// Writes act[pos] = r and slot[r] = pos; workgroup 0 also writes the total.
+// Writes act[pos] = r and slot[r] = pos (with every particle active the slots
+// are the ranks, and slot is not read); workgroup 0 also writes the total.
+// The positions go through LDS so that a full tile is written contiguously.
 __global__ __launch_bounds__(kScanBlock) void k_mark_compact(
-    const uint32_t *__restrict__ mark, int64_t n, uint32_t epoch,
+    const uint8_t *__restrict__ mark, int64_t n, uint32_t e4,
     const uint32_t *__restrict__ counts, uint32_t *__restrict__ act,
     uint32_t *__restrict__ slot, uint32_t *__restrict__ d_total) {
     __shared__ uint32_t s_w[kScanBlock / 64];
+    __shared__ uint16_t s_r[kCompTile];
     const uint32_t b = blockIdx.x, nb = gridDim.x;
     uint32_t before = 0, all = 0;
     for (uint32_t q = threadIdx.x; q < nb; q += kScanBlock) {
@@ -371,21 +405,20 @@ __global__ __launch_bounds__(kScanBlock) void k_mark_compact(
     const uint32_t total = block_excl_scan(all, s_w, excl);
     if (b == 0 && threadIdx.x == 0)
         *d_total = total;
-    // kScanItems rounds of kScanBlock consecutive slots: lanes take
-    // consecutive slots, so the outputs of a full set are written contiguously
-    const int64_t base = (int64_t)b * kScanTile;
-    uint32_t pos = off;
-#pragma unroll
-    for (int j = 0; j < kScanItems; j++) {
-        const int64_t r = base + j * kScanBlock + threadIdx.x;
-        const uint32_t f = (r < n && mark[r] == epoch) ? 1u : 0u;
-        uint32_t ex;
-        const uint32_t tot = block_excl_scan(f, s_w, ex);
-        if (f) {
-            act[pos + ex] = (uint32_t)r;
-            slot[r] = pos + ex;
-        }
-        pos += tot;
+    const int64_t base = (int64_t)b * kCompTile;
+    uint32_t bits = marked_bits(mark, base + threadIdx.x * kCompItems, n, e4);
+    uint32_t ex;
+    const uint32_t tot = block_excl_scan((uint32_t)__popc(bits), s_w, ex);
+    while (bits) {
+        s_r[ex++] = (uint16_t)(threadIdx.x * kCompItems + __builtin_ctz(bits));
+        bits &= bits - 1u;
+    }
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < tot; k += kScanBlock) {
+        const uint32_t r = (uint32_t)base + s_r[k];
+        act[off + k] = r;
+        if (total != (uint32_t)n)
+            slot[r] = off + k;
     }
 }
 
@@ -393,14 +426,15 @@ __global__ __launch_bounds__(kScanBlock) void k_mark_compact(
 
 int64_t compaction_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
 
-int compact_marked(tpm_ctx *c, const uint32_t *mark, uint32_t epoch, int64_t n, uint32_t *act,
+int compact_marked(tpm_ctx *c, const uint8_t *mark, uint8_t epoch, int64_t n, uint32_t *act,
                    uint32_t *slot, uint32_t *d_total, uint32_t *counts) {
     if (n <= 0)
         return fill_u32(c, d_total, 0u, 1);
-    const int64_t nb = compaction_tiles(n);
-    k_mark_count<<<(unsigned)nb, kScanBlock, 0, c->stream>>>(mark, n, epoch, counts);
+    const int64_t nb = (n + kCompTile - 1) / kCompTile;  // <= compaction_tiles(n)
+    const uint32_t e4 = epoch * 0x01010101u;
+    k_mark_count<<<(unsigned)nb, kScanBlock, 0, c->stream>>>(mark, n, e4, counts);
     TPM_LAUNCHED(c, "k_mark_count");
-    k_mark_compact<<<(unsigned)nb, kScanBlock, 0, c->stream>>>(mark, n, epoch, counts, act, slot,
+    k_mark_compact<<<(unsigned)nb, kScanBlock, 0, c->stream>>>(mark, n, e4, counts, act, slot,
                                                                d_total);
     TPM_LAUNCHED(c, "k_mark_compact");
     return TPM_OK;

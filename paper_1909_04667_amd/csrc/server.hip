@@ -89,7 +89,7 @@ struct alignas(128) SrvReq {
     WalkArgs A;
     const int32_t *idx;   // caller's active list [n_act]
     const int32_t *rank;  // build index -> rank
-    uint32_t *mark;
+    uint8_t *mark;
     uint32_t *slot;
     uint32_t *counts;
     void *acc;            // [3][n_act], the precision of the server
@@ -309,7 +309,7 @@ __device__ __forceinline__ void item_clear(const SrvReq &R, uint32_t it) {
     const int lane = threadIdx.x & 63;
     const uint32_t n = R.A.n;
     for (uint32_t k = it * kSrvChunk + lane; k < min(n, (it + 1) * kSrvChunk); k += 64)
-        coherent_st(R.mark + k, 0u);
+        coherent_st(R.mark + k, (uint8_t)0);
 }
 
 __device__ __forceinline__ void item_mark(const SrvReq &R, uint32_t it) {
@@ -318,7 +318,7 @@ __device__ __forceinline__ void item_mark(const SrvReq &R, uint32_t it) {
     for (uint32_t k = it * kSrvChunk + lane; k < min(R.n_act, (it + 1) * kSrvChunk); k += 64) {
         const int32_t i = R.idx[k];
         if (i >= 0 && (uint32_t)i < n)
-            coherent_st(R.mark + R.rank[i], R.epoch);  // out-of-range indices: the output phase
+            coherent_st(R.mark + R.rank[i], (uint8_t)R.epoch);  // out-of-range indices: the output phase
     }
 }
 

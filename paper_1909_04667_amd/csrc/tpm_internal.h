@@ -77,7 +77,7 @@ struct tpm_ctx {
     int64_t E = 0;          // depth-first entries of the last build
     int built = 0;
     int pm_ready = 0;
-    uint32_t epoch = 0;     // active-set marking generation
+    uint8_t epoch = 0;      // active-set marking generation
     int walk_mode = 0;      // 0: automatic, 1: shared cursor, 2: independent lanes,
                             // 3: one wavefront per target
     tpm::Frame frame_host{};
@@ -170,8 +170,8 @@ void bump_memory_epoch();
 // results in slot order.  Either the context's own buffers (allocated on
 // demand) or a fixed region the caller provides.
 struct Work {
-    uint32_t *mark = nullptr;   // [n] epoch marks
-    uint32_t epoch = 0;         // the mark of this call
+    uint8_t *mark = nullptr;    // [n] epoch marks (rounded up to whole 16-byte words)
+    uint8_t epoch = 0;          // the mark of this call
     bool clear = false;         // clear the marks [0, n) before marking
     uint32_t *act = nullptr;    // [n] active slots in curve order
     uint32_t *slot = nullptr;   // [n] rank -> position in act
@@ -182,6 +182,9 @@ struct Work {
                                 // one plane per share of the walk
     void *rpot = nullptr;       // [result_slots(n)]
 };
+
+// Bytes of the marks of n particles.
+inline size_t mark_bytes(int64_t n) { return ((size_t)n + 15) & ~size_t(15); }
 
 // Walks of small sets are divided into shares (walk_device.h), at most eight and
 // at most 3 2^18 records altogether: slots of the results of a tree of n.
@@ -196,7 +199,7 @@ int scan_u32(tpm_ctx *c, const uint32_t *in, uint32_t *out, int64_t n, uint32_t 
 // act[0 .. total) = the slots r < n with mark[r] == epoch, increasing;
 // slot[r] = the position of r in act; the total goes to *d_total (device);
 // counts: compaction_tiles(n) words of scratch.
-int compact_marked(tpm_ctx *c, const uint32_t *mark, uint32_t epoch, int64_t n, uint32_t *act,
+int compact_marked(tpm_ctx *c, const uint8_t *mark, uint8_t epoch, int64_t n, uint32_t *act,
                    uint32_t *slot, uint32_t *d_total, uint32_t *counts);
 int64_t compaction_tiles(int64_t n);
 // Stable ascending sort of (key, value) pairs; result lands in key[0]/idx[0].

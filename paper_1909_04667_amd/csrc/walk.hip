@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kBlock) void k_walk32s(const WalkArgs A) {
 
 __global__ __launch_bounds__(kBlock) void k_mark(const int32_t *__restrict__ idx, int64_t n_act,
                                                  int64_t n, const int32_t *__restrict__ rank,
-                                                 uint32_t *__restrict__ mark, uint32_t epoch) {
+                                                 uint8_t *__restrict__ mark, uint8_t epoch) {
     int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= n_act)
         return;
@@ -153,7 +153,7 @@ constexpr int64_t kSelN = 8192;       // particles
 constexpr int64_t kSelActive = 65536;  // entries of the active list
 __global__ __launch_bounds__(kSelBlock) void k_select_small(
     const int32_t *__restrict__ idx, int n_act, int n, const int32_t *__restrict__ rank,
-    uint32_t *__restrict__ mark, int clear, uint32_t *__restrict__ act,
+    uint8_t *__restrict__ mark, int clear, uint32_t *__restrict__ act,
     uint32_t *__restrict__ slot, uint32_t *__restrict__ d_total) {
     __shared__ uint8_t s_m[kSelN];
     __shared__ uint32_t s_w[kSelBlock / 64];
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kSelBlock) void k_select_small(
     for (int r = tid; r < n; r += kSelBlock) {
         s_m[r] = 0;
         if (clear)
-            mark[r] = 0u;
+            mark[r] = 0;
     }
     __syncthreads();
     for (int k = tid; k < n_act; k += kSelBlock) {
@@ -367,7 +367,7 @@ int accel_norm(tpm_ctx *c, int64_t n_act, const int32_t *idx, const void *a, con
 
 int work_of_ctx(tpm_ctx *c, bool results, Work &w) {
     const int64_t n = c->n;
-    TPM_TRY(ensure(c, c->mark, (size_t)n * 4));
+    TPM_TRY(ensure(c, c->mark, mark_bytes(n)));
     TPM_TRY(ensure(c, c->act, (size_t)n * 4));
     TPM_TRY(ensure(c, c->slot, (size_t)n * 4));
     TPM_TRY(ensure(c, c->scan_tmp, (size_t)compaction_tiles(n) * 4));
@@ -377,7 +377,7 @@ int work_of_ctx(tpm_ctx *c, bool results, Work &w) {
         TPM_TRY(ensure(c, c->rpot, (size_t)result_slots(n) * esz));
     }
     w = Work{};
-    w.mark = (uint32_t *)c->mark.p;
+    w.mark = (uint8_t *)c->mark.p;
     w.clear = false;
     if (++c->epoch == 0 || c->epoch == 1) {  // fresh or wrapped: clear the marks
         w.clear = true;
@@ -404,7 +404,7 @@ int select_active_into(tpm_ctx *c, int64_t n_act, const int32_t *idx, const Work
         return TPM_OK;
     }
     if (w.clear)
-        TPM_TRY(fill_u32(c, w.mark, 0u, n));
+        TPM_TRY(fill_u32(c, (uint32_t *)w.mark, 0u, (int64_t)(mark_bytes(n) / 4)));
     if (n_act > 0) {
         k_mark<<<grid_for(n_act, kBlock), kBlock, 0, st>>>(idx, n_act, n,
                                                            (const int32_t *)c->rank.p, w.mark,

@@ -338,6 +338,27 @@ def test_active_subsets_and_duplicates():
     ctx.check()
 
 
+@pytest.mark.parametrize("n", [8192, 8193, 8192 + 31, 3 * 8192 - 1, 40001])
+def test_active_slots_over_many_calls(n):
+    """The marks of the active set are bytes that count calls: more calls than a
+    byte holds, each with another set (none, one, ragged runs, all), select
+    exactly that set -- counts as the full set's at the same targets, in the
+    caller's order."""
+    p = W.uniform_cube(n, 53)
+    ctx = _ctx(precision="fp32", eps=0.01, theta=1.5)
+    _build(ctx, p)
+    full = torch.empty(n, dtype=torch.int32, device=_dev())
+    ctx.compute_forces(_t(np.arange(n), torch.int32), "bh", n_interactions=full)
+    g = torch.Generator(device=_dev()).manual_seed(7)
+    for call in range(530):
+        k = (1, 2, 33, 700, n)[call % 5]
+        ids = torch.randperm(n, generator=g, device=_dev())[:k].to(torch.int32)
+        got = torch.full((k,), -1, dtype=torch.int32, device=_dev())
+        ctx.compute_forces(ids, "bh", n_interactions=got)
+        assert torch.equal(got, full[ids.long()]), call
+    ctx.check()
+
+
 @pytest.mark.parametrize("n", [4097, 65536, 65537, 196609, 262145])
 @pytest.mark.parametrize("mesh", [0, 16])
 def test_shares_of_a_walk(n, mesh, monkeypatch):
