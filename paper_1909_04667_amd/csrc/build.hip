@@ -11,6 +11,7 @@
 // subtree) come from a galloping search for the end of each prefix run.
 #include "tpm_internal.h"
 
+#include <algorithm>
 #include <cstring>
 #include <vector>
 
@@ -257,15 +258,37 @@ __device__ __forceinline__ int common_levels(uint64_t a, uint64_t b) {
     return (kMaxLevel - 1) - top / 3;
 }
 
+// The smallest depth shared by neighbours from this thread's particle to the
+// end of its workgroup's kBlock particles (r: the depth shared with the right
+// neighbour).  A node of level lev ends inside them if lev is larger.
+__device__ __forceinline__ int suffix_min(int r, int *s_w) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int m = r;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_down(m, o, 64);
+        m = lane + o < 64 ? min(m, t) : m;
+    }
+    if (lane == 0)
+        s_w[w] = m;
+    __syncthreads();
+    for (int q = w + 1; q < kBlock / 64; q++)
+        m = min(m, s_w[q]);
+    __syncthreads();
+    return m;
+}
+
 // Per particle: depth shared with the right neighbour, entries it starts
 // (nodes at levels (dL, dR] plus itself), and per block and level the number
-// of nodes its particles start: hist[level * nb + block] (a counting sort by
-// level, so node lists come out in particle order without global atomics).
+// of nodes its particles start that end beyond the block: hist[level * nb + block]
+// (a counting sort by level, so node lists come out in particle order without
+// global atomics).  The others' moments are summed where they are emitted.
 __global__ __launch_bounds__(kBlock) void k_count(const uint64_t *__restrict__ key, int64_t n,
                                                   int8_t *__restrict__ dR,
                                                   uint32_t *__restrict__ cnt,
                                                   uint32_t *__restrict__ hist, uint32_t nb) {
     __shared__ uint32_t h[kLevels][kBlock / 64];
+    __shared__ int s_w[kBlock / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     int r = -1, l = -1;
@@ -277,8 +300,9 @@ __global__ __launch_bounds__(kBlock) void k_count(const uint64_t *__restrict__ k
         const int nn = r > l ? r - l : 0;
         cnt[s] = (uint32_t)nn + 1u;
     }
+    const int top = min(r, suffix_min(r, s_w));
     for (int lev = 0; lev < kLevels; lev++) {
-        const uint64_t m = __ballot(lev > l && lev <= r);
+        const uint64_t m = __ballot(lev > l && lev <= top);
         if (lane == 0)
             h[lev][w] = (uint32_t)__popcll(m);
     }
@@ -328,21 +352,40 @@ __device__ __forceinline__ void rec32_centre(Rec32 &o, const uint32_t q[3], int 
     o.cz = (int32_t)((uint32_t)C[2] << sh);
 }
 
+// Node record without its moments: the centre of the level-lev cell that holds
+// the integer position q.
+__device__ __forceinline__ void node_record(Rec64 &R, const uint32_t q[3], int lev,
+                                            const Frame &F) {
+    const double len = ldexp(F.L, -lev);
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        R.cen[a] = F.x0[a] + ((double)(q[a] >> (kBits - lev)) + 0.5) * len;
+        R.com[a] = 0.0;
+    }
+    R.mass = 0.0;
+    R.skip = 0u;  // set with the moments
+    R.meta = (uint32_t)lev;
+}
+
 // The entries that particle s (slot) starts, from entry b on: its nodes of
-// levels l + 1 .. r (the depths it shares with its left and right neighbours)
-// and itself.
+// levels l + 1 .. r (the depths it shares with its left and right neighbours;
+// written here, without moments, those up to level top) and itself.  FP32
+// contexts (out32 set): a particle's FP32 record is written here, a node's with
+// its moments.  q: the particle's integer position.
 __device__ __forceinline__ void emit_particle(
-    int64_t s, int64_t n, int l, int r, uint32_t b, const Frame &F,
+    int64_t s, int64_t n, int l, int top, int r, uint32_t b, const Frame &F,
     const double *__restrict__ ps, const double *__restrict__ ms,
     const uint64_t *__restrict__ qs, Rec64 *__restrict__ rec, uint32_t *__restrict__ efirst,
     uint32_t *__restrict__ ecount, uint32_t *__restrict__ pe, const double *__restrict__ hs,
-    double *__restrict__ eh, double G, Rec32 *__restrict__ out32, float *__restrict__ eh32) {
+    double *__restrict__ eh, double G, Rec32 *__restrict__ out32, float *__restrict__ eh32,
+    uint32_t q[3]) {
     const int nn = r > l ? r - l : 0;
     const uint32_t ep = b + (uint32_t)nn;
     const int sh = F.periodic ? kRecShiftPer : kRecShiftIso;
     const uint64_t qq = qs[s];
-    const uint32_t q[3] = {(uint32_t)(qq >> 42) & 0x1fffffu, (uint32_t)(qq >> 21) & 0x1fffffu,
-                           (uint32_t)qq & 0x1fffffu};
+    q[0] = (uint32_t)(qq >> 42) & 0x1fffffu;
+    q[1] = (uint32_t)(qq >> 21) & 0x1fffffu;
+    q[2] = (uint32_t)qq & 0x1fffffu;
     {
         Rec64 R;
         R.com[0] = ps[s];
@@ -374,80 +417,22 @@ __device__ __forceinline__ void emit_particle(
                 eh32[ep] = (float)hs[s];
         }
     }
-    for (int lev = l + 1; lev <= r; ++lev) {
+    for (int lev = l + 1; lev <= top; ++lev) {
         const uint32_t e = b + (uint32_t)(lev - l - 1);
         Rec64 R;
-        const double len = ldexp(F.L, -lev);
-#pragma unroll
-        for (int a = 0; a < 3; a++) {
-            const uint32_t P_a = q[a] >> (kBits - lev);
-            R.cen[a] = F.x0[a] + ((double)P_a + 0.5) * len;
-            R.com[a] = 0.0;
-        }
-        R.mass = 0.0;
-        R.skip = 0u;  // set by k_moments
-        R.meta = (uint32_t)lev;
+        node_record(R, q, lev, F);
         rec[e] = R;
         efirst[e] = (uint32_t)s;
     }
 }
 
-// Emit the particle entry and the node entries a particle starts.  Skip
-// pointers and counts of nodes are filled bottom-up by k_moments: every
-// entry carries a depth (nodes: their level; a particle: the level of the
-// cell it occupies alone, one below its deepest shared prefix), and the
-// subtree of a node of level l ends at the first later entry of depth <= l.
-// FP32 contexts (out32 set): a particle's FP32 record is written here, a
-// node's by k_moments.
-__global__ __launch_bounds__(kBlock) void k_emit(
-    const uint64_t *__restrict__ key, int64_t n, const int8_t *__restrict__ dR,
-    const uint32_t *__restrict__ base, const Frame *__restrict__ Fp,
-    const double *__restrict__ ps, const double *__restrict__ ms,
-    const uint64_t *__restrict__ qs, Rec64 *__restrict__ rec, uint32_t *__restrict__ efirst,
-    uint32_t *__restrict__ ecount, uint32_t *__restrict__ pe,
-    const uint32_t *__restrict__ loff, uint32_t nb, uint32_t *__restrict__ lvl_list,
-    const double *__restrict__ hs, double *__restrict__ eh, double G, Rec32 *__restrict__ out32,
-    float *__restrict__ eh32) {
-    __shared__ uint32_t h[kLevels][kBlock / 64];
-    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool live = s < n;
-    const int r = live ? (int)dR[s] : -1;
-    const int l = (live && s > 0) ? (int)dR[s - 1] : -1;
-    const uint32_t b = live ? base[s] : 0u;
-    // level lists in particle order: block offset (scanned histogram) +
-    // preceding wavefronts of the block + preceding lanes of the wavefront
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    for (int lev = 0; lev < kLevels; lev++) {
-        const uint64_t m = __ballot(lev > l && lev <= r);
-        if (lane == 0)
-            h[lev][w] = (uint32_t)__popcll(m);
-    }
-    __syncthreads();
-    for (int lev = 0; lev < kLevels; lev++) {
-        const bool has = lev > l && lev <= r;
-        const uint64_t m = __ballot(has);
-        if (has) {
-            uint32_t at = loff[(size_t)lev * nb + blockIdx.x];
-            for (int q = 0; q < w; q++)
-                at += h[lev][q];
-            lvl_list[at + (uint32_t)__popcll(m & lt)] = b + (uint32_t)(lev - l - 1);
-        }
-    }
-    if (!live)
-        return;
-    emit_particle(s, n, l, r, b, *Fp, ps, ms, qs, rec, efirst, ecount, pe, hs, eh, G, out32, eh32);
-}
-
 // Writes node e's records from its sums over the children; k: the entry
-// after its subtree, f: its first particle.
-__device__ __forceinline__ void finish_node(Rec64 *rec, uint32_t e, uint32_t k, uint32_t E,
-                                            uint32_t n, uint32_t f, uint32_t lev, Rec64 R,
-                                            double M, double X0, double X1, double X2,
-                                            double hmax, uint64_t qq, const uint32_t *efirst,
+// after its subtree, cnt: its particles, q: an integer position in it.
+__device__ __forceinline__ void finish_node(Rec64 *rec, uint32_t e, uint32_t k, uint32_t cnt,
+                                            uint32_t lev, Rec64 R, double M, double X0, double X1,
+                                            double X2, double hmax, const uint32_t q[3],
                                             uint32_t *ecount, double *eh, double G, int sh,
                                             Rec32 *out32, float *eh32) {
-    const uint32_t cnt = (k < E ? efirst[k] : n) - f;
     const bool leaf_parent = k - e - 1u == cnt;  // no entry below but the particles themselves
     R.mass = M;
     R.com[0] = X0 / M;
@@ -460,8 +445,6 @@ __device__ __forceinline__ void finish_node(Rec64 *rec, uint32_t e, uint32_t k, 
     if (eh)
         eh[e] = hmax;
     if (out32) {  // exact integer centre from the node's first particle
-        const uint32_t q[3] = {(uint32_t)(qq >> 42) & 0x1fffffu,
-                               (uint32_t)(qq >> 21) & 0x1fffffu, (uint32_t)qq & 0x1fffffu};
         Rec32 o;
         rec32_centre(o, q, (int)lev, sh, false);
         o.dx = (float)(R.com[0] - R.cen[0]);
@@ -476,8 +459,146 @@ __device__ __forceinline__ void finish_node(Rec64 *rec, uint32_t e, uint32_t k, 
     }
 }
 
-// Nodes of one level (deepest level first): walk the children through their
-// skip pointers (all deeper, so already final), sum the monopole moments in
+// Emits the entries of kBlock particles in curve order, and sums the moments of
+// the nodes that end inside them (nine in ten or more): level by level, deepest
+// first, a thread per particle taking the node it starts at that level, the
+// children's sums, subtree ends and particle counts in LDS, so that a record is
+// written once, whole.  Summed by one launch per level, every node read its
+// children's records from memory again: 256^3 clustered particles, topology and
+// moments 3.11 -> 1.81 ms.  Nodes that end beyond go, without moments, to the level
+// lists of k_moments.  Every entry carries a depth (nodes: their level; a
+// particle: the level of the cell it occupies alone, one below its deepest
+// shared prefix), and the subtree of a node of level l ends at the first later
+// entry of depth <= l.  kLocal: entries that LDS holds (a block's particles
+// start 1.1 to 1.7 entries each in the workloads); a block with more works on
+// its records in memory.
+constexpr uint32_t kLocal = 640;
+template <bool MIXED>
+__global__ __launch_bounds__(kBlock) void k_emit(
+    int64_t n, uint32_t E, const int8_t *__restrict__ dR, const uint32_t *__restrict__ base,
+    const Frame *__restrict__ Fp, const double *__restrict__ ps, const double *__restrict__ ms,
+    const uint64_t *__restrict__ qs, Rec64 *rec, uint32_t *efirst, uint32_t *ecount,
+    uint32_t *__restrict__ pe, const uint32_t *__restrict__ loff, uint32_t nb,
+    uint32_t *__restrict__ lvl_list, const double *__restrict__ hs, double *eh, double G,
+    Rec32 *out32, float *eh32) {
+    __shared__ uint32_t h[kLevels][kBlock / 64];
+    __shared__ int s_w[kBlock / 64];
+    __shared__ uint32_t s_levels;
+    __shared__ double s_m[4][kLocal], s_h[MIXED ? kLocal : 1];
+    __shared__ uint32_t s_skip[kLocal];
+    __shared__ uint16_t s_cnt[kLocal];
+    __shared__ uint8_t s_dep[kLocal];
+    const int64_t s0 = (int64_t)blockIdx.x * kBlock;
+    const int64_t s = s0 + threadIdx.x, s1 = s0 + kBlock < n ? s0 + kBlock : n;
+    const bool live = s < n;
+    const int r = live ? (int)dR[s] : -1;
+    const int l = (live && s > 0) ? (int)dR[s - 1] : -1;
+    const uint32_t b = live ? base[s] : 0u;
+    const uint32_t e0 = base[s0], e1 = s1 < n ? base[s1] : E;  // the block's entries
+    const bool lds = e1 - e0 <= kLocal;
+    const int top = min(r, suffix_min(r, s_w));  // nodes of levels (l, top] end beyond
+    // level lists in particle order: block offset (scanned histogram) +
+    // preceding wavefronts of the block + preceding lanes of the wavefront
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    if (threadIdx.x == 0)
+        s_levels = 0u;
+    for (int lev = 0; lev < kLevels; lev++) {
+        const uint64_t m = __ballot(lev > l && lev <= top);
+        if (lane == 0)
+            h[lev][w] = (uint32_t)__popcll(m);
+    }
+    __syncthreads();
+    for (int lev = 0; lev < kLevels; lev++) {
+        const bool has = lev > l && lev <= top;
+        const uint64_t m = __ballot(has);
+        if (has) {
+            uint32_t at = loff[(size_t)lev * nb + blockIdx.x];
+            for (int q = 0; q < w; q++)
+                at += h[lev][q];
+            lvl_list[at + (uint32_t)__popcll(m & lt)] = b + (uint32_t)(lev - l - 1);
+        }
+    }
+    const int from = max(l, top);  // nodes of levels (from, r] are summed here
+    if (live && r > from)
+        atomicOr(&s_levels, (1u << (r + 1)) - (1u << (from + 1)));
+    const Frame F = *Fp;
+    uint32_t q[3] = {0u, 0u, 0u};
+    if (live) {
+        emit_particle(s, n, l, lds ? top : r, r, b, F, ps, ms, qs, rec, efirst, ecount, pe, hs,
+                      eh, G, out32, eh32, q);
+        if (lds) {
+            for (int lev = l + 1; lev <= r; lev++)
+                s_dep[b - e0 + (uint32_t)(lev - l - 1)] = (uint8_t)lev;
+            const uint32_t a = b - e0 + (uint32_t)(r > l ? r - l : 0);
+            s_m[0][a] = ms[s];
+            s_m[1][a] = ps[s];
+            s_m[2][a] = ps[n + s];
+            s_m[3][a] = ps[2 * n + s];
+            if (MIXED)
+                s_h[a] = hs[s];
+            s_skip[a] = a + 1u;
+            s_cnt[a] = 1;
+            s_dep[a] = (uint8_t)((r > l ? r : l) + 1);
+        }
+    }
+    __syncthreads();
+    const int sh = F.periodic ? kRecShiftPer : kRecShiftIso;
+    for (uint32_t todo = s_levels; todo;) {
+        const int lev = 31 - __clz((int)todo);
+        todo &= ~(1u << lev);
+        if (lev > from && lev <= r) {
+            const uint32_t e = b + (uint32_t)(lev - l - 1);
+            double M = 0.0, X0 = 0.0, X1 = 0.0, X2 = 0.0, hmax = 0.0;
+            uint32_t k, cnt;
+            if (lds) {
+                cnt = 0u;
+                for (k = e - e0 + 1u; k < e1 - e0 && s_dep[k] > lev; k = s_skip[k]) {
+                    const double mk = s_m[0][k];
+                    if (MIXED)
+                        hmax = s_h[k] > hmax ? s_h[k] : hmax;
+                    M = M + mk;
+                    X0 = fma(mk, s_m[1][k], X0);
+                    X1 = fma(mk, s_m[2][k], X1);
+                    X2 = fma(mk, s_m[3][k], X2);
+                    cnt += s_cnt[k];
+                }
+                k += e0;
+            } else {
+                for (k = e + 1u; k < e1 && (int)(rec[k].meta & 0xffu) > lev; k = rec[k].skip) {
+                    const double mk = rec[k].mass;
+                    if (MIXED)
+                        hmax = eh[k] > hmax ? eh[k] : hmax;
+                    M = M + mk;
+                    X0 = fma(mk, rec[k].com[0], X0);
+                    X1 = fma(mk, rec[k].com[1], X1);
+                    X2 = fma(mk, rec[k].com[2], X2);
+                }
+                cnt = (k < e1 ? efirst[k] : (uint32_t)s1) - (uint32_t)s;
+            }
+            Rec64 R;
+            node_record(R, q, lev, F);
+            finish_node(rec, e, k, cnt, (uint32_t)lev, R, M, X0, X1, X2, hmax, q, ecount,
+                        MIXED ? eh : nullptr, G, sh, out32, eh32);
+            if (lds) {
+                efirst[e] = (uint32_t)s;
+                const uint32_t a = e - e0;
+                s_m[0][a] = M;
+                s_m[1][a] = X0 / M;
+                s_m[2][a] = X1 / M;
+                s_m[3][a] = X2 / M;
+                if (MIXED)
+                    s_h[a] = hmax;
+                s_skip[a] = k - e0;
+                s_cnt[a] = (uint16_t)cnt;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// A node of the level lists (deepest level first): walk the children through
+// their skip pointers (all deeper, so already final), sum the monopole moments in
 // curve order -- M = (M1 + M2) + ..., X = fma(M_k, s_k, X), s = X / M -- and
 // set the node's particle count, skip pointer and leaf-parent flag.  With individual
 // softening the node also takes the largest spline support of its children.
@@ -487,19 +608,10 @@ __device__ __forceinline__ void finish_node(Rec64 *rec, uint32_t e, uint32_t k, 
 // FP32 contexts (out32 set): the node's FP32 record is written too (exact
 // integer centre from its first particle's cell, float offset of the centre of
 // mass from it, G m, skip, leaf-parent flag).
-__global__ __launch_bounds__(kBlock) void k_moments(Rec64 *__restrict__ rec, uint32_t E,
-                                                    uint32_t n, const uint32_t *__restrict__ efirst,
-                                                    uint32_t *__restrict__ ecount,
-                                                    const uint32_t *__restrict__ list,
-                                                    uint32_t count, uint32_t lev,
-                                                    double *__restrict__ eh, double G,
-                                                    const uint64_t *__restrict__ qs, int sh,
-                                                    Rec32 *__restrict__ out32,
-                                                    float *__restrict__ eh32) {
-    uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= count)
-        return;
-    const uint32_t e = list[i];
+__device__ __forceinline__ void sum_node(Rec64 *rec, uint32_t e, uint32_t E, uint32_t n,
+                                         const uint32_t *efirst, uint32_t *ecount, uint32_t lev,
+                                         double *eh, double G, const uint64_t *qs, int sh,
+                                         Rec32 *out32, float *eh32) {
     // what does not depend on the children first, so that its loads overlap
     // the walk over them
     Rec64 R = rec[e];
@@ -517,10 +629,44 @@ __global__ __launch_bounds__(kBlock) void k_moments(Rec64 *__restrict__ rec, uin
         X2 = fma(mk, rec[k].com[2], X2);
         k = rec[k].skip;
     }
-    finish_node(rec, e, k, E, n, f, lev, R, M, X0, X1, X2, hmax, qq, efirst, ecount, eh, G, sh, out32,
-                eh32);
+    const uint32_t q[3] = {(uint32_t)(qq >> 42) & 0x1fffffu, (uint32_t)(qq >> 21) & 0x1fffffu,
+                           (uint32_t)qq & 0x1fffffu};
+    finish_node(rec, e, k, (k < E ? efirst[k] : n) - f, lev, R, M, X0, X1, X2, hmax, q, ecount, eh,
+                G, sh, out32, eh32);
 }
 
+__global__ __launch_bounds__(kBlock) void k_moments(Rec64 *rec, uint32_t E, uint32_t n,
+                                                    const uint32_t *efirst, uint32_t *ecount,
+                                                    const uint32_t *__restrict__ list,
+                                                    uint32_t count, uint32_t lev, double *eh,
+                                                    double G, const uint64_t *__restrict__ qs,
+                                                    int sh, Rec32 *out32, float *eh32) {
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < count)
+        sum_node(rec, list[i], E, n, efirst, ecount, lev, eh, G, qs, sh, out32, eh32);
+}
+
+// Consecutive levels of at most kRunNodes nodes each in one launch by one
+// workgroup, a barrier between them: a launch of its own takes each level 7 us,
+// however few its nodes, against 5 here (moments of 100,000 particles 125 -> 104
+// us, of 50,001 78 -> 63; with 1024 nodes a level, of 2^20 157 -> 181).
+constexpr int kRunNodes = 256;
+struct LevelOffsets {
+    uint32_t off[kLevels + 1];
+};
+__global__ __launch_bounds__(kRunNodes) void k_moments_run(
+    Rec64 *rec, uint32_t E, uint32_t n, const uint32_t *efirst, uint32_t *ecount,
+    const uint32_t *__restrict__ list, LevelOffsets lo, int deepest, int top, double *eh, double G,
+    const uint64_t *__restrict__ qs, int sh, Rec32 *out32, float *eh32) {
+    for (int lev = deepest; lev >= top; lev--) {
+        const uint32_t i = lo.off[lev] + threadIdx.x;
+        if (lo.off[lev] == lo.off[lev + 1])
+            continue;
+        if (i < lo.off[lev + 1])
+            sum_node(rec, list[i], E, n, efirst, ecount, (uint32_t)lev, eh, G, qs, sh, out32, eh32);
+        __syncthreads();
+    }
+}
 
 // ---- trees of at most kSmallN particles: one workgroup ---------------------------
 //
@@ -786,8 +932,9 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_back(
     for (int s = tid; s < n; s += kSmallBlock) {
         const int r = dR[s], l = s > 0 ? (int)dR[s - 1] : -1;
         const uint32_t b = base[s];
-        emit_particle(s, n, l, r, b, F, ps, ms, qs, rec, efirst, ecount, pe, hs, eh, G, out32,
-                      eh32);
+        uint32_t q[3];
+        emit_particle(s, n, l, r, r, b, F, ps, ms, qs, rec, efirst, ecount, pe, hs, eh, G, out32,
+                      eh32, q);
         for (int lev = l + 1; lev <= r; lev++) {
             const uint32_t e = b + (uint32_t)(lev - l - 1);
             lvl_list[atomicAdd(&s_cur[lev], 1u)] = e;
@@ -843,8 +990,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_back(
                     break;
             }
             s_skip[e] = k;
-            finish_node(rec, e, k, E, (uint32_t)n, f, (uint32_t)lev, R, M, X0, X1, X2, hmax, qq,
-                        efirst, ecount, eh, G, sh, out32, eh32);
+            const uint32_t q[3] = {(uint32_t)(qq >> 42) & 0x1fffffu,
+                                   (uint32_t)(qq >> 21) & 0x1fffffu, (uint32_t)qq & 0x1fffffu};
+            finish_node(rec, e, k, (k < E ? efirst[k] : (uint32_t)n) - f, (uint32_t)lev, R, M, X0,
+                        X1, X2, hmax, q, ecount, eh, G, sh, out32, eh32);
         }
         __syncthreads();
     }
@@ -858,6 +1007,15 @@ size_t topology_hist_bytes(int64_t n) {
 
 size_t bbox_bytes(int64_t n) {
     return (size_t)std::min<int64_t>(1024, (n + kBlock - 1) / kBlock) * 6 * sizeof(double);
+}
+
+// The level lists' offsets from the sizes read back.
+static void set_levels(tpm_ctx *c) {
+    for (int l = 0; l < kLevels; l++)
+        c->level_off[l] = c->hpin[l];
+    c->level_off[kLevels] = c->hpin[33];
+    for (int l = 0; l < kLevels; l++)
+        c->level_count[l] = c->level_off[l + 1] - c->level_off[l];
 }
 
 int build(tpm_ctx *c, int64_t n, const double *x, const double *y, const double *z,
@@ -967,14 +1125,10 @@ int build(tpm_ctx *c, int64_t n, const double *x, const double *y, const double 
         !(c->frame_host.L >= 0x1p-80 && c->frame_host.L <= 0x1p+80))
         return fail(c, TPM_EINVAL, "FP32 path: root cube size outside [2^-80, 2^80]");
     const uint32_t E = c->hpin[32];
-    const uint32_t nodes = c->hpin[33];
-    if ((uint64_t)E != (uint64_t)n + nodes)
+    const uint32_t nodes = c->hpin[33];  // in the level lists
+    if (E < (uint64_t)n || (uint64_t)E - (uint64_t)n < nodes)
         return fail(c, TPM_EDEVICE, "tree build: entry count mismatch");
-    for (int l = 0; l < kLevels; l++)
-        c->level_off[l] = c->hpin[l];
-    c->level_off[kLevels] = nodes;
-    for (int l = 0; l < kLevels; l++)
-        c->level_count[l] = c->level_off[l + 1] - c->level_off[l];
+    set_levels(c);
     const uint32_t off = nodes;
     TPM_TRY(ensure(c, c->rec64, (size_t)E * sizeof(Rec64)));
     TPM_TRY(ensure(c, c->efirst, (size_t)E * 4));
@@ -1017,28 +1171,46 @@ int build(tpm_ctx *c, int64_t n, const double *x, const double *y, const double 
         k_count<<<nb, kBlock, 0, st>>>(key, n, (int8_t *)c->dR.p, (uint32_t *)c->cnt.p, lhist,
                                        nb);
         TPM_LAUNCHED(c, "k_count");
-        TPM_TRY(scan_u32(c, lhist, loff, (int64_t)kLevels * nb, nullptr));
+        TPM_TRY(scan_u32(c, lhist, loff, (int64_t)kLevels * nb, lvl_count + 33));
+        k_sizes<<<1, 64, 0, st>>>(loff, nb, lvl_count + 32, F, bad_eps, c->hpin_dev);
+        TPM_LAUNCHED(c, "k_sizes");
+        TPM_HIP(c, hipStreamSynchronize(st));
+        set_levels(c);
     }
     TPM_TRY(timer_begin(c, TPM_TIMER_TOPOLOGY));
-    k_emit<<<grid_for(n, kBlock), kBlock, 0, st>>>(
-        key, n, (const int8_t *)c->dR.p, (const uint32_t *)c->base.p, F,
-        (const double *)c->ps.p, (const double *)c->ms.p, (const uint64_t *)c->qs.p, rec,
-        (uint32_t *)c->efirst.p, (uint32_t *)c->ecount.p, (uint32_t *)c->pe.p, loff, nb,
-        (uint32_t *)c->lvl_list.p, (const double *)c->hs.p, eh, P.G, rec32, eh32);
+    auto emit = c->mixed ? k_emit<true> : k_emit<false>;
+    emit<<<grid_for(n, kBlock), kBlock, 0, st>>>(
+        n, E, (const int8_t *)c->dR.p, (const uint32_t *)c->base.p, F, (const double *)c->ps.p,
+        (const double *)c->ms.p, (const uint64_t *)c->qs.p, rec, (uint32_t *)c->efirst.p,
+        (uint32_t *)c->ecount.p, (uint32_t *)c->pe.p, loff, nb, (uint32_t *)c->lvl_list.p,
+        (const double *)c->hs.p, eh, P.G, rec32, eh32);
     TPM_LAUNCHED(c, "k_emit");
     TPM_TRY(timer_end(c, TPM_TIMER_TOPOLOGY));
     // 5. moments, deepest level first
     TPM_TRY(timer_begin(c, TPM_TIMER_MOMENTS));
-    for (int l = kMaxLevel; l >= 0; l--) {
-        const uint32_t cnt = c->level_count[l];
-        if (!cnt)
-            continue;
-        k_moments<<<grid_for(cnt, kBlock), kBlock, 0, st>>>(
-            rec, E, (uint32_t)n, (const uint32_t *)c->efirst.p, (uint32_t *)c->ecount.p,
-            (const uint32_t *)c->lvl_list.p + c->level_off[l],
-            cnt, (uint32_t)l, eh, P.G, (const uint64_t *)c->qs.p,
-            P.periodic ? kRecShiftPer : kRecShiftIso, rec32, eh32);
-        TPM_LAUNCHED(c, "k_moments");
+    LevelOffsets lo;
+    std::memcpy(lo.off, c->level_off, sizeof lo.off);
+    const int sh = P.periodic ? kRecShiftPer : kRecShiftIso;
+    for (int l = kMaxLevel; l >= 0;) {
+        int top = l;  // levels top .. l: one launch
+        uint32_t most = c->level_count[l];
+        while (most <= kRunNodes && top > 0 && c->level_count[top - 1] <= kRunNodes)
+            most = std::max(most, c->level_count[--top]);
+        if (most > kRunNodes) {
+            const uint32_t cnt = c->level_count[l];
+            k_moments<<<grid_for(cnt, kBlock), kBlock, 0, st>>>(
+                rec, E, (uint32_t)n, (const uint32_t *)c->efirst.p, (uint32_t *)c->ecount.p,
+                (const uint32_t *)c->lvl_list.p + c->level_off[l], cnt, (uint32_t)l, eh, P.G,
+                (const uint64_t *)c->qs.p, sh, rec32, eh32);
+            TPM_LAUNCHED(c, "k_moments");
+        } else if (most > 0) {
+            k_moments_run<<<1, kRunNodes, 0, st>>>(
+                rec, E, (uint32_t)n, (const uint32_t *)c->efirst.p, (uint32_t *)c->ecount.p,
+                (const uint32_t *)c->lvl_list.p, lo, l, top, eh, P.G, (const uint64_t *)c->qs.p,
+                sh, rec32, eh32);
+            TPM_LAUNCHED(c, "k_moments_run");
+        }
+        l = top - 1;
     }
     TPM_TRY(timer_end(c, TPM_TIMER_MOMENTS));
     c->n = n;

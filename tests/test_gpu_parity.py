@@ -119,6 +119,44 @@ def test_tree_bit_exact(case):
     _tree_equal(g, T)
 
 
+def _pairs(n, seed, gap):
+    """n / 2 pairs of particles `gap` apart: a chain of nodes above every pair."""
+    rng = np.random.default_rng(seed)
+    x, y, z = rng.uniform(-1.0, 1.0, (3, n))
+    h = n // 2
+    for v in (x, y, z):
+        v[h:2 * h] = v[:h] + gap * rng.uniform(-1.0, 1.0, h)
+    return W.Particles(x, y, z)
+
+
+@pytest.mark.parametrize("n,gap", [(63, 0.0), (64, 1e-3), (65, 1e-5), (1023, 1e-4), (1024, 1.0),
+                                   (1025, 1e-6), (4095, 1e-6), (8000, 1e-6), (8191, 1.0),
+                                   (8192, 1.0), (8193, 1.0), (8193, 1e-6), (10240, 0.0),
+                                   (20001, 1e-6), (20480, 1e-3)])
+def test_tree_bit_exact_at_the_builds_edges(n, gap):
+    """Trees around the sizes where the build changes its kernels: one workgroup
+    up to 8192 particles (with more entries than its LDS holds at 8000 and
+    1e-6), 256 particles per block beyond (with more entries than a block's
+    LDS, 640, where the pairs' chains are long), last blocks full and ragged;
+    with masses and individual softening, whose records take the same path;
+    the FP32 records by the forces they give."""
+    p = _pairs(n, n, gap)
+    p.mass = np.random.default_rng(n).uniform(0.5, 2.0, n)
+    T = O.Tree(p.x, p.y, p.z, mass=p.mass)
+    eps = np.random.default_rng(n + 1).uniform(0.01, 0.05, n)
+    res = {}
+    idx = _t(np.arange(n), torch.int32)
+    for prec, e in (("fp64", None), ("fp64", eps), ("fp32", None)):
+        ctx = _ctx(precision=prec, eps=0.03)
+        _build(ctx, p, e)
+        _tree_equal(ctx.export_tree(), T)
+        acc, _ = ctx.compute_forces(idx, "bh")
+        ctx.check()
+        res[prec, e is None] = acc.double().cpu().numpy()
+    err = rel_err(res["fp32", True], res["fp64", True])
+    assert np.percentile(err, 99) <= 1e-3, np.percentile(err, [50, 99, 100])
+
+
 def test_sort_many_tiles_bit_exact():
     """Keys and stable sort order at 2^21 + 12345 particles (516 tiles of the
     radix sort), with 6000 copies of one position spread over the whole index
