@@ -148,6 +148,35 @@ def test_kernel_index_errors_are_reported():
     assert ei.value.code == B.TPM_EINDEX
 
 
+@pytest.mark.parametrize("n,m", [(1, 1), (255, 255), (257, 256), (1025, 1024), (5000, 4999)])
+def test_time_bin_counts(n, m):
+    """Counts of the new bins over several workgroups, the last one ragged, with
+    all of the 41 bins in use: those of the bins written; an index out of range
+    is reported and counted nowhere."""
+    from paper_1909_04667_amd import binding as B
+    from paper_1909_04667_amd import integrate as GI
+    x, v = _state(n, 9)
+    integ = GI.BlockLeapfrog((_t(x[0]), _t(x[1]), _t(x[2])), (_t(v[0]), _t(v[1]), _t(v[2])),
+                             C=0.5, dt_max=1.0, max_bin=40, precision="fp64", eps=1.0)
+    rng = np.random.default_rng(n)
+    a = 4.0 ** rng.uniform(-2, 42, n)  # steps 2^2 .. 2^-42
+    idx = rng.permutation(n)[:m].astype(np.int32)
+    acc = np.zeros((3, m))
+    acc[n % 3] = a[:m]
+    hist = integ._time_bins(torch.as_tensor(idx, device=_dev()), _t(acc), None, 0)
+    # the longest 2^-b not above sqrt(2 C eps / a) = a^(-1/2)
+    want = np.clip(np.ceil(0.5 * np.log2(a[:m])), 0, 40).astype(np.int64)
+    got = integ.bins.cpu().numpy()[idx]
+    assert np.array_equal(got, want)
+    assert np.array_equal(hist, np.bincount(want, minlength=41))
+    integ.ctx.check()
+    idx[0] = n
+    hist = integ._time_bins(torch.as_tensor(idx, device=_dev()), _t(acc), None, 0)
+    assert np.array_equal(hist, np.bincount(want[1:], minlength=41))
+    with pytest.raises(B.TreePMError):
+        integ.ctx.check()
+
+
 def _periodic_case():
     p = W.zeldovich_box(16, 100.0, 3)
     x = np.stack([p.x, p.y, p.z])
