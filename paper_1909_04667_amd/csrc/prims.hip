@@ -3,6 +3,8 @@
 // a wavefront come from 64-bit ballots, across wavefronts from LDS.
 #include "tpm_internal.h"
 
+#include <algorithm>
+
 namespace tpm {
 namespace {
 
@@ -116,9 +118,14 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_add(uint32_t *out, int64_t 
 // words; a tile then writes each digit's keys as one contiguous run.  With
 // every tile resident at once, the inclusive counts advance a few tiles per
 // look-back round trip, so large tiles (fewer of them) shorten the pass.
+// Smaller sorts take smaller tiles, or a few blocks each work through many rounds
+// while the chip idles: with tiles of 8192, 2048 and 4096 keys all eight passes
+// over 50,001 keys take 145, 83, - us, over 2^18 166, 118, 120, over 400,000 175,
+// 139, 134, over 2^20 210, 231, 184.
 constexpr int kSortBlock = 1024;
-constexpr int kSortRounds = 8;
-constexpr int kSortTile = kSortBlock * kSortRounds;  // 8192 keys per block
+constexpr int64_t kSortN2 = int64_t(1) << 18;  // two rounds per tile up to here
+constexpr int64_t kSortN4 = int64_t(1) << 20;  // four up to here, eight beyond
+constexpr int sort_rounds(int64_t n) { return n <= kSortN2 ? 2 : n <= kSortN4 ? 4 : 8; }
 constexpr int kSortWaves = kSortBlock / 64;
 constexpr int kRadix = 256;  // digit values; threads 0 .. 255 own one each
 constexpr int kPasses = 8;
@@ -128,23 +135,24 @@ constexpr uint64_t kAggregate = 1ull << 32;  // this tile's own count
 constexpr uint64_t kInclusive = 2ull << 32;  // count of this and all earlier tiles
 
 // The eight digit histograms of all keys (one read of the keys).
+// per: keys per lane and chunk.
 __global__ __launch_bounds__(kSortBlock) void k_radix_count(const uint64_t *__restrict__ keys,
-                                                            int64_t n,
+                                                            int64_t n, int per,
                                                             unsigned long long *__restrict__ hist) {
     __shared__ uint32_t h[kPasses][kRadix];
     for (int k = threadIdx.x; k < kPasses * kRadix; k += kSortBlock)
         (&h[0][0])[k] = 0u;
     __syncthreads();
-    // a wavefront takes chunks of 1024 keys, lane l the keys 16 l .. 16 l + 15
-    // of a chunk: keys of neighbouring lanes lie 16 apart in the input, whose
-    // order is often spatial, which keeps one instruction's atomics apart
+    // a wavefront takes chunks of 64 per keys, lane l the keys per l .. per l +
+    // per - 1 of a chunk: keys of neighbouring lanes lie apart in the input,
+    // whose order is often spatial, which keeps one instruction's atomics apart
     const int lane = threadIdx.x & 63;
     const int64_t nw = (int64_t)gridDim.x * (kSortBlock / 64);
     for (int64_t ch = (int64_t)blockIdx.x * (kSortBlock / 64) + (threadIdx.x >> 6);
-         ch * 1024 < n; ch += nw) {
+         ch * 64 * per < n; ch += nw) {
 #pragma unroll 4
-        for (int j = 0; j < 16; j++) {
-            const int64_t i = ch * 1024 + lane * 16 + j;
+        for (int j = 0; j < per; j++) {
+            const int64_t i = (ch * 64 + lane) * per + j;
             if (i < n) {
                 const uint64_t k = keys[i];
 #pragma unroll
@@ -170,10 +178,12 @@ __device__ __forceinline__ void store_word(uint64_t *p, uint64_t v) {
 
 // One digit pass.  ctr: this pass's tile counter; hist: its digit histogram;
 // look: its nb x 256 look-back words (all zero on entry).
+template <int ROUNDS>
 __global__ __launch_bounds__(kSortBlock) void k_radix_pass(
     const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t n, int shift,
     unsigned long long *ctr, const unsigned long long *__restrict__ hist, uint64_t *look) {
+    constexpr int kSortTile = kSortBlock * ROUNDS;
     __shared__ uint64_t s_k[kSortTile];
     __shared__ uint32_t s_v[kSortTile];
     __shared__ uint32_t s_wc[kSortWaves][kRadix];  // per-wavefront digit counts
@@ -196,11 +206,11 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_pass(
     // wavefront's share of the tile (contiguous keys, no block barrier):
     // a ballot match finds the lanes with the same digit, the wavefront's
     // own counter in LDS gives the keys of that digit in earlier rounds
-    uint64_t k[kSortRounds];
-    uint32_t v[kSortRounds], pos[kSortRounds];
+    uint64_t k[ROUNDS];
+    uint32_t v[ROUNDS], pos[ROUNDS];
     const int64_t wbase = base + (int64_t)w * (kSortTile / kSortWaves);
 #pragma unroll
-    for (int r = 0; r < kSortRounds; r++) {
+    for (int r = 0; r < ROUNDS; r++) {
         const int64_t i = wbase + (int64_t)r * 64 + lane;
         const bool valid = i < n;
         k[r] = valid ? kin[i] : 0ull;
@@ -301,7 +311,7 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_pass(
 
     // 4. place the keys in tile order by digit, then write the runs out
 #pragma unroll
-    for (int r = 0; r < kSortRounds; r++) {
+    for (int r = 0; r < ROUNDS; r++) {
         const int64_t i = wbase + (int64_t)r * 64 + lane;
         if (i < n) {
             const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
@@ -461,28 +471,45 @@ int scan_u32(tpm_ctx *c, const uint32_t *in, uint32_t *out, int64_t n, uint32_t 
     return TPM_OK;
 }
 
-size_t sort_scratch_bytes(int64_t n) {
-    const int64_t nb = (n + kSortTile - 1) / kSortTile;
+// Tiles of a sort of n keys.
+static int64_t sort_tiles(int64_t n) {
+    const int64_t tile = kSortBlock * sort_rounds(n);
+    return (n + tile - 1) / tile;
+}
+
+static size_t sort_words(int64_t n) {
     // tile counters, digit histograms, look-back words of every pass
-    return (size_t)(kPasses + kPasses * kRadix + kPasses * nb * kRadix) * sizeof(uint64_t);
+    return (size_t)(kPasses + kPasses * kRadix + kPasses * sort_tiles(n) * kRadix);
+}
+
+size_t sort_scratch_bytes(int64_t n) {  // of sorts of at most n keys
+    return std::max({sort_words(std::min(n, kSortN2)), sort_words(std::min(n, kSortN4)),
+                     sort_words(n)}) *
+           sizeof(uint64_t);
 }
 
 int radix_sort_pairs(tpm_ctx *c, int64_t n) {
-    const int64_t nb = (n + kSortTile - 1) / kSortTile;
-    const int64_t words = (int64_t)(sort_scratch_bytes(n) / sizeof(uint64_t));
+    const int64_t nb = sort_tiles(n);
+    const int64_t words = (int64_t)sort_words(n);
     TPM_TRY(ensure(c, c->hist, (size_t)words * sizeof(uint64_t)));
     unsigned long long *ctr = (unsigned long long *)c->hist.p;
     unsigned long long *hist = ctr + kPasses;
     uint64_t *look = (uint64_t *)(hist + kPasses * kRadix);
     TPM_TRY(timer_begin(c, TPM_TIMER_SORT));
     TPM_TRY(fill_u64(c, (uint64_t *)ctr, 0ull, words));
-    const int64_t cb = nb < 1024 ? nb : 1024;
+    const int rounds = sort_rounds(n);
+    const int per = rounds < 8 ? 2 : 16;  // (16 at 2^20: 202 us instead of 184)
+    const int64_t chunks = (n + 64 * per - 1) / (64 * per);
+    const int64_t cb = std::min<int64_t>((chunks + kSortWaves - 1) / kSortWaves, 1024);
     k_radix_count<<<(unsigned)cb, kSortBlock, 0, c->stream>>>(
-        (const uint64_t *)c->key[0].p, n, hist);
+        (const uint64_t *)c->key[0].p, n, per, hist);
     TPM_LAUNCHED(c, "k_radix_count");
     int cur = 0;
     for (int p = 0; p < kPasses; p++) {
-        k_radix_pass<<<(unsigned)nb, kSortBlock, 0, c->stream>>>(
+        auto pass = rounds == 2   ? k_radix_pass<2>
+                    : rounds == 4 ? k_radix_pass<4>
+                                  : k_radix_pass<8>;
+        pass<<<(unsigned)nb, kSortBlock, 0, c->stream>>>(
             (const uint64_t *)c->key[cur].p, (const uint32_t *)c->idx[cur].p,
             (uint64_t *)c->key[cur ^ 1].p, (uint32_t *)c->idx[cur ^ 1].p, n, 8 * p, ctr + p,
             hist + (size_t)p * kRadix, look + (size_t)p * nb * kRadix);

@@ -157,6 +157,25 @@ def test_tree_bit_exact_at_the_builds_edges(n, gap):
     assert np.percentile(err, 99) <= 1e-3, np.percentile(err, [50, 99, 100])
 
 
+@pytest.mark.parametrize("n", [8193, 10240, 10241, 65536 + 63, 1 << 18, (1 << 18) + 1, 1 << 20,
+                               (1 << 20) + 1])
+def test_sort_bit_exact_at_the_tiles_edges(n):
+    """Keys and stable sort order in tiles of 2048 keys (up to 2^18), 4096 (up to
+    2^20) and 8192: full and ragged last tiles, both sides of each change, a
+    sixteenth of the particles on one position."""
+    rng = np.random.default_rng(n)
+    x, y, z = rng.uniform(-50.0, 50.0, (3, n))
+    dup = rng.choice(n, n // 16, replace=False)
+    x[dup], y[dup], z[dup] = 1.25, -3.5, 7.0
+    ctx = _ctx(eps=0.01)
+    _build(ctx, W.Particles(x, y, z))
+    g = ctx.export_tree()
+    _, _, key = O.positions(x, y, z, False, O.frame(x, y, z))
+    perm = O.sort(key)
+    assert np.array_equal(g["perm"], perm)
+    assert np.array_equal(g["key"], key[perm])
+
+
 def test_sort_many_tiles_bit_exact():
     """Keys and stable sort order at 2^21 + 12345 particles (516 tiles of the
     radix sort), with 6000 copies of one position spread over the whole index
