@@ -21,7 +21,7 @@ namespace {
 // Largest tree the array serves, and its layout (byte offsets, 256-aligned):
 // marks, active slots, slot map, results [n][4] (acceleration and interaction
 // count) and potentials [n] in FP64 (the planes of a walk's shares, at most
-// 3 2^18 slots, fit in them), compaction tile counts, and the unique-active
+// 2^20 slots, fit in them), compaction tile counts, and the unique-active
 // counter.
 constexpr int64_t kMaxN = int64_t(1) << 20;
 constexpr size_t align256(size_t b) { return (b + 255) & ~size_t(255); }

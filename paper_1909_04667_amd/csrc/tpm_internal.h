@@ -187,9 +187,9 @@ struct Work {
 inline size_t mark_bytes(int64_t n) { return ((size_t)n + 15) & ~size_t(15); }
 
 // Walks of small sets are divided into shares (walk_device.h), at most eight and
-// at most 3 2^18 records altogether: slots of the results of a tree of n.
+// at most 2^20 records altogether: slots of the results of a tree of n.
 inline int64_t result_slots(int64_t n) {
-    const int64_t s = 8 * n < 3 * (int64_t(1) << 18) ? 8 * n : 3 * (int64_t(1) << 18);
+    const int64_t s = 8 * n < (int64_t(1) << 20) ? 8 * n : (int64_t(1) << 20);
     return n > s ? n : s;
 }
 

@@ -463,6 +463,13 @@ Variant wk::walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok) {
 //   clustered 64^3, FP32        .68 .92 | .63 .78 | .69 .84
 //   Hernquist 2^18, FP32       1.20 1.02 | 1.25 .80 | 1.46 .80
 //   Zel'dovich 64^3, FP32       .32 .31 | .34 .32 | .39 .37
+// and one and two shares beyond 2^18:
+//   Hernquist 500,000, FP32    1.90 1.21 | 1.90 1.13
+//   with a mesh, 400,000, FP32 1.96 1.79 | 1.92 1.38
+//   with a mesh, 300,000, FP64 4.61 3.65 | 4.87 2.96
+//   Zel'dovich 70^3, FP64      2.50 5.46 | 2.35 4.81
+//   Zel'dovich 80^3, FP32       .99 1.29 |  .99 1.36
+//   Hernquist 2^20, FP32       3.43 1.79 | 3.44 2.11
 // Blocks of entries give each share some of a group's dense neighbourhood: 256
 // entries in a periodic box, where the cutoff bounds the neighbourhood (128
 // and 512: within 10 %), an isolated tree's entries over 128, 256 to 4096
@@ -473,6 +480,8 @@ void wk::set_shares(const tpm_ctx *c, int64_t n_act, int opening, Variant v, Wal
     const bool fp32 = c->P.precision == TPM_FP32;
     // (FP64: four, the sums that the server's LDS holds)
     A.shares_log = t <= 65536 && fp32 ? 3u : t <= 196608 ? 2u : t <= 262144 ? 1u : 0u;
+    if (t > 262144 && t <= 524288 && opening == TPM_OPEN_REL && !(fp32 && c->P.periodic))
+        A.shares_log = 1u;
     if (v == kSplitWalk || (fp32 && opening == TPM_OPEN_BH))
         A.shares_log = 0u;
     A.shares = 1u << A.shares_log;

@@ -416,7 +416,7 @@ def test_active_slots_over_many_calls(n):
     ctx.check()
 
 
-@pytest.mark.parametrize("n", [4097, 65536, 65537, 196609, 262145])
+@pytest.mark.parametrize("n", [4097, 65536, 65537, 196609, 262145, 524288, 524289])
 @pytest.mark.parametrize("mesh", [0, 16])
 def test_shares_of_a_walk(n, mesh, monkeypatch):
     """Walks of small sets are divided into shares, eight to one at these
