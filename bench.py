@@ -690,8 +690,8 @@ def main():
     walk_ms = h["walk_rel_ms_per_launch"]
     achieved = res[precs[0]]["inter_rel"] * fl / (walk_ms * 1e-3) / 1e12
     per, tpm = ("true", "true") if periodic else ("false", "false")
-    walk_kernel = (f"k_walk32<{per}, {tpm}, 1, false, false>" if precs[0] == "fp32"
-                   else f"k_walk64{'i' if periodic else ''}<{per}, {tpm}, 1, false, false>")
+    walk_kernel = (f"k_walk32<false, {per}, {tpm}, 1, false, false>" if precs[0] == "fp32"
+                   else f"k_walk64<false, {per}, {tpm}, 1, false, false>")
     meas = peaks["fp32_fma_unpacked_tflops" if precs[0] == "fp32" else "fp64_fma_tflops"]
     line = {
         "metric": METRIC,

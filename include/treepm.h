@@ -264,8 +264,12 @@ int tpm_accel_norm(tpm_ctx *ctx, int64_t n_act, const int32_t *active_idx, const
 #define TPM_TIMER_KEYS 6       /* root cube and Peano-Hilbert keys (within the build) */
 #define TPM_TIMER_GATHER 7     /* gather into curve order (within the build) */
 #define TPM_TIMER_TOPOLOGY 8   /* depth-first entries: counts and scans, then emission
-                                  (two records per build) */
-#define TPM_TIMER_MOMENTS 9    /* monopole moments and FP32 records (within the build) */
+                                  with the moments of the nodes that end inside a block
+                                  of 256 particles (two records per build; up to 8192
+                                  particles one, from the root cube to the scan) */
+#define TPM_TIMER_MOMENTS 9    /* the remaining nodes' moments and FP32 records; up to
+                                  8192 particles emission and all moments (then kinds
+                                  4, 6 and 7 have no records) */
 #define TPM_TIMER_DEPOSIT 10   /* mesh clear and CIC deposit (within the solve) */
 #define TPM_TIMER_FFT 11       /* the five FFT passes with the Green's function */
 #define TPM_TIMER_KINDS 12

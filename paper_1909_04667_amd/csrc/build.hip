@@ -7,8 +7,8 @@
 // which is exactly the tree sequential insertion produces.  Every particle
 // starts the nodes whose prefix level lies between its common-prefix depths
 // with its left and right neighbours, so one scan over per-particle counts
-// gives the depth-first position of every entry, and skip pointers (end of a
-// subtree) come from a galloping search for the end of each prefix run.
+// gives the depth-first position of every entry; a subtree ends (its skip
+// pointer) at the first later entry that is not deeper.
 #include "tpm_internal.h"
 
 #include <algorithm>
