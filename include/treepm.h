@@ -186,10 +186,11 @@ int tpm_set_shift(tpm_ctx *ctx, const double *shift);
  * pot:         device [n_act] of the same type, or NULL.
  * n_interactions: device uint32[n_act] node + particle interactions per
  *              target (the cost factor g_i of Sec. 8), or NULL.
- * Results are deterministic.  Small active sets (at most 4096 targets, or
- * 65536 in trees of 2^22 particles or more) are walked with one wavefront per
- * target, and sets of at most 262144 targets in two, four (at most 196608) or
- * eight (at most 65536, FP32) shares that are then added: a target's
+ * Results are deterministic.  Small active sets (at most 4096 targets, 16384 in
+ * FP64 with a mesh where they are a quarter of the particles, or 65536 in trees of 2^22 particles or more) are walked with
+ * one wavefront per target, and sets of at most 262144 targets (524288 in the
+ * relative pass) in two, four (at most 196608) or eight (at most 65536, FP32)
+ * shares that are then added: a target's
  * interactions are added in another order than in larger sets, and its force
  * may differ in the last bits between sets of different kinds; interaction
  * counts never differ.

@@ -424,8 +424,9 @@ int select_active(tpm_ctx *c, int64_t n_act, const int32_t *idx) {
 // for sparse active sets whose groups are too spread out for a shared cursor
 // (it would visit the union of their walks); the shared cursor otherwise.
 // One wavefront per target for active sets
-// of at most 4096 targets, and of at most 65536 in trees of 2^22 particles or
-// more: with that few wavefronts a lane's serial walk (the longest, which
+// of at most 4096 targets (16384 of a quarter or more of
+// all particles, in FP64 with a cutoff), and of at most 65536 in
+// trees of 2^22 particles or more: with that few wavefronts a lane's serial walk (the longest, which
 // grows with the tree) is the critical path, while the frontier walk spreads
 // each target over its wavefront and fills the chip.  Measured, FP32
 // relative walk, lanes against one wavefront per target: the densest targets
@@ -435,14 +436,24 @@ int select_active(tpm_ctx *c, int64_t n_act, const int32_t *idx) {
 // walks are short and the frontier walk's larger work per target loses
 // (block steps of a 2^18 Hernquist sphere with sets up to 65536: 15.6 ms
 // against 25.5 ms for the integration; the serving mix, up to 2^21
-// particles per system: half the burst capacity).
+// particles per system: half the burst capacity).  In FP64 with a cutoff a
+// target's work is bounded by its neighbourhood, and a step costs most where
+// few lanes share it; one wavefront per target against the better of the other
+// two, relative and geometric pass in us: whole boxes of 20^3 500 418 -> 146 118,
+// 25^3 679 547 -> 385 268, 25^3 clustered 501 420 -> 379 318; isolated, 16000 with a
+// mesh 578 928 -> 374 611; 16384 of 64,000 clustered 649 540 -> 392 341.  (Sparse sets
+// would gain as much, but the shared cursor and the lanes give them the bits of
+// the whole set at equal shares.)  Without a cutoff the geometric pass loses beyond 4096
+// (8192 of 2^18: 986 -> 1623), and the FP32 geometric pass keeps its order of
+// summation there (see set_shares).
 // TPM_WALK_MODE (1 shared cursor, 2 lanes, 3 one wavefront per target)
 // overrides the choice.
 Variant wk::walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok) {
     if (c->walk_mode != 0)
         return c->walk_mode == 1 ? kGroupWalk : c->walk_mode == 2 ? kLaneWalk : kSplitWalk;
     const int64_t targets = std::min<int64_t>(n_act, c->n);
-    if (targets <= 4096 || (targets <= 65536 && c->n >= (int64_t(1) << 22)))
+    const bool near64 = c->P.precision == TPM_FP64 && c->P.pm_grid > 0 && 4 * n_act >= c->n;
+    if (targets <= (near64 ? 16384 : 4096) || (targets <= 65536 && c->n >= (int64_t(1) << 22)))
         return kSplitWalk;
     if (4 * n_act >= c->n)
         return kGroupWalk;

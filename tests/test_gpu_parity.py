@@ -450,6 +450,41 @@ def test_shares_of_a_walk(n, mesh, monkeypatch):
     assert float(err.max()) <= 64 * 2.0 ** -24 * float(out[0][2].max())
 
 
+@pytest.mark.parametrize("n", [4097, 16383, 16384, 16385])
+@pytest.mark.parametrize("periodic", [False, True])
+def test_wavefront_per_target_with_a_cutoff(n, periodic, monkeypatch):
+    """FP64 with a mesh takes one wavefront per target up to 16384 targets: the
+    interactions of the shared cursor, summed in another order; the walk that
+    runs by default is that one up to there, and not beyond."""
+    p = W.uniform_cube(n, 47, side=100.0)
+    for v in (p.x, p.y, p.z):
+        v[50:750] = 31.0
+    kw = dict(precision="fp64", eps=0.05, alpha=0.02, want_potential=True, pm_grid=16, rcut=2.0,
+              periodic=periodic)
+    if periodic:
+        kw["box_size"] = 100.0
+    for opening in ("bh", "rel"):
+        out = []
+        for mode in ("0", "1", "3"):
+            monkeypatch.setenv("TPM_WALK_MODE", mode)
+            ctx = _ctx(**kw)
+            _build(ctx, p)
+            nint = torch.full((n,), -1, dtype=torch.int32, device=_dev())
+            acc, pot = ctx.compute_forces(_t(np.arange(n), torch.int32), opening,
+                                          n_interactions=nint,
+                                          a_old_norm=_t(np.full(n, 1e-3)))
+            ctx.check()
+            out.append((acc, pot, nint))
+        for a, b in zip(out[0], out[2 if n <= 16384 else 1]):
+            assert torch.equal(a, b)
+        assert torch.equal(out[1][2], out[2][2])
+        mag = out[1][0].norm(dim=0)
+        scale = mag.clamp_min(float(mag.square().mean().sqrt()))
+        err = (out[2][0] - out[1][0]).norm(dim=0) / scale
+        # rounding of two summation orders of at most n_int terms
+        assert float(err.max()) <= 64 * 2.0 ** -53 * float(out[1][2].max())
+
+
 @pytest.mark.parametrize("n", [255 * 64, 64 * 256 + 1, 8192 * 256 - 63, 8305 * 256 - 1])
 def test_block_order_covers_every_group(n, monkeypatch):
     """The blocks of a walk are dealt to the dies in runs of a length that
