@@ -882,6 +882,7 @@ int submit_impl(tpm_server *s, tpm_ctx *c, bool step, int32_t opening, int64_t n
     s->slot_ticket[sid] = R.ticket;
     s->slot_ctx[sid] = c;
     s->published++;
+    marks_queued(w);  // (the request's clear phase is part of what is published)
     __atomic_store_n(&s->host->tail, (unsigned long long)s->published, __ATOMIC_RELEASE);
     if (!running(s))
         TPM_TRY(launch(s));

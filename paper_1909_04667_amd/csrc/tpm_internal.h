@@ -77,7 +77,7 @@ struct tpm_ctx {
     int64_t E = 0;          // depth-first entries of the last build
     int built = 0;
     int pm_ready = 0;
-    uint8_t epoch = 0;      // active-set marking generation
+    uint8_t epoch = 0;      // last mark written to `mark` (0: to be cleared first)
     int walk_mode = 0;      // 0: automatic, 1: shared cursor, 2: independent lanes,
                             // 3: one wavefront per target
     tpm::Frame frame_host{};
@@ -173,6 +173,8 @@ struct Work {
     uint8_t *mark = nullptr;    // [n] epoch marks (rounded up to whole 16-byte words)
     uint8_t epoch = 0;          // the mark of this call
     bool clear = false;         // clear the marks [0, n) before marking
+    uint8_t *last = nullptr;    // the context's epoch (null: none is kept), set to this
+                                // call's by marks_queued() once its clear is queued
     uint32_t *act = nullptr;    // [n] active slots in curve order
     uint32_t *slot = nullptr;   // [n] rank -> position in act
     uint32_t *counts = nullptr; // [ceil(n / scan tile)] compaction tile counts
@@ -182,6 +184,15 @@ struct Work {
                                 // one plane per share of the walk
     void *rpot = nullptr;       // [result_slots(n)]
 };
+
+// The clear that a call on the marks asked for is queued (or none was needed):
+// its mark counts as used from here on, before the first particle is marked.  A
+// call that queues nothing (no active particles, a failure before this) leaves
+// the marks as they were, and so leaves the clear to the next call.
+inline void marks_queued(const Work &w) {
+    if (w.last)
+        *w.last = w.epoch;
+}
 
 // Bytes of the marks of n particles.
 inline size_t mark_bytes(int64_t n) { return ((size_t)n + 15) & ~size_t(15); }
@@ -220,7 +231,7 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
                 const double *anorm, void *acc, void *pot, uint32_t *nint, const Work &w,
                 bool timed);
 // the context's own working memory, allocated as needed (results: res and
-// rpot too); advances the context's mark epoch
+// rpot too), with the mark that follows the context's last one
 int work_of_ctx(tpm_ctx *c, bool results, Work &w);
 int select_active(tpm_ctx *c, int64_t n_act, const int32_t *idx);
 int select_active_into(tpm_ctx *c, int64_t n_act, const int32_t *idx, const Work &w);

@@ -378,12 +378,9 @@ int work_of_ctx(tpm_ctx *c, bool results, Work &w) {
     }
     w = Work{};
     w.mark = (uint8_t *)c->mark.p;
-    w.clear = false;
-    if (++c->epoch == 0 || c->epoch == 1) {  // fresh or wrapped: clear the marks
-        w.clear = true;
-        c->epoch = 1;
-    }
-    w.epoch = c->epoch;
+    w.clear = c->epoch == 0 || c->epoch == 255;  // fresh, or every mark was used
+    w.epoch = w.clear ? 1 : (uint8_t)(c->epoch + 1);
+    w.last = &c->epoch;
     w.act = (uint32_t *)c->act.p;
     w.slot = (uint32_t *)c->slot.p;
     w.counts = (uint32_t *)c->scan_tmp.p;
@@ -401,10 +398,12 @@ int select_active_into(tpm_ctx *c, int64_t n_act, const int32_t *idx, const Work
                                                 (const int32_t *)c->rank.p, w.mark, w.clear, w.act,
                                                 w.slot, w.nuniq);
         TPM_LAUNCHED(c, "k_select_small");
+        marks_queued(w);
         return TPM_OK;
     }
     if (w.clear)
         TPM_TRY(fill_u32(c, (uint32_t *)w.mark, 0u, (int64_t)(mark_bytes(n) / 4)));
+    marks_queued(w);
     if (n_act > 0) {
         k_mark<<<grid_for(n_act, kBlock), kBlock, 0, st>>>(idx, n_act, n,
                                                            (const int32_t *)c->rank.p, w.mark,

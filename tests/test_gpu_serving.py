@@ -82,6 +82,100 @@ def test_batch_rejects_same_context_twice():
     torch.cuda.synchronize()
 
 
+def _marked_before(n=20000):
+    """A context above 8192 particles whose marks hold the value 2 for every
+    particle, and the full set's interaction counts."""
+    from paper_1909_04667_amd import binding as B
+    p = W.uniform_cube(n, 59)
+    ctx = B.Context(precision="fp32", eps=0.01, theta=1.5)
+    t = lambda a: torch.as_tensor(a, dtype=torch.float64, device=_dev())
+    xyz = (t(p.x), t(p.y), t(p.z))
+    ctx.build_tree(*xyz)
+    idx = torch.arange(n, dtype=torch.int32, device=_dev())
+    full = torch.empty(n, dtype=torch.int32, device=_dev())
+    for _ in range(2):
+        ctx.compute_forces(idx, "bh", n_interactions=full)
+    return ctx, xyz, full
+
+
+def _check_small_set(ctx, full, seed, k=700):
+    g = torch.Generator(device=_dev()).manual_seed(seed)
+    ids = torch.randperm(full.numel(), generator=g, device=_dev())[:k].to(torch.int32)
+    got = torch.full((k,), -1, dtype=torch.int32, device=_dev())
+    ctx.compute_forces(ids, "bh", n_interactions=got)
+    ctx.check()
+    assert torch.equal(got, full[ids.long()])
+
+
+@pytest.mark.parametrize("calls", [0, 253, 254, 255])
+def test_empty_batch_request_keeps_the_marks(calls):
+    """An empty batch request queues no clear of the active set's marks: the
+    clear that it would have been due (the first call after a build, the call
+    after the last of a byte's 255 values) is left to the next call."""
+    from paper_1909_04667_amd import binding as B
+    ctx, xyz, full = _marked_before()
+    none = torch.empty(0, dtype=torch.int32, device=_dev())
+    one = torch.zeros(1, dtype=torch.int32, device=_dev())
+    every = torch.arange(full.numel(), dtype=torch.int32, device=_dev())
+    ctx.build_tree(*xyz)
+    for k in range(calls):  # the second one marks every particle with 2
+        ctx.compute_forces(every if k == 1 else one, "bh")
+    b = B.Batch()
+    for _ in range(3):
+        b.add(ctx, none, "bh")
+        b.launch()
+    for k in range(4):
+        _check_small_set(ctx, full, k)
+    b.close()
+
+
+def test_failed_submission_keeps_the_marks():
+    """A submission that fails (the mesh does not fit the context's arena)
+    leaves the clear that it was due to the next call."""
+    from paper_1909_04667_amd import binding as B
+    n = 20000
+    p = W.uniform_cube(n, 61, side=100.0)
+    kw = dict(precision="fp32", eps=0.05, theta=1.5, periodic=True, box_size=100.0, pm_grid=256,
+              asmth=20.0, rcut=2.0)
+    held = B.bytes_needed(B.make_params(precision="fp32", eps=0.05), n)
+    ctx = B.Context(arena_bytes=held, **kw)
+    t = lambda a: torch.as_tensor(a, dtype=torch.float64, device=_dev())
+    xyz = (t(p.x), t(p.y), t(p.z))
+    ctx.build_tree(*xyz)
+    idx = torch.arange(n, dtype=torch.int32, device=_dev())
+    full = torch.empty(n, dtype=torch.int32, device=_dev())
+    for _ in range(2):
+        ctx.compute_forces(idx, "bh", n_interactions=full)
+    ctx.build_tree(*xyz)
+    lp = B.ResidentServer("fp32")
+    with pytest.raises(B.TreePMError) as ei:
+        lp.submit_step(ctx, idx[:1].contiguous())
+    assert ei.value.code == B.TPM_ENOMEM
+    for k in range(3):
+        _check_small_set(ctx, full, k)
+    lp.close()
+
+
+def test_resident_marks_through_their_wrap():
+    """More requests than a mark byte has values, on a tree above 8192
+    particles: every request selects exactly its own set."""
+    from paper_1909_04667_amd import binding as B
+    ctx, _, full = _marked_before()
+    lp = B.ResidentServer("fp32")
+    g = torch.Generator(device=_dev()).manual_seed(3)
+    n = full.numel()
+    for call in range(300):
+        k = (1, 33, 700, n)[call % 4]
+        ids = torch.randperm(n, generator=g, device=_dev())[:k].to(torch.int32)
+        got = torch.full((k,), -1, dtype=torch.int32, device=_dev())
+        torch.cuda.synchronize()
+        tk, _ = lp.submit(ctx, ids, "bh", n_interactions=got)
+        lp.wait(tk)
+        assert torch.equal(got, full[ids.long()]), call
+    lp.close()
+    ctx.check()
+
+
 def test_resident_alone_equals_mix_equals_single():
     """Requests for four systems of both precisions submitted together to
     the running kernels (and one at a time): bit-identical to the
