@@ -374,16 +374,16 @@ __device__ __forceinline__ void srv_group(const WalkArgs &A, uint32_t g, uint32_
                                           WaveLds *Q) {
     if constexpr (FP32) {
         if (var == kSplitWalk)
-            walk_lanes32<kWhole, PER, TPM, OPEN, false, MIXED, true>(A, g, 1u, Q->front);
+            walk_lanes32<kWhole, PER, TPM, OPEN, false, MIXED, true>(A, g, Q->front);
         else if (var == kLaneWalk)
-            walk_lanes32<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, 1u, nullptr, &Q->parts);
+            walk_lanes32<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, nullptr, &Q->parts);
         else
             walk_group32<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, &Q->parts);
     } else {
         if (var == kSplitWalk)
-            walk_lanes64<kWhole, PER, TPM, OPEN, false, MIXED, true>(A, g, 1u, Q->front);
+            walk_lanes64<kWhole, PER, TPM, OPEN, false, MIXED, true>(A, g, Q->front);
         else if (var == kLaneWalk)
-            walk_lanes64<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, 1u, nullptr, &Q->d.parts);
+            walk_lanes64<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, nullptr, &Q->d.parts);
         else
             walk_group64<kAllShares, PER, TPM, OPEN, false, MIXED>(A, g, &Q->d.q, &Q->d.parts);
     }

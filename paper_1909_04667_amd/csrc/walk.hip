@@ -46,16 +46,6 @@ __global__ __launch_bounds__(kBlock) void k_walk32(const WalkArgs A) {
     walk_group32<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id());
 }
 
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
-__global__ __launch_bounds__(kBlock) void k_walk64i(const WalkArgs A, uint32_t K) {
-    walk_lanes64<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), K);
-}
-
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
-__global__ __launch_bounds__(kBlock) void k_walk32i(const WalkArgs A, uint32_t K) {
-    walk_lanes32<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), K);
-}
-
 // Sparse active sets: a census counts the compact groups (group_compact),
 // then one of two launches walks every group -- with the shared cursor when
 // at least half of the groups are compact (a set of dense clumps, as the
@@ -79,7 +69,10 @@ __global__ __launch_bounds__(kBlock) void k_census(const WalkArgs A, uint32_t *c
         atomicAdd(census, 1u);
 }
 
+// (Without a census: lanes, where they were asked for.)
 __device__ __forceinline__ bool mostly_compact(const WalkArgs &A) {
+    if (!A.census)
+        return false;
     const uint32_t groups = (load_count(A.nuniq) + 63u) / 64u;
     return 2ull * load_count(A.census) >= groups;
 }
@@ -99,7 +92,7 @@ k_walk64m(const WalkArgs A) {
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk64im(const WalkArgs A) {
     if (!mostly_compact(A))
-        walk_lanes64<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), 1u);
+        walk_lanes64<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id());
 }
 
 template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
@@ -111,21 +104,21 @@ __global__ __launch_bounds__(kBlock) void k_walk32m(const WalkArgs A) {
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk32im(const WalkArgs A) {
     if (!mostly_compact(A))
-        walk_lanes32<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), 1u);
+        walk_lanes32<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, wave_id());
 }
 
 // one wavefront per target (sparse active sets)
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk64s(const WalkArgs A) {
     __shared__ uint32_t front[kBlock / 64][kFrontWords];
-    walk_lanes64<kWhole, PER, TPM, OPEN, POT, MIXED, true>(A, wave_id(), 1u,
+    walk_lanes64<kWhole, PER, TPM, OPEN, POT, MIXED, true>(A, wave_id(),
                                                               front[threadIdx.x >> 6]);
 }
 
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk32s(const WalkArgs A) {
     __shared__ uint32_t front[kBlock / 64][kFrontWords];
-    walk_lanes32<kWhole, PER, TPM, OPEN, POT, MIXED, true>(A, wave_id(), 1u,
+    walk_lanes32<kWhole, PER, TPM, OPEN, POT, MIXED, true>(A, wave_id(),
                                                               front[threadIdx.x >> 6]);
 }
 
@@ -274,7 +267,6 @@ __global__ __launch_bounds__(kBlock) void k_accel_norm(const int32_t *__restrict
 struct Launch {
     bool fp32;
     Variant variant;
-    uint32_t K;       // slots per lane (lane-independent walk)
     unsigned blocks;
     unsigned lane_blocks;    // kGroupOrLanes: of the lane walk
     unsigned census_blocks;  // and of the census
@@ -289,9 +281,9 @@ void launch_walk(const WalkArgs &A, const Launch &L, hipStream_t st) {
             k_walk64s<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
     } else if (L.variant == kLaneWalk) {
         if (L.fp32)
-            k_walk32i<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A, L.K);
+            k_walk32im<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
         else
-            k_walk64i<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A, L.K);
+            k_walk64im<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
     } else if (L.variant == kGroupOrLanes) {
         k_census<PER, TPM><<<L.census_blocks, kBlock, 0, st>>>(A, (uint32_t *)A.census);
         if (L.fp32) {
@@ -456,7 +448,7 @@ Variant wk::walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok) {
         return kSplitWalk;
     if (4 * n_act >= c->n)
         return kGroupWalk;
-    // a sparse set: with a cutoff, as the census of its groups decides
+    // a sparse set: as the census of its groups decides
     return census_ok ? kGroupOrLanes : kLaneWalk;
 }
 
@@ -599,26 +591,14 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
     const int64_t groups = (std::min<int64_t>(n_act, n) + 63) / 64;
     Launch LA;
     LA.fp32 = fp32;
-    // lane-independent walks pay off where the interaction is expensive and
-    // the wavefront's union of cutoff spheres is large: FP64 with TreePM
     LA.variant = walk_variant(c, n_act, true);
     set_shares(c, n_act, opening, LA.variant, A);
     if (LA.variant == kGroupOrLanes) {  // the census word follows the unique count
         A.census = w.nuniq + 1;
         TPM_TRY(fill_u32(c, w.nuniq + 1, 0u, 1));
     }
-    LA.K = 1;
-    if (LA.variant == kLaneWalk) {
-        // several slots per lane once there are enough wavefronts to fill the chip
-        const int64_t slots_per_chip = 256 * 4 * 8;
-        while (LA.K < 8 && groups / (2 * LA.K) >= 2 * slots_per_chip)
-            LA.K *= 2;
-    }
     const uint32_t targets = (uint32_t)std::min<int64_t>(n_act, n);
-    uint32_t waves = walk_waves(LA.variant, targets, A.shares);
-    if (LA.variant == kLaneWalk)
-        waves = (waves + LA.K - 1) / LA.K;
-    LA.blocks = (waves + 3) / 4;
+    LA.blocks = (walk_waves(LA.variant, targets, A.shares) + 3) / 4;
     LA.lane_blocks = (walk_waves(kLaneWalk, targets, A.shares) + 3) / 4;
     LA.census_blocks = (unsigned)((groups + 3) / 4);
     const bool want_pot = pot != nullptr && P.want_potential;
@@ -678,14 +658,14 @@ __device__ __forceinline__ void batch_group(const WalkArgs &A, uint32_t g, uint3
                                             IQ64 *Q) {
     if constexpr (FP32) {
         if (var == kLaneWalk)
-            walk_lanes32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, 1u);
+            walk_lanes32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g);
         else if (OPEN == TPM_OPEN_REL && A.shares > 1u)
             walk_group32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g);
         else
             walk_group32<kWhole, PER, TPM, OPEN, false, MIXED>(A, g);
     } else {
         if (var == kLaneWalk)
-            walk_lanes64<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, 1u);
+            walk_lanes64<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g);
         else if (A.shares > 1u)
             walk_group64<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, Q);
         else
@@ -910,7 +890,7 @@ int tpm_batch_launch(tpm_batch *b) {
         set_shares(c, p.n_act, p.opening, variant, R.A);
         const bool split = p.n_act > 0 && variant == kSplitWalk;
         if (split) {  // its own launch, after the staging below
-            Launch LA{c->P.precision == TPM_FP32, kSplitWalk, 1u, (tg + 3) / 4, 0u, 0u};
+            Launch LA{c->P.precision == TPM_FP32, kSplitWalk, (tg + 3) / 4, 0u, 0u};
             own.push_back({R.A, LA, p.opening, c->mixed != 0, c->P.periodic != 0,
                            c->P.pm_grid > 0});
         }

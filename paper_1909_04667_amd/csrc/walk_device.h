@@ -45,9 +45,9 @@ struct WalkArgs {
     const double *hs;
     const void *eh;
     // largest extent of a group's targets for the shared cursor in the
-    // census of compact groups (squared; TreePM: half the cutoff radius)
+    // census of compact groups (squared; with a cutoff: half its radius)
     double group_ext2;
-    const uint32_t *census;  // count of compact groups (sparse sets with a cutoff)
+    const uint32_t *census;  // count of compact groups (sparse sets; null: no census)
     // results stored device-coherently (written through to memory at once):
     // set by the resident server, whose later work items read them inside
     // the same kernel; other launches store plainly (visible at kernel end)
@@ -1242,9 +1242,8 @@ __device__ __forceinline__ uint32_t wave_id() {
 // sequence of its own walk (open -> next entry, accept/discard -> skip), so
 // the accumulation order per target is the same as in the shared-cursor walk
 // and in a sequential walk.  Entries are gathered per lane.  A wavefront owns
-// a chunk of 64 * K consecutive slots; lane l takes slots l, l + 64, ... of
-// the chunk one after the other, which evens out the lanes' work while the
-// wave's targets stay spatially close on the curve.
+// 64 consecutive slots (or, where a walk is divided, the shares of as many
+// slots as fill its lanes).
 //
 // FRONT (sparse active sets, too few targets to fill the chip one per lane):
 // a wavefront walks ONE target (slot `wave`).  Phase 1 takes the walk's upper
@@ -1394,7 +1393,7 @@ __device__ __forceinline__ void expand_front(const Rec *__restrict__ R, uint32_t
 }
 
 template <int SHARES, bool PER, bool TPM, int OPEN, bool POT, bool MIXED, bool FRONT = false>
-__device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, uint32_t K,
+__device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave,
                                              uint32_t *front = nullptr,
                                              Parts<double> *P = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
@@ -1402,11 +1401,10 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, u
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
     // (kOneShare: lane l takes share l mod A.shares of a target)
-    const uint32_t T = SHARED ? 64u >> A.shares_log : 64u;  // targets at a time
-    const uint32_t base = FRONT ? wave : wave * T * K;
+    const uint32_t T = SHARED ? 64u >> A.shares_log : 64u;  // targets of a wavefront
+    const uint32_t base = FRONT ? wave : wave * T;
     if (base >= nu)
         return;
-    const uint32_t chunk_end = min(nu, base + T * K);
     const Rec64 *__restrict__ R = (const Rec64 *)A.rec;
     double x0 = 0.0, x1 = 0.0, x2 = 0.0, an = 0.0, a0 = 0.0, a1 = 0.0, a2 = 0.0, pot = 0.0,
            hi = 0.0;
@@ -1481,10 +1479,9 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, u
     if constexpr (!FRONT) {
         const uint32_t share = SHARED ? (uint32_t)lane & (A.shares - 1u) : 0u;
         const uint32_t block = 1u << A.share_shift;
-        const uint32_t own0 = SHARES != kWhole && A.shares > 1u ? 0u : 0xffffffffu;
-        uint32_t slot = base + (SHARED ? (uint32_t)lane >> A.shares_log : (uint32_t)lane);
-        bool live = slot < chunk_end;
-        uint32_t e = 0, own_end = own0;
+        const uint32_t slot = base + (SHARED ? (uint32_t)lane >> A.shares_log : (uint32_t)lane);
+        bool live = slot < nu;
+        uint32_t e = 0, own_end = SHARES != kWhole && A.shares > 1u ? 0u : 0xffffffffu;
         if (live)
             start(slot);
         while (__ballot(live)) {
@@ -1509,12 +1506,7 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, u
                     if (ALL)
                         parts_total(P, cs, A.shares, a0, a1, a2);
                     store_result<double>(A, share * A.plane + slot, a0, a1, a2, POT, pot, nint);
-                    slot += T;
-                    live = slot < chunk_end;
-                    e = 0;
-                    own_end = own0;
-                    if (live)
-                        start(slot);
+                    live = false;
                 }
             }
         }
@@ -1551,7 +1543,7 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave, u
 }
 
 template <int SHARES, bool PER, bool TPM, int OPEN, bool POT, bool MIXED, bool FRONT = false>
-__device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, uint32_t K,
+__device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave,
                                              uint32_t *front = nullptr,
                                              Parts<float> *P = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
@@ -1560,11 +1552,10 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
     // (kOneShare: lane l takes share l mod A.shares of a target)
-    const uint32_t T = SHARED ? 64u >> A.shares_log : 64u;  // targets at a time
-    const uint32_t base = FRONT ? wave : wave * T * K;
+    const uint32_t T = SHARED ? 64u >> A.shares_log : 64u;  // targets of a wavefront
+    const uint32_t base = FRONT ? wave : wave * T;
     if (base >= nu)
         return;
-    const uint32_t chunk_end = min(nu, base + T * K);
     const Rec32 *__restrict__ R = (const Rec32 *)A.rec;
     const double len21 = ldexp(A.L, -kMaxLevel);
     constexpr int SH = PER ? kRecShiftPer : kRecShiftIso;
@@ -1639,10 +1630,9 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
     if constexpr (!FRONT) {
         const uint32_t share = SHARED ? (uint32_t)lane & (shares - 1u) : 0u;
         const uint32_t block = 1u << A.share_shift;
-        const uint32_t own0 = SHARES != kWhole && shares > 1u ? 0u : 0xffffffffu;
-        uint32_t slot = base + (SHARED ? (uint32_t)lane >> A.shares_log : (uint32_t)lane);
-        bool live = slot < chunk_end;
-        uint32_t e = 0, own_end = own0;
+        const uint32_t slot = base + (SHARED ? (uint32_t)lane >> A.shares_log : (uint32_t)lane);
+        bool live = slot < nu;
+        uint32_t e = 0, own_end = SHARES != kWhole && shares > 1u ? 0u : 0xffffffffu;
         if (live)
             start(slot);
         while (__ballot(live)) {
@@ -1667,12 +1657,7 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave, u
                     if (ALL)
                         parts_total(P, cs, shares, a0, a1, a2);
                     store_result<float>(A, share * A.plane + slot, a0, a1, a2, POT, pot, nint);
-                    slot += T;
-                    live = slot < chunk_end;
-                    e = 0;
-                    own_end = own0;
-                    if (live)
-                        start(slot);
+                    live = false;
                 }
             }
         }
