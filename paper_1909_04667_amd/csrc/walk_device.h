@@ -55,6 +55,7 @@ struct WalkArgs {
     // Shares of a target's walk (a power of two; 1: the whole walk in one
     // piece).  See owns() below.
     uint32_t shares, shares_log;
+    uint32_t shares_bh;    // those of the geometric pass, where one request runs both
     uint32_t share_shift;  // log2 of the entries of a block
     uint32_t plane;        // slots per share in res and rpot
 };
@@ -474,19 +475,15 @@ __device__ __forceinline__ bool owns(const WalkArgs &A, uint32_t e, uint32_t sha
     return ((e >> A.share_shift) & (A.shares - 1u)) == share;
 }
 
+// The shares of the pass with that criterion (a resident step runs both).
+__device__ __forceinline__ uint32_t shares_of(const WalkArgs &A, int opening) {
+    return opening == TPM_OPEN_BH ? A.shares_bh : A.shares;
+}
+
 // All ones for equal shares, none otherwise (on the scalar unit).
 __device__ __forceinline__ uint64_t equal_mask(uint32_t a, uint32_t b) {
     const uint32_t m = (uint32_t)((int32_t)((a ^ b) - 1u) >> 31);
     return ((uint64_t)m << 32) | m;
-}
-
-// The shares of an FP32 walk: the geometric pass is not divided.  Its forces
-// give the |a| by which the relative pass opens cubes; summed in another
-// order they differ in the last bits, and the few decisions that then change
-// move single forces by up to 1.7e-3 (one in five systems of 10^5 particles
-// had one above 8e-4).  In FP64 no decision changes.
-__device__ __forceinline__ uint32_t shares32(const WalkArgs &A, int opening) {
-    return opening == TPM_OPEN_BH ? 1u : A.shares;
 }
 
 // Who walks a target's shares.
@@ -554,10 +551,11 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t item, I
                                              Parts<double> *P = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
     static_assert(!(ALL && POT), "");
+    const uint32_t shares = shares_of(A, OPEN);
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
     const uint32_t it = __builtin_amdgcn_readfirstlane(item);
-    const uint32_t share = SHARED ? it & (A.shares - 1u) : 0u;
+    const uint32_t share = SHARED ? it & (shares - 1u) : 0u;
     const uint32_t wave = SHARED ? it >> A.shares_log : it;  // the group
     if (wave * 64u >= nu)
         return;  // whole wavefront
@@ -732,16 +730,16 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t item, I
     uint64_t own = ~0ull;  // all ones: entries are accepted here (none: another share's)
     bool dealt = false;    // a cube larger than a block: its particles are dealt out
     if (ALL)
-        parts_clear(P, A.shares);
+        parts_clear(P, shares);
     uint32_t c = 0;
     while (c < A.E) {
         // the whole walk, or the next stretch of it that belongs to one share
         uint32_t end = A.E;
-        if (SHARES != kWhole && A.shares > 1u) {
+        if (SHARES != kWhole && shares > 1u) {
             const uint32_t cu = __builtin_amdgcn_readfirstlane(c);
             const uint32_t skip = uniform_skip(R, cu);
             dealt = skip - cu > 1u << A.share_shift;
-            sh = (cu >> A.share_shift) & (A.shares - 1u);
+            sh = (cu >> A.share_shift) & (shares - 1u);
             if (SHARED) {
                 if (!dealt && sh != share) {
                     c = skip;
@@ -822,7 +820,7 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t item, I
                         const uint32_t e = base + (uint32_t)__builtin_ctzll(m);
                         m &= m - 1;
                         if (ALL && dealt) {
-                            sh = (e >> A.share_shift) & (A.shares - 1u);
+                            sh = (e >> A.share_shift) & (shares - 1u);
                         }
                         particle(uniform_rec(R, e), e, desc);
                     }
@@ -834,7 +832,7 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t item, I
     if (TPM && qn)
         flush();
     if (ALL)
-        parts_total(P, cs, A.shares, a0, a1, a2);
+        parts_total(P, cs, shares, a0, a1, a2);
     if (valid)
         store_result<double>(A, (SHARED ? share * A.plane : 0u) + slot, a0, a1, a2, POT, pot, nint);
 }
@@ -995,7 +993,7 @@ __device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t item,
                                              Parts<float> *P = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
     static_assert(!(ALL && POT), "");
-    const uint32_t shares = shares32(A, OPEN);
+    const uint32_t shares = shares_of(A, OPEN);
     constexpr int SH = PER ? kRecShiftPer : kRecShiftIso;
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
@@ -1409,6 +1407,7 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave,
                                              Parts<double> *P = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
     static_assert(!(ALL && POT), "");
+    const uint32_t shares = shares_of(A, OPEN);
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
     // (kOneShare: lane l takes share l mod A.shares of a target)
@@ -1434,7 +1433,7 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave,
         nint = 0;
         if (ALL) {
             cs = sh = 0u;
-            parts_clear(P, A.shares);
+            parts_clear(P, shares);
         }
     };
     // entry e for this lane's target: the decision and the interaction, as
@@ -1488,11 +1487,11 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave,
         return step_in;
     };
     if constexpr (!FRONT) {
-        const uint32_t share = SHARED ? (uint32_t)lane & (A.shares - 1u) : 0u;
+        const uint32_t share = SHARED ? (uint32_t)lane & (shares - 1u) : 0u;
         const uint32_t block = 1u << A.share_shift;
         const uint32_t slot = base + (SHARED ? (uint32_t)lane >> A.shares_log : (uint32_t)lane);
         bool live = slot < nu;
-        uint32_t e = 0, own_end = SHARES != kWhole && A.shares > 1u ? 0u : 0xffffffffu;
+        uint32_t e = 0, own_end = SHARES != kWhole && shares > 1u ? 0u : 0xffffffffu;
         if (live)
             start(slot);
         while (__ballot(live)) {
@@ -1505,7 +1504,7 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave,
                         owned = owns(A, e, share);
                         over = small && !owned;
                     } else {
-                        sh = (e >> A.share_shift) & (A.shares - 1u);
+                        sh = (e >> A.share_shift) & (shares - 1u);
                     }
                     own_end = small && owned ? r.skip : own_end;
                 }
@@ -1515,7 +1514,7 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave,
                     e = visit(e, r, owned) ? e + 1u : r.skip;
                 if (e >= A.E) {
                     if (ALL)
-                        parts_total(P, cs, A.shares, a0, a1, a2);
+                        parts_total(P, cs, shares, a0, a1, a2);
                     store_result<double>(A, share * A.plane + slot, a0, a1, a2, POT, pot, nint);
                     live = false;
                 }
@@ -1559,7 +1558,7 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave,
                                              Parts<float> *P = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
     static_assert(!(ALL && POT), "");
-    const uint32_t shares = shares32(A, OPEN);
+    const uint32_t shares = shares_of(A, OPEN);
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
     // (kOneShare: lane l takes share l mod A.shares of a target)
@@ -1717,7 +1716,7 @@ enum Variant : uint32_t { kGroupWalk = 0, kLaneWalk = 1, kSplitWalk = 2, kGroupO
 // take the lanes there).
 Variant walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok = false);
 // Shares of a walk over n_act targets with that criterion and variant, into A
-// (a walk of both criteria, the server's steps: those of the relative pass).
+// (a resident step, which runs both: TPM_OPEN_REL).
 void set_shares(const tpm_ctx *c, int64_t n_act, int opening, Variant v, WalkArgs &A);
 // Wavefronts of a walk over nu unique targets.
 __host__ __device__ inline uint32_t walk_waves(Variant v, uint32_t nu, uint32_t shares) {

@@ -307,6 +307,58 @@ def test_resident_adds_the_same_shares(prec, mesh):
     lp.close()
 
 
+def _threshold_lattice(side=64):
+    """2 side^3 particles of a periodic lattice with a basis of two, on
+    coordinates without rounding: with every cube opened all particles have
+    one |a| up to the rounding of its sums.  alpha puts the relative criterion
+    for the cube two sites along x exactly at that |a|, so that last bits of
+    |a| decide."""
+    s = 1.0 / side
+    q = (np.arange(side) + 0.25) * s
+    g = np.stack(np.meshgrid(q, q, q, indexing="ij")).reshape(3, -1)
+    x = np.concatenate([g, g + np.array([[0.375 * s], [0.0], [0.0]])], axis=1)
+    kw = dict(periodic=True, box_size=1.0, pm_grid=side, asmth=1.0, rcut=2.5, theta=0.0,
+              eps=0.01 * s, precision="fp64")
+    d = (2.0 + 0.1875) * s  # from the first of a basis to the centre of the next but one
+    return x, kw, (2.0 / x.shape[1]) * s * s / d ** 4
+
+
+def test_resident_step_geometric_pass_between_2p18_and_2p19():
+    """An FP64 step of 2^19 targets: its geometric pass is summed as
+    tpm_compute_forces sums it (undivided at this size, where the relative
+    pass is divided), to the last bit of |a| -- opening decisions hang on it
+    here -- so the step equals the four calls bit for bit."""
+    from paper_1909_04667_amd import binding as B
+    x, kw, num = _threshold_lattice()
+    n = x.shape[1]
+    t = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device=_dev())
+    xyz = [t(v) for v in x]
+    ix = torch.arange(n, dtype=torch.int32, device=_dev())
+    ctx = B.Context(**kw)
+    ctx.build_tree(*xyz)
+    an = ctx.accel_norm(ix, ctx.compute_forces(ix, "bh")[0], ctx.pm_long_range(ix)[0])
+    ctx.close()
+    ctx = B.Context(alpha=num / float(an[: n // 2].median()), **kw)
+    ctx.build_tree(*xyz)
+    count = lambda: torch.empty(n, dtype=torch.int32, device=_dev())
+    c_ref, c_off, c_step = count(), count(), count()
+    pm, _ = ctx.pm_long_range(ix)
+    an = ctx.accel_norm(ix, ctx.compute_forces(ix, "bh")[0], pm)
+    ref, _ = ctx.compute_forces(ix, "rel", a_old_norm=an, n_interactions=c_ref)
+    # the last bit of |a| does decide here
+    off = torch.nextafter(an, torch.full_like(an, float("inf")))
+    ctx.compute_forces(ix, "rel", a_old_norm=off, n_interactions=c_off)
+    assert int((c_ref != c_off).sum()) > 100
+    lp = B.ResidentServer("fp64")
+    torch.cuda.synchronize()
+    tk, acc, acc_pm = lp.submit_step(ctx, ix, n_interactions=c_step)
+    lp.wait(tk)
+    lp.close()
+    ctx.check()
+    assert torch.equal(c_step, c_ref)
+    assert torch.equal(acc, ref) and torch.equal(acc_pm, pm)
+
+
 def test_resident_requests_join_the_running_kernel():
     """A large request keeps the kernel busy; requests submitted meanwhile
     are taken up by the same launch, and a context rebuilt meanwhile is
