@@ -92,7 +92,7 @@ k_walk64m(const WalkArgs A) {
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk64im(const WalkArgs A) {
     if (!mostly_compact(A))
-        walk_lanes64<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, lane_wave_id());
+        walk_lanes64<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, lane_wave_id<PER>());
 }
 
 template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kBlock) void k_walk32m(const WalkArgs A) {
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk32im(const WalkArgs A) {
     if (!mostly_compact(A))
-        walk_lanes32<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, lane_wave_id());
+        walk_lanes32<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, lane_wave_id<PER>());
 }
 
 // one wavefront per target (sparse active sets)

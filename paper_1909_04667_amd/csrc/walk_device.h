@@ -1230,19 +1230,23 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb) {
     return ((i / run) * 8u + (b & 7u)) * run + i % run;
 }
 
-// The lane walk keeps one contiguous eighth of the curve per XCD: its targets
-// are spread over the whole system, so the eighths are even, and its per-lane
-// record loads live off the L2.  Relative pass, in runs and in eighths:
-// clustered 160^3 box, random 10 % FP32 2.76 and 2.45 ms, 20 % 3.95 and 3.69, 5 %
-// FP64 2.94 and 2.75; random 2 to 20 % of a Hernquist sphere the same.
+__device__ __forceinline__ uint32_t wave_id() {
+    return (xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x) >> 6;
+}
+
+// The lane walk in a periodic box keeps one contiguous eighth of the curve per
+// XCD: its targets are spread over the whole box, so the eighths are even, and
+// its per-lane record loads live off the L2.  Relative pass, in runs and in
+// eighths: clustered 160^3 box, random 10 % FP32 2.76 and 2.45 ms, 20 % 3.95 and 3.69,
+// 5 % FP64 2.94 and 2.75; but random 5 % of a Hernquist sphere of 2^22 FP32 2.28 and
+// 2.53, FP64 3.16 and 3.71.
+template <bool PER>
 __device__ __forceinline__ uint32_t lane_wave_id() {
+    if (!PER)
+        return wave_id();
     const uint32_t b = blockIdx.x, full = gridDim.x & ~7u;
     const uint32_t x = b >= full ? b : (b & 7u) * (full >> 3) + (b >> 3);
     return (x * kBlock + threadIdx.x) >> 6;
-}
-
-__device__ __forceinline__ uint32_t wave_id() {
-    return (xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x) >> 6;
 }
 
 // ---- lane-independent walks ------------------------------------------------
