@@ -849,7 +849,7 @@ int submit_impl(tpm_server *s, tpm_ctx *c, bool step, int32_t opening, int64_t n
     s->free_slots.pop_back();
     SrvReq R{};
     wk::fill_args(c, step ? (const double *)c->srv_an.p : anorm, w, R.A);
-    const wk::Variant variant = wk::walk_variant(c, n_act);
+    const wk::Variant variant = wk::walk_variant(c, n_act, opening);
     wk::set_shares(c, n_act, opening, variant, R.A);
     R.A.coherent = 1u;  // later items of the request read the results in this kernel
     R.idx = idx;

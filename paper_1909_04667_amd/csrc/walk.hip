@@ -57,7 +57,10 @@ __global__ __launch_bounds__(kBlock) void k_walk32(const WalkArgs A) {
 // 0.80 against 1.55, the densest 2 % 0.63 against 1.11, random 20 % 1.03
 // against 1.46, 10 % 0.97 against 1.16, 7 % 1.06 against 1.03, 5 % 0.98 against
 // 0.76; of 2^18 (eight shares) random 20 % 0.54 against 0.71, 10 % 0.63 against
-// 0.47.
+// 0.47.  With an isolated mesh the cutoff spans many such groups, so both tests
+// apply; FP64, Hernquist sphere of 2^20, 64^3 mesh: random 2 % 2.50 against 1.44 (the
+// geometric pass 3.98 against 1.95), 5 % 2.31 against 1.81, 10 % 2.29 against 2.74, the
+// densest 2 % 2.21 against 2.75.
 // (Choosing per group inside one kernel made its lane walk slower: 7.6
 // against 6.0 ms on a random 10 % of the box.)
 template <bool PER, bool TPM>
@@ -69,10 +72,7 @@ __global__ __launch_bounds__(kBlock) void k_census(const WalkArgs A, uint32_t *c
         atomicAdd(census, 1u);
 }
 
-// (Without a census: lanes, where they were asked for.)
 __device__ __forceinline__ bool mostly_compact(const WalkArgs &A) {
-    if (!A.census)
-        return false;
     const uint32_t groups = (load_count(A.nuniq) + 63u) / 64u;
     return 2ull * load_count(A.census) >= groups;
 }
@@ -101,10 +101,10 @@ __global__ __launch_bounds__(kBlock) void k_walk32m(const WalkArgs A) {
         walk_group32<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id());
 }
 
-template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_walk32im(const WalkArgs A) {
     if (!mostly_compact(A))
-        walk_lanes32<kOneShare, PER, TPM, OPEN, POT, MIXED>(A, lane_wave_id<PER>());
+        walk_lanes32<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, lane_wave_id<PER>());
 }
 
 // one wavefront per target (sparse active sets)
@@ -272,6 +272,19 @@ struct Launch {
     unsigned census_blocks;  // and of the census
 };
 
+// Undivided lanes have an instance of their own in FP32, where the geometric pass
+// always is (random 2 to 10 % of Hernquist spheres, 1.53 -> 1.47 to 1.72 -> 1.60 ms); the
+// FP64 one was slower (10 % of 2^20 with a mesh: 2.90 -> 3.48).
+template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+void launch_lanes(const WalkArgs &A, bool fp32, unsigned blocks, hipStream_t st) {
+    if (!fp32)
+        k_walk64im<PER, TPM, OPEN, POT, MIXED><<<blocks, kBlock, 0, st>>>(A);
+    else if (A.shares > 1u)
+        k_walk32im<OPEN == TPM_OPEN_REL, PER, TPM, OPEN, POT, MIXED><<<blocks, kBlock, 0, st>>>(A);
+    else
+        k_walk32im<false, PER, TPM, OPEN, POT, MIXED><<<blocks, kBlock, 0, st>>>(A);
+}
+
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 void launch_walk(const WalkArgs &A, const Launch &L, hipStream_t st) {
     if (L.variant == kSplitWalk) {
@@ -280,10 +293,7 @@ void launch_walk(const WalkArgs &A, const Launch &L, hipStream_t st) {
         else
             k_walk64s<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
     } else if (L.variant == kLaneWalk) {
-        if (L.fp32)
-            k_walk32im<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
-        else
-            k_walk64im<PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+        launch_lanes<PER, TPM, OPEN, POT, MIXED>(A, L.fp32, L.blocks, st);
     } else if (L.variant == kGroupOrLanes) {
         k_census<PER, TPM><<<L.census_blocks, kBlock, 0, st>>>(A, (uint32_t *)A.census);
         if (L.fp32) {
@@ -291,14 +301,13 @@ void launch_walk(const WalkArgs &A, const Launch &L, hipStream_t st) {
                 k_walk32m<OPEN == TPM_OPEN_REL, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
             else
                 k_walk32m<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
-            k_walk32im<PER, TPM, OPEN, POT, MIXED><<<L.lane_blocks, kBlock, 0, st>>>(A);
         } else {
             if (A.shares > 1u)
                 k_walk64m<true, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
             else
                 k_walk64m<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
-            k_walk64im<PER, TPM, OPEN, POT, MIXED><<<L.lane_blocks, kBlock, 0, st>>>(A);
         }
+        launch_lanes<PER, TPM, OPEN, POT, MIXED>(A, L.fp32, L.lane_blocks, st);
     } else {
         if (L.fp32) {
             if (A.shares > 1u)
@@ -411,6 +420,27 @@ int select_active(tpm_ctx *c, int64_t n_act, const int32_t *idx) {
     return select_active_into(c, n_act, idx, w);
 }
 
+// The geometric pass over a sparse set of an isolated system in FP64: thousands
+// of interactions for each target, and every share repeats the steps of the upper
+// tree, so shares stop paying early.  ms for 1, 2, 4 shares, random | densest set
+// (shared cursor or lanes by the census): Hernquist 2^20, 4 % 2.04 1.65 1.97 | 2.41 1.62
+// 1.26, 6 % 2.04 1.83 2.87 | 2.11 1.64 1.32, 7.5 % 2.05 2.23 3.25 | 2.10 1.72 1.45; 2^22, 2 %
+// 2.51 3.17 5.00 | 2.29 2.04 2.14, 4 % 3.73 5.33 9.42 | 2.68 3.00 3.37.
+// With a mesh the cutoff spans tens of length units, and lanes win from there on
+// (2^20, 64^3 mesh, lanes | shared cursor at the better of the two: 5 % random 2.44 | 3.48,
+// densest 2.45 | 2.38; 10 % 2.86 | 3.60, 3.05 | 3.25; 2^21, 9 % 3.71 | 5.54, 3.85 | 4.97).
+// With individual softening, whose interactions cost more, four shares pay as
+// elsewhere (2^20, 10 % 4.48 3.36 2.75 | 3.24 2.57 2.21).
+constexpr int64_t kGeoShares4 = 49152, kGeoShares2 = 98304;
+static bool sparse_geometric(const tpm_ctx *c, int64_t n_act, int opening) {
+    return !c->P.periodic && !c->mixed && opening == TPM_OPEN_BH && 4 * n_act < c->n;
+}
+// In FP32 that pass is undivided (below), and up to here lanes fill the chip
+// better than groups.  Without a mesh, lanes | shared cursor: Hernquist 2^18, 10 %
+// random 1.34 | 1.93, densest 1.28 | 1.41; 2^20, 10 % 1.64 | 2.14, 1.59 | 1.77, 20 %
+// 2.30 | 1.89, 2.21 | 2.19; 2^22, the densest 3 % 1.82 | 1.91, 4 % 1.95 | 1.81.
+constexpr int64_t kGeoLanes32 = 131072;
+
 // Walk variant.  Independent lanes (results identical to the shared cursor)
 // for sparse active sets whose groups are too spread out for a shared cursor
 // (it would visit the union of their walks); the shared cursor otherwise.
@@ -439,7 +469,7 @@ int select_active(tpm_ctx *c, int64_t n_act, const int32_t *idx) {
 // summation there (see set_shares).
 // TPM_WALK_MODE (1 shared cursor, 2 lanes, 3 one wavefront per target)
 // overrides the choice.
-Variant wk::walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok) {
+Variant wk::walk_variant(const tpm_ctx *c, int64_t n_act, int opening, bool census_ok) {
     if (c->walk_mode != 0)
         return c->walk_mode == 1 ? kGroupWalk : c->walk_mode == 2 ? kLaneWalk : kSplitWalk;
     const int64_t targets = std::min<int64_t>(n_act, c->n);
@@ -449,6 +479,10 @@ Variant wk::walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok) {
     if (4 * n_act >= c->n)
         return kGroupWalk;
     // a sparse set: as the census of its groups decides
+    const bool fp32 = c->P.precision == TPM_FP32, mesh = c->P.pm_grid > 0;
+    if (sparse_geometric(c, n_act, opening) &&
+        (fp32 ? !mesh && n_act <= kGeoLanes32 : mesh && n_act > kGeoShares4))
+        return kLaneWalk;
     return census_ok ? kGroupOrLanes : kLaneWalk;
 }
 
@@ -482,10 +516,13 @@ Variant wk::walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok) {
 // bits, and the few decisions that then change move single forces by up to
 // 1.7e-3 (one in five systems of 10^5 particles had one above 8e-4).  In FP64 no
 // decision changes.
-static uint32_t shares_log(const tpm_ctx *c, int64_t t, int opening, Variant v) {
+static uint32_t shares_log(const tpm_ctx *c, int64_t n_act, int opening, Variant v) {
+    const int64_t t = std::min<int64_t>(n_act, c->n);
     const bool fp32 = c->P.precision == TPM_FP32, rel = opening == TPM_OPEN_REL;
     if (v == kSplitWalk || (fp32 && !rel))
         return 0u;
+    if (sparse_geometric(c, n_act, opening))  // FP64
+        return n_act <= kGeoShares4 ? 2u : n_act <= kGeoShares2 ? 1u : 0u;
     if (t <= 65536 && fp32)
         return 3u;
     if (t <= 196608)
@@ -496,15 +533,14 @@ static uint32_t shares_log(const tpm_ctx *c, int64_t t, int opening, Variant v) 
 }
 
 void wk::set_shares(const tpm_ctx *c, int64_t n_act, int opening, Variant v, WalkArgs &A) {
-    const int64_t t = std::min<int64_t>(n_act, c->n);
-    A.shares_log = shares_log(c, t, opening, v);
+    A.shares_log = shares_log(c, n_act, opening, v);
     A.shares = 1u << A.shares_log;
-    A.shares_bh = 1u << shares_log(c, t, TPM_OPEN_BH, v);
+    A.shares_bh = 1u << shares_log(c, n_act, TPM_OPEN_BH, v);
     A.share_shift = 8;
     if (!c->P.periodic)
         while (A.share_shift < 12u && (c->E >> (A.share_shift + 7)) > 1)
             A.share_shift++;
-    A.plane = (uint32_t)t;
+    A.plane = (uint32_t)std::min<int64_t>(n_act, c->n);
 }
 
 void wk::fill_args(tpm_ctx *c, const double *anorm, const Work &w, WalkArgs &A) {
@@ -604,9 +640,10 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
     const int64_t groups = (std::min<int64_t>(n_act, n) + 63) / 64;
     Launch LA;
     LA.fp32 = fp32;
-    LA.variant = walk_variant(c, n_act, true);
+    LA.variant = walk_variant(c, n_act, opening, true);
     set_shares(c, n_act, opening, LA.variant, A);
-    if (LA.variant == kGroupOrLanes) {  // the census word follows the unique count
+    if (LA.variant == kGroupOrLanes || LA.variant == kLaneWalk) {
+        // the census word follows the unique count (no census: no compact group)
         A.census = w.nuniq + 1;
         TPM_TRY(fill_u32(c, w.nuniq + 1, 0u, 1));
     }
@@ -671,7 +708,7 @@ __device__ __forceinline__ void batch_group(const WalkArgs &A, uint32_t g, uint3
                                             IQ64 *Q) {
     if constexpr (FP32) {
         if (var == kLaneWalk)
-            walk_lanes32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g);
+            walk_lanes32<OPEN == TPM_OPEN_REL ? kOneShare : kWhole, PER, TPM, OPEN, false, MIXED>(A, g);
         else if (OPEN == TPM_OPEN_REL && A.shares > 1u)
             walk_group32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g);
         else
@@ -894,12 +931,12 @@ int tpm_batch_launch(tpm_batch *b) {
         BatchReq &R = b->host[o];
         R = BatchReq{};
         fill_args(c, p.anorm, w, R.A);
+        const Variant variant = walk_variant(c, p.n_act, p.opening);
         R.variant = (p.opening == TPM_OPEN_REL ? 1u : 0u) | (c->P.pm_grid > 0 ? 2u : 0u) |
-                    ((uint32_t)walk_variant(c, p.n_act) << 5) | (c->P.periodic ? 8u : 0u) |
+                    ((uint32_t)variant << 5) | (c->P.periodic ? 8u : 0u) |
                     (c->mixed ? 16u : 0u);
         R.first = items[which];
         const uint32_t tg = (uint32_t)std::min<int64_t>(p.n_act, c->n);
-        const Variant variant = walk_variant(c, p.n_act);
         set_shares(c, p.n_act, p.opening, variant, R.A);
         const bool split = p.n_act > 0 && variant == kSplitWalk;
         if (split) {  // its own launch, after the staging below

@@ -47,7 +47,7 @@ struct WalkArgs {
     // largest extent of a group's targets for the shared cursor in the
     // census of compact groups (squared; with a cutoff: half its radius)
     double group_ext2;
-    const uint32_t *census;  // count of compact groups (sparse sets; null: no census)
+    const uint32_t *census;  // count of compact groups (sparse sets)
     // results stored device-coherently (written through to memory at once):
     // set by the resident server, whose later work items read them inside
     // the same kernel; other launches store plainly (visible at kernel end)
@@ -1715,10 +1715,10 @@ void fill_args(tpm_ctx *c, const double *anorm, const Work &w, WalkArgs &A);
 // shared cursor or lanes as a census of the groups' extents decides on the
 // device (the two give the same results).
 enum Variant : uint32_t { kGroupWalk = 0, kLaneWalk = 1, kSplitWalk = 2, kGroupOrLanes = 3 };
-// The walk for an active set of n_act targets.  census_ok: kGroupOrLanes may
-// be returned (single-system launches; the batch and the resident server
-// take the lanes there).
-Variant walk_variant(const tpm_ctx *c, int64_t n_act, bool census_ok = false);
+// The walk for an active set of n_act targets and that criterion (a resident
+// step: the relative one).  census_ok: kGroupOrLanes may be returned
+// (single-system launches; the batch and the resident server take the lanes there).
+Variant walk_variant(const tpm_ctx *c, int64_t n_act, int opening, bool census_ok = false);
 // Shares of a walk over n_act targets with that criterion and variant, into A
 // (a resident step, which runs both: TPM_OPEN_REL).
 void set_shares(const tpm_ctx *c, int64_t n_act, int opening, Variant v, WalkArgs &A);
@@ -1734,21 +1734,23 @@ __host__ __device__ inline uint32_t walk_waves(Variant v, uint32_t nu, uint32_t 
 }
 
 // Whether the targets of group `wave` (its 64 slots; the caller has checked
-// that the group is not empty) lie within a box of side sqrt(A.group_ext2)
-// (nearest images in a periodic box), so that a shared cursor walks little
-// more than each target's own walk.  Wavefront-uniform.
-// Without a cutoff: whether they lie close on the curve, at most 8 particles
-// for each target (12 where the walk has at most four shares; the measurements
+// that the group is not empty) are close enough that a shared cursor walks
+// little more than each target's own walk.  Wavefront-uniform.
+// With a cutoff: within a box of side sqrt(A.group_ext2) (nearest images in a
+// periodic box).  In an isolated system: on the curve, at most 8 particles for
+// each target (12 where the walk has at most four shares; the measurements
 // are at k_census).
 template <bool PER, bool TPM>
 __device__ __forceinline__ bool group_compact(const WalkArgs &A, uint32_t wave) {
     const int lane = threadIdx.x & 63;
     const uint32_t nu = load_count(A.nuniq);
-    if constexpr (!TPM) {
+    if constexpr (!PER) {
         const uint32_t first = coherent_ld(A.act + wave * 64u);
         const uint32_t last = coherent_ld(A.act + min(wave * 64u + 63u, nu - 1u));
-        return __builtin_amdgcn_readfirstlane(
-                   (int)(last - first < (A.shares > 4u ? 512u : 768u))) != 0;
+        const bool near = __builtin_amdgcn_readfirstlane(
+                              (int)(last - first < (A.shares > 4u ? 512u : 768u))) != 0;
+        if (!TPM || !near)
+            return near;
     }
     const uint32_t slot = wave * 64u + lane;
     const uint32_t s = coherent_ld(A.act + (slot < nu ? slot : wave * 64u));

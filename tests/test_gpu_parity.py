@@ -531,6 +531,43 @@ def test_sparse_sets_group_or_lanes_identical(prec):
         assert torch.equal(acc.cpu(), full[:, sub])
 
 
+@pytest.mark.parametrize("k", [4097, 49152, 49153, 98304, 98305])
+@pytest.mark.parametrize("prec,mesh", [("fp64", 0), ("fp64", 32), ("fp32", 32)])
+def test_sparse_sets_of_an_isolated_system(prec, mesh, k, monkeypatch):
+    """Sparse sets of an isolated system: shared cursor or lanes by the census
+    (spread sets and compact ones), lanes in the FP64 geometric pass with a
+    mesh beyond 49152 targets, four, two shares or one there.  Whatever is
+    taken, the shared cursor and the lanes give it bit for bit, and no
+    interaction is lost (counts of one wavefront per target)."""
+    p = W.hernquist(400000, 31)
+    n = p.n
+    r = p.x ** 2 + p.y ** 2 + p.z ** 2
+    near = np.sort(np.argsort(r, kind="stable")[:k])
+    rand = np.sort(np.random.default_rng(k).choice(n, k, replace=False))
+    kw = dict(precision=prec, eps=0.02, theta=0.8)
+    if mesh:
+        kw.update(pm_grid=mesh, rcut=1.5)
+    ctxs = []
+    for mode in ("0", "1", "2", "3"):
+        monkeypatch.setenv("TPM_WALK_MODE", mode)
+        ctxs.append(_ctx(**kw))
+        _build(ctxs[-1], p)
+    an = _t(np.full(n, 1.0))
+    for sub in (near, rand):
+        for opening in ("bh", "rel"):
+            out = []
+            for ctx in ctxs:
+                nint = torch.empty(k, dtype=torch.int32, device=_dev())
+                acc, _ = ctx.compute_forces(_t(sub, torch.int32), opening, a_old_norm=an,
+                                            n_interactions=nint)
+                ctx.check()
+                out.append((acc, nint))
+            for acc, nint in out[1:3]:
+                assert torch.equal(acc, out[0][0])
+            for acc, nint in out[1:]:
+                assert torch.equal(nint, out[0][1])
+
+
 def test_out_of_range_index_reported():
     from paper_1909_04667_amd import binding as B
     p = W.plummer(500, 13)
