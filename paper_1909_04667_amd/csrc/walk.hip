@@ -140,10 +140,12 @@ __global__ __launch_bounds__(kBlock) void k_mark(const int32_t *__restrict__ idx
 // in LDS, then ranked) instead of four that are shorter than their gaps (mark,
 // count, compact and, after a build, clear: 20 us against 6).  The marks in
 // memory are cleared when the call asks for it, as later calls on the context
-// rely on.
+// rely on.  One workgroup reads a long list with many duplicates slower than the
+// chip does: whole calls for 16384, 32768 and 65536 entries 47, 52 and 63 us against
+// 51 in four launches (512 particles), 77, 83 and 96 against 87 (4096).
 constexpr int kSelBlock = 1024;
 constexpr int64_t kSelN = 8192;       // particles
-constexpr int64_t kSelActive = 65536;  // entries of the active list
+constexpr int64_t kSelActive = 16384;  // entries of the active list
 __global__ __launch_bounds__(kSelBlock) void k_select_small(
     const int32_t *__restrict__ idx, int n_act, int n, const int32_t *__restrict__ rank,
     uint8_t *__restrict__ mark, int clear, uint32_t *__restrict__ act,

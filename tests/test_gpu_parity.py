@@ -416,6 +416,35 @@ def test_active_slots_over_many_calls(n):
     ctx.check()
 
 
+@pytest.mark.parametrize("n", [1, 512, 8192])
+@pytest.mark.parametrize("m", [16384, 16385, 70001])
+def test_active_lists_of_many_duplicates(n, m):
+    """Lists longer than the tree, around the length where the selection of
+    small trees changes its kernels: every entry gets its particle's result
+    and count, out-of-range entries NaN, and the flag is set."""
+    from paper_1909_04667_amd import binding as B
+    p = W.uniform_cube(n, 67)
+    ctx = _ctx(precision="fp32", eps=0.01, theta=1.0)
+    _build(ctx, p)
+    nfull = torch.empty(n, dtype=torch.int32, device=_dev())
+    full, _ = ctx.compute_forces(_t(np.arange(n), torch.int32), "bh", n_interactions=nfull)
+    ids = torch.randint(0, n, (m,), dtype=torch.int32, device=_dev(),
+                        generator=torch.Generator(device=_dev()).manual_seed(m))
+    for bad in (False, True):
+        if bad:
+            ids[m // 2], ids[m - 1] = n, -1
+        got = torch.zeros(m, dtype=torch.int32, device=_dev())
+        acc, _ = ctx.compute_forces(ids, "bh", n_interactions=got)
+        ok = (ids >= 0) & (ids < n)
+        sel = ids[ok].long()
+        assert torch.equal(got[ok], nfull[sel])
+        assert bool(torch.isnan(acc[:, ~ok]).all())
+        assert torch.equal(acc[:, ok], full[:, sel])
+    with pytest.raises(B.TreePMError) as ei:
+        ctx.check()
+    assert ei.value.code == B.TPM_EINDEX
+
+
 @pytest.mark.parametrize("n", [4097, 65536, 65537, 196609, 262145, 524288, 524289])
 @pytest.mark.parametrize("mesh", [0, 16])
 def test_shares_of_a_walk(n, mesh, monkeypatch):
