@@ -318,10 +318,9 @@ int tpm_export_tree(tpm_ctx *ctx, int32_t *level, int64_t *first, int64_t *count
 /* ---- Serving: continuous batching over many systems ---------------------
  * A batch stages tree-force requests (one per context per batch) of many
  * resident systems with uneven N and active fractions (the time-step bins of
- * Sec. 7.2) and walks all of them in ONE persistent launch per precision:
- * wavefronts pop work items (a group of 64 curve-adjacent targets of one
- * request) from a device counter until the finite list is exhausted.  Every
- * work item runs the same per-group walk as tpm_compute_forces, so each
+ * Sec. 7.2) and walks all of them in ONE launch per precision, whose workgroups
+ * each take groups of 64 curve-adjacent targets of one request.  Every group
+ * runs the same walk as in tpm_compute_forces, so each
  * request's result is bit-identical alone and in any mix.
  * All work is enqueued on the batch's stream; the caller orders each
  * context's build (and PM solve) before the launch (same stream or an

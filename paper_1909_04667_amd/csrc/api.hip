@@ -125,8 +125,8 @@ void visit_sizes(tpm_ctx *c, const tpm_params &P, int64_t n, int64_t E, bool mix
     f(c->mark, mark_bytes(n), 0);
     f(c->act, 4 * N, 0);
     f(c->slot, 4 * N, 0);
-    f(c->res, 4 * (size_t)result_slots(n) * esz, 0);
-    f(c->rpot, (size_t)result_slots(n) * esz, 0);
+    f(c->res, 4 * N * esz, 0);
+    f(c->rpot, N * esz, 0);
     f(c->srv_an, 8 * N, 0);
     if (P.pm_grid > 0)
         f(c->srv_pm, 4 * N * esz, 0);

@@ -20,9 +20,8 @@ namespace {
 
 // Largest tree the array serves, and its layout (byte offsets, 256-aligned):
 // marks, active slots, slot map, results [n][4] (acceleration and interaction
-// count) and potentials [n] in FP64 (the planes of a walk's shares, at most
-// 2^20 slots, fit in them), compaction tile counts, and the unique-active
-// counter.
+// count) and potentials [n] in FP64, compaction tile counts, and the
+// unique-active counter.
 constexpr int64_t kMaxN = int64_t(1) << 20;
 constexpr size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 constexpr size_t kOffMark = 0;

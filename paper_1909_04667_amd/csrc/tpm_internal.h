@@ -179,10 +179,9 @@ struct Work {
     uint32_t *slot = nullptr;   // [n] rank -> position in act
     uint32_t *counts = nullptr; // [ceil(n / scan tile)] compaction tile counts
     uint32_t *nuniq = nullptr;  // [1] number of unique actives
-    void *res = nullptr;        // [result_slots(n)][4] results in slot order (dtype of the
-                                // context): acceleration and the interaction count's bits,
-                                // one plane per share of the walk
-    void *rpot = nullptr;       // [result_slots(n)]
+    void *res = nullptr;        // [n][4] results in slot order (dtype of the context):
+                                // acceleration and the interaction count's bits
+    void *rpot = nullptr;       // [n]
 };
 
 // The clear that a call on the marks asked for is queued (or none was needed):
@@ -196,13 +195,6 @@ inline void marks_queued(const Work &w) {
 
 // Bytes of the marks of n particles.
 inline size_t mark_bytes(int64_t n) { return ((size_t)n + 15) & ~size_t(15); }
-
-// Walks of small sets are divided into shares (walk_device.h), at most eight and
-// at most 2^20 records altogether: slots of the results of a tree of n.
-inline int64_t result_slots(int64_t n) {
-    const int64_t s = 8 * n < (int64_t(1) << 20) ? 8 * n : (int64_t(1) << 20);
-    return n > s ? n : s;
-}
 
 // Primitives (prims.hip) ---------------------------------------------------
 // Exclusive scan of n uint32 values; total written to d_total if non-null.

@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 namespace tpm {
@@ -27,23 +28,63 @@ namespace {
 
 using namespace wk;
 
+// The wavefronts of one workgroup of the group walks.  Divided walks: the
+// workgroup holds all shares of its groups (four wavefronts, eight for eight
+// shares) and adds them up.
+__host__ __device__ constexpr uint32_t group_waves(uint32_t shares) { return shares > 4u ? 8u : 4u; }
+
+template <int WAVES>
+__device__ __forceinline__ void clear_arrived(uint32_t *arrived) {
+    if (threadIdx.x < WAVES)
+        arrived[threadIdx.x] = 0u;
+    __syncthreads();
+}
+
+template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+__device__ __forceinline__ void group64(const WalkArgs &A) {
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (SHARED) {
+        __shared__ GroupLds64 lds[kShareWaves64];
+        __shared__ uint32_t arrived[kShareWaves64];
+        clear_arrived<kShareWaves64>(arrived);
+        walk_group64<kOneShare, PER, TPM, OPEN, POT, MIXED>(
+            A, wave_id(), &lds[w].q, nullptr, &lds[w], arrived + (w >> A.shares_log));
+    } else {
+        IQ64 *Q = nullptr;  // the interaction queue, with a cutoff
+        if constexpr (TPM) {
+            __shared__ IQ64 q[kBlock / 64];
+            Q = &q[w];
+        }
+        walk_group64<kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), Q);
+    }
+}
+
+template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
+__device__ __forceinline__ void group32(const WalkArgs &A) {
+    if constexpr (SHARED) {
+        const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        __shared__ GroupLds32 lds[kShareWaves32];
+        __shared__ uint32_t arrived[kShareWaves32];
+        clear_arrived<kShareWaves32>(arrived);
+        walk_group32<kOneShare, PER, TPM, OPEN, POT, MIXED>(
+            A, wave_id(group_waves(A.shares)), nullptr, &lds[w], arrived + (w >> A.shares_log));
+    } else {
+        walk_group32<kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id());
+    }
+}
+
 // With a cutoff held to 64 VGPRs (66 without the bound): eight wavefronts per
 // SIMD, 7.18 -> 6.64 ms for the geometric pass over 128^3 clustered particles
 // (six where potentials or individual softening need more registers).
 template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!TPM ? 4 : POT || MIXED ? 6 : 8))) void
 k_walk64(const WalkArgs A) {
-    IQ64 *Q = nullptr;  // the interaction queue, with a cutoff
-    if constexpr (TPM) {
-        __shared__ IQ64 q[kBlock / 64];
-        Q = &q[threadIdx.x >> 6];
-    }
-    walk_group64<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), Q);
+    group64<SHARED, PER, TPM, OPEN, POT, MIXED>(A);
 }
 
 template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
-__global__ __launch_bounds__(kBlock) void k_walk32(const WalkArgs A) {
-    walk_group32<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id());
+__global__ __launch_bounds__(SHARED ? kShareWaves32 * 64 : kBlock) void k_walk32(const WalkArgs A) {
+    group32<SHARED, PER, TPM, OPEN, POT, MIXED>(A);
 }
 
 // Sparse active sets: a census counts the compact groups (group_compact),
@@ -80,13 +121,8 @@ __device__ __forceinline__ bool mostly_compact(const WalkArgs &A) {
 template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!TPM ? 4 : POT || MIXED ? 6 : 8))) void
 k_walk64m(const WalkArgs A) {
-    IQ64 *Q = nullptr;
-    if constexpr (TPM) {
-        __shared__ IQ64 q[kBlock / 64];
-        Q = &q[threadIdx.x >> 6];
-    }
     if (mostly_compact(A))
-        walk_group64<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id(), Q);
+        group64<SHARED, PER, TPM, OPEN, POT, MIXED>(A);
 }
 
 template <bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
@@ -96,9 +132,9 @@ __global__ __launch_bounds__(kBlock) void k_walk64im(const WalkArgs A) {
 }
 
 template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
-__global__ __launch_bounds__(kBlock) void k_walk32m(const WalkArgs A) {
+__global__ __launch_bounds__(SHARED ? kShareWaves32 * 64 : kBlock) void k_walk32m(const WalkArgs A) {
     if (mostly_compact(A))
-        walk_group32<SHARED ? kOneShare : kWhole, PER, TPM, OPEN, POT, MIXED>(A, wave_id());
+        group32<SHARED, PER, TPM, OPEN, POT, MIXED>(A);
 }
 
 template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
@@ -195,9 +231,8 @@ template <typename T>
 __global__ __launch_bounds__(kBlock) void k_output(
     const int32_t *__restrict__ idx, int64_t n_act, int64_t n, const int32_t *__restrict__ rank,
     const uint32_t *__restrict__ slot, const uint32_t *__restrict__ nuniq,
-    const T *__restrict__ res, const T *__restrict__ rpot, uint32_t shares, uint32_t plane,
-    T *__restrict__ acc, T *__restrict__ pot, uint32_t *__restrict__ nint,
-    uint32_t *__restrict__ err) {
+    const T *__restrict__ res, const T *__restrict__ rpot, T *__restrict__ acc,
+    T *__restrict__ pot, uint32_t *__restrict__ nint, uint32_t *__restrict__ err) {
     int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= n_act)
         return;
@@ -219,26 +254,13 @@ __global__ __launch_bounds__(kBlock) void k_output(
     const uint32_t rk = (uint32_t)rank[i];
     const uint32_t sl = *nuniq == (uint32_t)n ? rk : slot[rk];
     const T *r = res + 4 * (size_t)sl;
-    T v0 = r[0], v1 = r[1], v2 = r[2];
-    uint32_t c = count_of(r[3]);
-    for (uint32_t p = 1; p < shares; p++) {  // the shares of the walk, in order
-        r = res + 4 * ((size_t)p * plane + sl);
-        v0 += r[0];
-        v1 += r[1];
-        v2 += r[2];
-        c += count_of(r[3]);
-    }
-    acc[k] = v0;
-    acc[n_act + k] = v1;
-    acc[2 * n_act + k] = v2;
-    if (pot) {
-        T v = rpot[sl];
-        for (uint32_t p = 1; p < shares; p++)
-            v += rpot[(size_t)p * plane + sl];
-        pot[k] = v;
-    }
+    acc[k] = r[0];
+    acc[n_act + k] = r[1];
+    acc[2 * n_act + k] = r[2];
+    if (pot)
+        pot[k] = rpot[sl];
     if (nint)
-        nint[k] = c;
+        nint[k] = count_of(r[3]);
 }
 
 template <typename T>
@@ -300,7 +322,8 @@ void launch_walk(const WalkArgs &A, const Launch &L, hipStream_t st) {
         k_census<PER, TPM><<<L.census_blocks, kBlock, 0, st>>>(A, (uint32_t *)A.census);
         if (L.fp32) {
             if (A.shares > 1u)
-                k_walk32m<OPEN == TPM_OPEN_REL, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+                k_walk32m<OPEN == TPM_OPEN_REL, PER, TPM, OPEN, POT, MIXED>
+                    <<<L.blocks, group_waves(A.shares) * 64, 0, st>>>(A);
             else
                 k_walk32m<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
         } else {
@@ -313,7 +336,8 @@ void launch_walk(const WalkArgs &A, const Launch &L, hipStream_t st) {
     } else {
         if (L.fp32) {
             if (A.shares > 1u)
-                k_walk32<OPEN == TPM_OPEN_REL, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
+                k_walk32<OPEN == TPM_OPEN_REL, PER, TPM, OPEN, POT, MIXED>
+                    <<<L.blocks, group_waves(A.shares) * 64, 0, st>>>(A);
             else
                 k_walk32<false, PER, TPM, OPEN, POT, MIXED><<<L.blocks, kBlock, 0, st>>>(A);
         } else {
@@ -376,8 +400,8 @@ int work_of_ctx(tpm_ctx *c, bool results, Work &w) {
     TPM_TRY(ensure(c, c->scan_tmp, (size_t)compaction_tiles(n) * 4));
     if (results) {
         const size_t esz = c->P.precision == TPM_FP32 ? 4 : 8;
-        TPM_TRY(ensure(c, c->res, (size_t)4 * result_slots(n) * esz));
-        TPM_TRY(ensure(c, c->rpot, (size_t)result_slots(n) * esz));
+        TPM_TRY(ensure(c, c->res, (size_t)4 * n * esz));
+        TPM_TRY(ensure(c, c->rpot, (size_t)n * esz));
     }
     w = Work{};
     w.mark = (uint8_t *)c->mark.p;
@@ -542,7 +566,6 @@ void wk::set_shares(const tpm_ctx *c, int64_t n_act, int opening, Variant v, Wal
     if (!c->P.periodic)
         while (A.share_shift < 12u && (c->E >> (A.share_shift + 7)) > 1)
             A.share_shift++;
-    A.plane = (uint32_t)std::min<int64_t>(n_act, c->n);
 }
 
 void wk::fill_args(tpm_ctx *c, const double *anorm, const Work &w, WalkArgs &A) {
@@ -650,7 +673,8 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
         TPM_TRY(fill_u32(c, w.nuniq + 1, 0u, 1));
     }
     const uint32_t targets = (uint32_t)std::min<int64_t>(n_act, n);
-    LA.blocks = (walk_waves(LA.variant, targets, A.shares) + 3) / 4;
+    const uint32_t wg = LA.variant == kLaneWalk ? kBlock / 64 : group_waves(A.shares);
+    LA.blocks = (walk_waves(LA.variant, targets, A.shares) + wg - 1) / wg;
     LA.lane_blocks = (walk_waves(kLaneWalk, targets, A.shares) + 3) / 4;
     LA.census_blocks = (unsigned)((groups + 3) / 4);
     const bool want_pot = pot != nullptr && P.want_potential;
@@ -671,12 +695,12 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
     if (fp32)
         k_output<float><<<ob, kBlock, 0, st>>>(
             idx, n_act, n, (const int32_t *)c->rank.p, w.slot, w.nuniq, (const float *)w.res,
-            (const float *)w.rpot, A.shares, A.plane, (float *)acc, want_pot ? (float *)pot : nullptr,
+            (const float *)w.rpot, (float *)acc, want_pot ? (float *)pot : nullptr,
             nint, (uint32_t *)c->err_flag.p);
     else
         k_output<double><<<ob, kBlock, 0, st>>>(
             idx, n_act, n, (const int32_t *)c->rank.p, w.slot, w.nuniq, (const double *)w.res,
-            (const double *)w.rpot, A.shares, A.plane, (double *)acc, want_pot ? (double *)pot : nullptr,
+            (const double *)w.rpot, (double *)acc, want_pot ? (double *)pot : nullptr,
             nint, (uint32_t *)c->err_flag.p);
     TPM_LAUNCHED(c, "k_output");
     return TPM_OK;
@@ -686,11 +710,10 @@ int forces_into(tpm_ctx *c, int32_t opening, int64_t n_act, const int32_t *idx,
 
 // ---- batched walks over many systems (continuous batching) -------------------
 //
-// One persistent launch per precision walks the groups of every request staged
-// in a batch: wavefronts pop work items (one group of one request) from a
-// device counter until the finite item list is exhausted.  A work item runs
-// the same per-group code as a single-system launch, so each result is the
-// same whether its request runs alone or in a mix.
+// One launch per precision walks the groups of every request staged in a
+// batch: each request takes the workgroups it needs.  A workgroup runs the same
+// per-group code as a single-system launch, so each result is the same whether
+// its request runs alone or in a mix.
 
 namespace tpm {
 namespace {
@@ -699,85 +722,80 @@ struct BatchReq {
     WalkArgs A;
     uint32_t variant;  // bit 0 relative criterion, 1 TreePM, 3 periodic, 4 individual
                        // softening, bits 5-6 the walk variant (wk::Variant)
-    uint32_t first;    // first work item of the request
+    uint32_t first;    // first workgroup of the request
 };
 
 // The batch kernel holds the shared-cursor and lane walks only; requests
 // that take one wavefront per target are launched on their own (inlined
 // here, that walk would push the kernel's registers into heavy spills).
+constexpr int batch_waves(bool fp32) { return fp32 ? kShareWaves32 : kShareWaves64; }
+template <bool FP32>
+struct BatchLds {
+    typename std::conditional<FP32, GroupLds32, GroupLds64>::type w[batch_waves(FP32)];
+    uint32_t arrived[batch_waves(FP32)];
+};
+
 template <bool FP32, bool PER, bool TPM, int OPEN, bool MIXED>
 __device__ __forceinline__ void batch_group(const WalkArgs &A, uint32_t g, uint32_t var,
-                                            IQ64 *Q) {
+                                            BatchLds<FP32> &lds) {
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t *arrived = lds.arrived + (w >> A.shares_log);
     if constexpr (FP32) {
         if (var == kLaneWalk)
             walk_lanes32<OPEN == TPM_OPEN_REL ? kOneShare : kWhole, PER, TPM, OPEN, false, MIXED>(A, g);
         else if (OPEN == TPM_OPEN_REL && A.shares > 1u)
-            walk_group32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g);
+            walk_group32<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, nullptr, &lds.w[w], arrived);
         else
             walk_group32<kWhole, PER, TPM, OPEN, false, MIXED>(A, g);
     } else {
         if (var == kLaneWalk)
             walk_lanes64<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g);
         else if (A.shares > 1u)
-            walk_group64<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, Q);
+            walk_group64<kOneShare, PER, TPM, OPEN, false, MIXED>(A, g, &lds.w[w].q, nullptr,
+                                                                  &lds.w[w], arrived);
         else
-            walk_group64<kWhole, PER, TPM, OPEN, false, MIXED>(A, g, Q);
+            walk_group64<kWhole, PER, TPM, OPEN, false, MIXED>(A, g, &lds.w[w].q);
     }
 }
 
 template <bool FP32, int OPEN, bool MIXED>
 __device__ __forceinline__ void batch_geometry(const BatchReq &R, uint32_t g, uint32_t lanes,
-                                               IQ64 *Q) {
+                                               BatchLds<FP32> &lds) {
     if (R.variant & 8u)  // periodic box (always with the mesh)
-        batch_group<FP32, true, true, OPEN, MIXED>(R.A, g, lanes, Q);
+        batch_group<FP32, true, true, OPEN, MIXED>(R.A, g, lanes, lds);
     else if (R.variant & 2u)  // isolated TreePM
-        batch_group<FP32, false, true, OPEN, MIXED>(R.A, g, lanes, Q);
+        batch_group<FP32, false, true, OPEN, MIXED>(R.A, g, lanes, lds);
     else
-        batch_group<FP32, false, false, OPEN, MIXED>(R.A, g, lanes, Q);
+        batch_group<FP32, false, false, OPEN, MIXED>(R.A, g, lanes, lds);
 }
 
-// The FP64 instance inlines every walk variant and takes 75 VGPRs (six
-// wavefronts per SIMD), the FP32 instance 48 (eight).
 template <bool FP32>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_walk_batch(const BatchReq *__restrict__ reqs,
-                                                       uint32_t nreq, uint32_t nitems,
-                                                       uint32_t *__restrict__ counter) {
-    const int lane = threadIdx.x & 63;
-    IQ64 *Q = nullptr;  // the FP64 walk's interaction queue (used with a cutoff)
-    if constexpr (!FP32) {
-        __shared__ IQ64 q[kBlock / 64];
-        Q = &q[threadIdx.x >> 6];
+__global__ __launch_bounds__(batch_waves(FP32) * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_walk_batch(
+    const BatchReq *__restrict__ reqs, uint32_t nreq) {
+    __shared__ BatchLds<FP32> lds;
+    clear_arrived<batch_waves(FP32)>(lds.arrived);
+    uint32_t lo = 0, hi = nreq;  // the last request that starts at or before this workgroup
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (reqs[mid].first <= blockIdx.x)
+            lo = mid;
+        else
+            hi = mid;
     }
-    for (;;) {
-        uint32_t item = 0;
-        if (lane == 0)
-            item = atomicAdd(counter, 1u);
-        item = __builtin_amdgcn_readfirstlane(__shfl(item, 0, 64));
-        if (item >= nitems)
-            break;  // every wavefront reaches this once the items are exhausted
-        uint32_t lo = 0, hi = nreq;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (reqs[mid].first <= item)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        const BatchReq &R = reqs[lo];
-        const uint32_t g = item - R.first;
-        const uint32_t lanes = (R.variant >> 5) & 3u;  // walk variant
-        const bool rel = (R.variant & 1u) != 0, mixed = (R.variant & 16u) != 0;
-        if (rel) {
-            if (mixed)
-                batch_geometry<FP32, TPM_OPEN_REL, true>(R, g, lanes, Q);
-            else
-                batch_geometry<FP32, TPM_OPEN_REL, false>(R, g, lanes, Q);
-        } else {
-            if (mixed)
-                batch_geometry<FP32, TPM_OPEN_BH, true>(R, g, lanes, Q);
-            else
-                batch_geometry<FP32, TPM_OPEN_BH, false>(R, g, lanes, Q);
-        }
+    const BatchReq &R = reqs[lo];
+    const uint32_t g = (blockIdx.x - R.first) * batch_waves(FP32) + (threadIdx.x >> 6);
+    const uint32_t lanes = (R.variant >> 5) & 3u;  // walk variant
+    const bool rel = (R.variant & 1u) != 0, mixed = (R.variant & 16u) != 0;
+    if (rel) {
+        if (mixed)
+            batch_geometry<FP32, TPM_OPEN_REL, true>(R, g, lanes, lds);
+        else
+            batch_geometry<FP32, TPM_OPEN_REL, false>(R, g, lanes, lds);
+    } else {
+        if (mixed)
+            batch_geometry<FP32, TPM_OPEN_BH, true>(R, g, lanes, lds);
+        else
+            batch_geometry<FP32, TPM_OPEN_BH, false>(R, g, lanes, lds);
     }
 }
 
@@ -801,7 +819,6 @@ struct tpm_batch {
     size_t host_cap = 0;
     void *dev = nullptr;            // device request table
     size_t dev_cap = 0;
-    uint32_t *counter = nullptr;    // two work counters
     hipEvent_t done = nullptr;      // last launch finished: staging reusable
     bool launched = false;
 };
@@ -831,10 +848,7 @@ int tpm_batch_create(void *hip_stream, tpm_batch **out) {
     if (!b)
         return TPM_ENOMEM;
     b->stream = (hipStream_t)hip_stream;
-    if (hipMalloc((void **)&b->counter, 16) != hipSuccess ||
-        hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) {
-        if (b->counter)
-            (void)hipFree(b->counter);
+    if (hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) {
         delete b;
         return TPM_ENOMEM;
     }
@@ -850,8 +864,6 @@ int tpm_batch_destroy(tpm_batch *b) {
         (void)hipHostFree(b->host);
     if (b->dev)
         (void)hipFree(b->dev);
-    if (b->counter)
-        (void)hipFree(b->counter);
     if (b->done)
         (void)hipEventDestroy(b->done);
     delete b;
@@ -904,7 +916,7 @@ int tpm_batch_launch(tpm_batch *b) {
         b->dev_cap = 2 * np * sizeof(BatchReq);
     }
     // stage: active sets of every request on the batch stream, FP32 first
-    uint32_t items[2] = {0, 0}, nreq[2] = {0, 0};
+    uint32_t blocks[2] = {0, 0}, nreq[2] = {0, 0};
     struct Own {  // a request walked by a launch of its own
         WalkArgs A;
         Launch L;
@@ -937,7 +949,7 @@ int tpm_batch_launch(tpm_batch *b) {
         R.variant = (p.opening == TPM_OPEN_REL ? 1u : 0u) | (c->P.pm_grid > 0 ? 2u : 0u) |
                     ((uint32_t)variant << 5) | (c->P.periodic ? 8u : 0u) |
                     (c->mixed ? 16u : 0u);
-        R.first = items[which];
+        R.first = blocks[which];
         const uint32_t tg = (uint32_t)std::min<int64_t>(p.n_act, c->n);
         set_shares(c, p.n_act, p.opening, variant, R.A);
         const bool split = p.n_act > 0 && variant == kSplitWalk;
@@ -946,29 +958,22 @@ int tpm_batch_launch(tpm_batch *b) {
             own.push_back({R.A, LA, p.opening, c->mixed != 0, c->P.periodic != 0,
                            c->P.pm_grid > 0});
         }
-        if (p.n_act > 0 && !split)
-            items[which] += walk_waves(variant, tg, R.A.shares);
+        if (p.n_act > 0 && !split) {
+            const uint32_t wg = batch_waves(which == 0);
+            blocks[which] += (walk_waves(variant, tg, R.A.shares) + wg - 1) / wg;
+        }
         nreq[which]++;
     }
     BHIP(b, hipMemcpyAsync(b->dev, b->host, np * sizeof(BatchReq), hipMemcpyHostToDevice,
                            b->stream));
-    {
-        tpm_ctx tmp;  // fill kernels only need a stream
-        tmp.stream = b->stream;
-        if (fill_u32(&tmp, b->counter, 0u, 2) != TPM_OK)
-            return bfail(b, TPM_EDEVICE, tmp.err);
-    }
     const BatchReq *dreq = (const BatchReq *)b->dev;
-    const uint32_t max_blocks = 2048;
-    if (items[0]) {
-        const uint32_t blocks = std::min<uint32_t>(max_blocks, (items[0] + 3) / 4);
-        k_walk_batch<true><<<blocks, kBlock, 0, b->stream>>>(dreq, nreq[0], items[0], b->counter);
+    if (blocks[0]) {
+        k_walk_batch<true><<<blocks[0], batch_waves(true) * 64, 0, b->stream>>>(dreq, nreq[0]);
         BHIP(b, hipGetLastError());
     }
-    if (items[1]) {
-        const uint32_t blocks = std::min<uint32_t>(max_blocks, (items[1] + 3) / 4);
-        k_walk_batch<false><<<blocks, kBlock, 0, b->stream>>>(dreq + nreq[0], nreq[1], items[1],
-                                                              b->counter + 1);
+    if (blocks[1]) {
+        k_walk_batch<false><<<blocks[1], batch_waves(false) * 64, 0, b->stream>>>(dreq + nreq[0],
+                                                                                  nreq[1]);
         BHIP(b, hipGetLastError());
     }
     for (const Own &o : own) {
@@ -986,17 +991,16 @@ int tpm_batch_launch(tpm_batch *b) {
         if (p.n_act == 0)
             continue;
         tpm_ctx *c = p.c;
-        const uint32_t shares = b->host[o].A.shares, plane = b->host[o].A.plane;
         const unsigned ob = grid_for(p.n_act, kBlock);
         if (c->P.precision == TPM_FP32)
             k_output<float><<<ob, kBlock, 0, b->stream>>>(
                 p.idx, p.n_act, c->n, (const int32_t *)c->rank.p, (const uint32_t *)c->slot.p,
-                (const uint32_t *)c->counters.p + 40, (const float *)c->res.p, (const float *)c->rpot.p, shares, plane, (float *)p.acc, nullptr,
+                (const uint32_t *)c->counters.p + 40, (const float *)c->res.p, (const float *)c->rpot.p, (float *)p.acc, nullptr,
                 p.nint, (uint32_t *)c->err_flag.p);
         else
             k_output<double><<<ob, kBlock, 0, b->stream>>>(
                 p.idx, p.n_act, c->n, (const int32_t *)c->rank.p, (const uint32_t *)c->slot.p,
-                (const uint32_t *)c->counters.p + 40, (const double *)c->res.p, (const double *)c->rpot.p, shares, plane, (double *)p.acc, nullptr,
+                (const uint32_t *)c->counters.p + 40, (const double *)c->res.p, (const double *)c->rpot.p, (double *)p.acc, nullptr,
                 p.nint, (uint32_t *)c->err_flag.p);
         BHIP(b, hipGetLastError());
     }

@@ -57,7 +57,6 @@ struct WalkArgs {
     uint32_t shares, shares_log;
     uint32_t shares_bh;    // those of the geometric pass, where one request runs both
     uint32_t share_shift;  // log2 of the entries of a block
-    uint32_t plane;        // slots per share in res and rpot
 };
 
 // Wavefront masks: ballot of a lane predicate, and a mask read back as the
@@ -489,7 +488,7 @@ __device__ __forceinline__ uint64_t equal_mask(uint32_t a, uint32_t b) {
 // Who walks a target's shares.
 enum Shares : int {
     kWhole = 0,      // the walk is not divided
-    kOneShare = 1,   // each wavefront (lane) one share; the output adds them
+    kOneShare = 1,   // each wavefront (lane) one share; its workgroup (wavefront) adds them
     kAllShares = 2,  // one wavefront (lane) all of them in one pass, each with its
                      // own sum in LDS: the same total without the divided
                      // walks' repeated steps (the resident server, whose other
@@ -536,6 +535,77 @@ __device__ __forceinline__ void parts_total(Parts<T> *P, uint32_t cs, uint32_t s
     }
 }
 
+// The sums of one wavefront's share of a group (kOneShare): a group's shares are
+// neighbouring wavefronts of one workgroup, and the last of them to finish adds
+// them up, so a walk's shares need no memory beyond the workgroup's LDS.
+template <typename T>
+struct ShareSum {
+    T v[4][64];  // acceleration, potential
+    uint32_t n[64];
+};
+// Wavefronts of a workgroup whose walks may be divided: a group's shares at most.
+constexpr int kShareWaves32 = kMaxShares32, kShareWaves64 = kMaxShares64;
+static_assert(kShareWaves64 * 64 == kBlock, "");
+// LDS of one wavefront of such a workgroup; FP64: the interaction queue, then the sums.
+struct GroupLds32 {
+    ShareSum<float> sums;
+};
+union GroupLds64 {
+    IQ64 q;
+    ShareSum<double> sums;
+};
+// Adds up the shares of this wavefront's group; true in the one wavefront that
+// then holds the total, share 0 + share 1 + ...  lds: this wavefront's, with those
+// of the group's other shares beside it in their order; arrived: the group's
+// count, zero when the workgroup starts.
+template <bool POT, typename Lds, typename T>
+__device__ __forceinline__ bool join_shares(Lds *lds, uint32_t *arrived, uint32_t share,
+                                            uint32_t shares, T &a0, T &a1, T &a2, T &pot,
+                                            uint32_t &nint) {
+    const int lane = threadIdx.x & 63;
+    ShareSum<T> &mine = lds->sums;
+    mine.v[0][lane] = a0;
+    mine.v[1][lane] = a1;
+    mine.v[2][lane] = a2;
+    if (POT)
+        mine.v[3][lane] = pot;
+    mine.n[lane] = nint;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    uint32_t before = 0u;
+    if (lane == 0)
+        before = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__builtin_amdgcn_readfirstlane(before) != shares - 1u)
+        return false;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    for (uint32_t p = 0; p < shares; p++) {
+        const ShareSum<T> &s = (lds - share + p)->sums;
+        a0 = p ? a0 + s.v[0][lane] : s.v[0][lane];
+        a1 = p ? a1 + s.v[1][lane] : s.v[1][lane];
+        a2 = p ? a2 + s.v[2][lane] : s.v[2][lane];
+        if (POT)
+            pot = p ? pot + s.v[3][lane] : s.v[3][lane];
+        nint = p ? nint + s.n[lane] : s.n[lane];
+    }
+    return true;
+}
+// The same for the shares of a target in neighbouring lanes: the total in the
+// lane of share 0.
+template <bool POT, typename T>
+__device__ __forceinline__ void join_lanes(uint32_t shares, T &a0, T &a1, T &a2, T &pot,
+                                           uint32_t &nint) {
+    const T s0 = a0, s1 = a1, s2 = a2, sp = pot;
+    const uint32_t sn = nint;
+    for (uint32_t p = 1; p < shares; p++) {
+        a0 += __shfl_down(s0, p);
+        a1 += __shfl_down(s1, p);
+        a2 += __shfl_down(s2, p);
+        if (POT)
+            pot += __shfl_down(sp, p);
+        nint += __shfl_down(sn, p);
+    }
+}
+
 // Side of a level-`lev` cube, scaled from the root side through the exponent
 // field (exact: the root side is a normal number and lev <= 21).
 __device__ __forceinline__ double scale_level(double v, uint32_t lev) {
@@ -548,7 +618,9 @@ __device__ __forceinline__ double scale_level(double v, uint32_t lev) {
 // (as masks) and only branches on wavefront-uniform conditions are taken.
 template <int SHARES, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t item, IQ64 *Q,
-                                             Parts<double> *P = nullptr) {
+                                             Parts<double> *P = nullptr,
+                                             GroupLds64 *lds = nullptr,
+                                             uint32_t *arrived = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
     static_assert(!(ALL && POT), "");
     const uint32_t shares = shares_of(A, OPEN);
@@ -833,8 +905,10 @@ __device__ __forceinline__ void walk_group64(const WalkArgs &A, uint32_t item, I
         flush();
     if (ALL)
         parts_total(P, cs, shares, a0, a1, a2);
+    if (SHARED && !join_shares<POT>(lds, arrived, share, shares, a0, a1, a2, pot, nint))
+        return;
     if (valid)
-        store_result<double>(A, (SHARED ? share * A.plane : 0u) + slot, a0, a1, a2, POT, pot, nint);
+        store_result<double>(A, slot, a0, a1, a2, POT, pot, nint);
 }
 
 // ---- FP32 walk ----------------------------------------------------------------
@@ -990,7 +1064,9 @@ __device__ __forceinline__ float max3_abs(float a, float b, float c) {
 
 template <int SHARES, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t item,
-                                             Parts<float> *P = nullptr) {
+                                             Parts<float> *P = nullptr,
+                                             GroupLds32 *lds = nullptr,
+                                             uint32_t *arrived = nullptr) {
     constexpr bool SHARED = SHARES == kOneShare, ALL = SHARES == kAllShares;
     static_assert(!(ALL && POT), "");
     const uint32_t shares = shares_of(A, OPEN);
@@ -1207,8 +1283,10 @@ __device__ __forceinline__ void walk_group32(const WalkArgs &A, uint32_t item,
     }
     if (ALL)
         parts_total(P, cs, shares, a0, a1, a2);
+    if (SHARED && !join_shares<POT>(lds, arrived, share, shares, a0, a1, a2, pot, nint))
+        return;
     if (valid)
-        store_result<float>(A, (SHARED ? share * A.plane : 0u) + slot, a0, a1, a2, POT, pot, nint);
+        store_result<float>(A, slot, a0, a1, a2, POT, pot, nint);
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
@@ -1230,8 +1308,9 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb) {
     return ((i / run) * 8u + (b & 7u)) * run + i % run;
 }
 
-__device__ __forceinline__ uint32_t wave_id() {
-    return (xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x) >> 6;
+// waves: wavefronts of a workgroup.
+__device__ __forceinline__ uint32_t wave_id(uint32_t waves = kBlock / 64) {
+    return xcd_block(blockIdx.x, gridDim.x) * waves + (threadIdx.x >> 6);
 }
 
 // The lane walk in a periodic box keeps one contiguous eighth of the curve per
@@ -1516,14 +1595,15 @@ __device__ __forceinline__ void walk_lanes64(const WalkArgs &A, uint32_t wave,
                     e = r.skip;
                 else
                     e = visit(e, r, owned) ? e + 1u : r.skip;
-                if (e >= A.E) {
-                    if (ALL)
-                        parts_total(P, cs, shares, a0, a1, a2);
-                    store_result<double>(A, share * A.plane + slot, a0, a1, a2, POT, pot, nint);
-                    live = false;
-                }
+                live = e < A.E;
             }
         }
+        if (ALL)
+            parts_total(P, cs, shares, a0, a1, a2);
+        if (SHARED)
+            join_lanes<POT>(shares, a0, a1, a2, pot, nint);
+        if (slot < nu && share == 0u)
+            store_result<double>(A, slot, a0, a1, a2, POT, pot, nint);
     } else {
         start(base);
         uint32_t *cur, nf;  // the set-aside subtrees
@@ -1667,14 +1747,15 @@ __device__ __forceinline__ void walk_lanes32(const WalkArgs &A, uint32_t wave,
                     e = r.skip;
                 else
                     e = visit(e, r, owned) ? e + 1u : r.skip;
-                if (e >= A.E) {
-                    if (ALL)
-                        parts_total(P, cs, shares, a0, a1, a2);
-                    store_result<float>(A, share * A.plane + slot, a0, a1, a2, POT, pot, nint);
-                    live = false;
-                }
+                live = e < A.E;
             }
         }
+        if (ALL)
+            parts_total(P, cs, shares, a0, a1, a2);
+        if (SHARED)
+            join_lanes<POT>(shares, a0, a1, a2, pot, nint);
+        if (slot < nu && share == 0u)
+            store_result<float>(A, slot, a0, a1, a2, POT, pot, nint);
     } else {
         start(base);
         uint32_t *cur, nf;  // the set-aside subtrees

@@ -71,6 +71,17 @@ def test_parameter_validation_on_host():
 
 
 @pytest.mark.skipif(not os.path.exists(LIB), reason="library not built")
+@pytest.mark.parametrize("n", [4096, 8193, 65536, 100003, 131072, 262145, 1 << 20])
+def test_memory_per_particle(n):
+    """The admission estimate of a tree without a mesh: at most 465 (FP64) or
+    545 bytes per particle (2.5 entries each, individual softening, an eighth
+    of headroom), small trees, whose walks are divided, like large ones."""
+    from paper_1909_04667_amd import binding as B
+    for prec, per in (("fp64", 465), ("fp32", 545)):
+        assert B.bytes_needed(B.make_params(precision=prec, eps=0.01), n) <= per * n + 30000
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="library not built")
 def test_product_path_does_not_reference_the_oracle():
     """The HIP library and its binding never load the CPU oracle."""
     pkg = os.path.join(ROOT, "paper_1909_04667_amd")

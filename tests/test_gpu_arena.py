@@ -115,6 +115,26 @@ def test_arena_matches_lazy_allocation(name, prec):
     c2.close()
 
 
+@pytest.mark.parametrize("prec,mesh,arena", [("fp64", 0, 45183839), ("fp32", 0, 53062158),
+                                             ("fp64", 32, 58622460), ("fp32", 32, 59944693)])
+def test_divided_walks_need_no_memory_of_their_own(prec, mesh, arena):
+    """Walks divided into shares add them up in their workgroups: an arena of
+    452 (FP64) or 531 bytes per particle, plus the mesh, holds every call, with
+    the results of a lazily allocating context."""
+    from paper_1909_04667_amd import binding as B
+    p = W.hernquist(100003, 8)
+    kw = dict(eps=0.005, want_potential=True, **({"pm_grid": mesh} if mesh else {}))
+    lazy = B.Context(precision=prec, **kw)
+    ref = _exercise(lazy, p, 0.5)
+    assert lazy.bytes_held() <= arena
+    lazy.close()
+    ctx = B.Context(precision=prec, arena_bytes=arena, **kw)
+    got = _exercise(ctx, p, 0.5)
+    for k, (a, b) in enumerate(zip(ref, got)):
+        assert np.array_equal(a, b), k
+    ctx.close()
+
+
 def test_arena_too_small_fails_before_writing():
     from paper_1909_04667_amd import binding as B
     p = W.zeldovich_box(32, 100.0, 7)

@@ -479,6 +479,42 @@ def test_shares_of_a_walk(n, mesh, monkeypatch):
     assert float(err.max()) <= 64 * 2.0 ** -24 * float(out[0][2].max())
 
 
+@pytest.mark.parametrize("n", [20000, 196608, 196609, 262144, 262145, 524288, 524289])
+@pytest.mark.parametrize("mesh", [0, 16])
+def test_shares_of_a_walk_fp64(n, mesh, monkeypatch):
+    """The same in FP64, around the sizes where its number of shares changes
+    (the relative pass is divided in two up to 524288, the geometric one up to
+    262144), with potentials: a group's shares are added in one workgroup, a
+    target's in neighbouring lanes."""
+    p = W.uniform_cube(n, 43, side=100.0)
+    for v in (p.x, p.y, p.z):
+        v[50:750] = 31.0
+    kw = dict(precision="fp64", eps=0.05, alpha=0.02, theta=1.0, want_potential=True)
+    if mesh:
+        kw.update(periodic=True, box_size=100.0, pm_grid=mesh, rcut=0.5)
+    for opening in ("bh", "rel"):
+        out = []
+        for mode in ("1", "2", "3"):
+            monkeypatch.setenv("TPM_WALK_MODE", mode)
+            ctx = _ctx(**kw)
+            _build(ctx, p)
+            nint = torch.full((n,), -1, dtype=torch.int32, device=_dev())
+            acc, pot = ctx.compute_forces(_t(np.arange(n), torch.int32), opening,
+                                          n_interactions=nint, a_old_norm=_t(np.full(n, 1e-3)))
+            ctx.check()
+            out.append((acc, pot, nint))
+        for a, b in zip(out[0], out[1]):
+            assert torch.equal(a, b)
+        assert torch.equal(out[0][2], out[2][2])
+        for k in (0, 1):
+            a, b = (out[q][k].reshape(-1, n) for q in (0, 2))
+            mag = a.norm(dim=0)
+            scale = mag.clamp_min(float(mag.square().mean().sqrt()))
+            # rounding of two summation orders of at most n_int terms
+            bound = 64 * 2.0 ** -53 * float(out[0][2].max())
+            assert float(((a - b).norm(dim=0) / scale).max()) <= bound
+
+
 @pytest.mark.parametrize("n", [4097, 16383, 16384, 16385])
 @pytest.mark.parametrize("periodic", [False, True])
 def test_wavefront_per_target_with_a_cutoff(n, periodic, monkeypatch):

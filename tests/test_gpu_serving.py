@@ -307,6 +307,39 @@ def test_resident_adds_the_same_shares(prec, mesh):
     lp.close()
 
 
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [65537, 196609, 262145])
+def test_shares_in_batch_and_resident(prec, n):
+    """Beyond each size where the number of shares changes: batch and resident
+    kernel add the shares of the single-system launch, bit for bit -- all
+    targets (shared cursor) and a spread-out fifth (lanes)."""
+    from paper_1909_04667_amd import binding as B
+    p = W.uniform_cube(n, 47, side=100.0)
+    for v in (p.x, p.y, p.z):
+        v[50:750] = 31.0
+    ctx = B.Context(precision=prec, eps=0.05, alpha=0.02, theta=1.0)
+    t = lambda a: torch.as_tensor(a, dtype=torch.float64, device=_dev())
+    ctx.build_tree(t(p.x), t(p.y), t(p.z))
+    lp, batch = B.ResidentServer(prec), B.Batch()
+    an = t(np.full(n, 1e-3))
+    for k in (n, n // 5):
+        ids = np.sort(np.random.default_rng(3).choice(n, k, replace=False)).astype(np.int32)
+        ix = torch.as_tensor(ids, device=_dev())
+        for opening in ("rel", "bh"):
+            c = [torch.empty(k, dtype=torch.int32, device=_dev()) for _ in range(3)]
+            ref, _ = ctx.compute_forces(ix, opening, a_old_norm=an, n_interactions=c[0])
+            got = batch.add(ctx, ix, opening, a_old_norm=an, n_interactions=c[1])
+            batch.launch()
+            torch.cuda.synchronize()
+            assert torch.equal(got, ref) and torch.equal(c[0], c[1]), (k, opening)
+            tk, acc = lp.submit(ctx, ix, opening, a_old_norm=an, n_interactions=c[2])
+            lp.wait(tk)
+            assert torch.equal(acc, ref) and torch.equal(c[0], c[2]), (k, opening)
+    ctx.check()
+    lp.close()
+    batch.close()
+
+
 def _threshold_lattice(side=64):
     """2 side^3 particles of a periodic lattice with a basis of two, on
     coordinates without rounding: with every cube opened all particles have
