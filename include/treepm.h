@@ -24,7 +24,7 @@
  *   tpm_kick, tpm_drift, tpm_time_bins, tpm_select_bins, tpm_gather
  *                       Sec. 7    leapfrog with power-of-two time bins and
  *                                 the split-Hamiltonian variant
- *   tpm_batch_*         many systems' walks in one persistent launch
+ *   tpm_batch_*         many systems' walks in one launch per precision
  *
  * Conventions for every entry point:
  *   - All particle arrays are DEVICE pointers (HIP global memory), borrowed
@@ -186,14 +186,19 @@ int tpm_set_shift(tpm_ctx *ctx, const double *shift);
  * pot:         device [n_act] of the same type, or NULL.
  * n_interactions: device uint32[n_act] node + particle interactions per
  *              target (the cost factor g_i of Sec. 8), or NULL.
- * Results are deterministic.  Small active sets (at most 4096 targets, 16384 in
- * FP64 with a mesh where they are a quarter of the particles, or 65536 in trees of 2^22 particles or more) are walked with
- * one wavefront per target, and sets of at most 262144 targets (524288 in the
- * relative pass) in two, four (at most 196608) or eight (at most 65536, FP32)
- * shares that are then added: a target's
- * interactions are added in another order than in larger sets, and its force
- * may differ in the last bits between sets of different kinds; interaction
- * counts never differ.
+ * Results are deterministic.  A target's interactions are added in an order that
+ * depends on the kind of its active set, so its force may differ in the last
+ * bits between sets of different kinds; interaction counts never differ.
+ * One wavefront per target walks sets of at most 4096 targets; in FP64 with a
+ * mesh of at most 16384 where they are a quarter of the particles or more; in
+ * trees of 2^22 particles or more of at most 65536.  Other sets are walked in
+ * shares that are then added, in order:
+ *   relative pass   FP32 8 up to 65536 targets, 4 up to 196608, 2 up to 262144
+ *                   (isolated systems 524288); FP64 4 up to 196608, 2 up to 524288
+ *   geometric pass  FP32 undivided; FP64 4 up to 196608, 2 up to 262144, except
+ *                   isolated systems with one softening length, sets of less
+ *                   than a quarter of the particles: 4 up to 49152, 2 up to 98304
+ * and larger ones undivided.
  * Enqueues work only; does not synchronise. */
 int tpm_compute_forces(tpm_ctx *ctx, int32_t opening, int64_t n_act, const int32_t *active_idx,
                        const double *a_old_norm, void *acc, void *pot,
@@ -339,8 +344,8 @@ int tpm_batch_add(tpm_batch *batch, tpm_ctx *ctx, int32_t opening, int64_t n_act
                   uint32_t *n_interactions);
 
 /* Enqueue the staged requests: active-set selection per request, one
- * persistent walk per precision, outputs per request; then clear the
- * stage.  Does not synchronise (except to reuse its pinned staging table
+ * walk per precision (requests walked with one wavefront per target: one
+ * each), outputs per request; then clear the stage.  Does not synchronise (except to reuse its pinned staging table
  * after the previous launch). */
 int tpm_batch_launch(tpm_batch *batch);
 

@@ -489,8 +489,8 @@ __device__ __forceinline__ void item_output(const SrvReq &R, uint32_t it) {
     }
 }
 
-// Both instances inline every walk variant (FP32: 77 VGPRs, FP64: 108, no
-// spills); each is launched with two wavefronts per SIMD.
+// Both instances inline every walk variant (FP32: 76 VGPRs, FP64: 107, none
+// spilled); each is launched with two wavefronts per SIMD.
 template <bool FP32>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FP32 ? 4 : 2))) void k_server(
     SrvDev *st, SrvHost *host, SrvReq *slots, Job *jobs, unsigned long long idle_ticks) {
@@ -727,7 +727,7 @@ int tpm_server_create(int32_t precision, double idle_ms, tpm_server **out) {
         hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, s->device) !=
             hipSuccess)
         rc = TPM_EDEVICE;
-    // Two wavefronts per SIMD each: FP32 (77 VGPRs) and FP64 (108) then fit
+    // Two wavefronts per SIMD each: FP32 (76 VGPRs) and FP64 (107) then fit
     // in a SIMD's registers beside each other (and four blocks of 34 KiB in
     // a CU's LDS); kernels of other work (builds of newly admitted systems)
     // run when the servers drain or idle.  Measured on the serving mix of 16

@@ -75,7 +75,8 @@ __device__ __forceinline__ void group32(const WalkArgs &A) {
 
 // With a cutoff held to 64 VGPRs (66 without the bound): eight wavefronts per
 // SIMD, 7.18 -> 6.64 ms for the geometric pass over 128^3 clustered particles
-// (six where potentials or individual softening need more registers).
+// (six where potentials or individual softening need more registers).  Scalar
+// registers spill into lanes of a vector register there; nothing goes to memory.
 template <bool SHARED, bool PER, bool TPM, int OPEN, bool POT, bool MIXED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!TPM ? 4 : POT || MIXED ? 6 : 8))) void
 k_walk64(const WalkArgs A) {
@@ -727,7 +728,8 @@ struct BatchReq {
 
 // The batch kernel holds the shared-cursor and lane walks only; requests
 // that take one wavefront per target are launched on their own (inlined
-// here, that walk would push the kernel's registers into heavy spills).
+// here, that walk would push the kernel's registers into heavy spills).  FP32: 35
+// VGPRs (eight wavefronts per SIMD), FP64: 67 (seven).
 constexpr int batch_waves(bool fp32) { return fp32 ? kShareWaves32 : kShareWaves64; }
 template <bool FP32>
 struct BatchLds {
