@@ -197,7 +197,8 @@ int tpm_set_shift(tpm_ctx *ctx, const double *shift);
  *                   (isolated systems 524288); FP64 4 up to 196608, 2 up to 524288
  *   geometric pass  FP32 undivided; FP64 4 up to 196608, 2 up to 262144, except
  *                   isolated systems with one softening length, sets of less
- *                   than a quarter of the particles: 4 up to 49152, 2 up to 98304
+ *                   than a twelfth of the particles (with a mesh a quarter):
+ *                   4 up to 49152, 2 up to 98304
  * and larger ones undivided.
  * Enqueues work only; does not synchronise. */
 int tpm_compute_forces(tpm_ctx *ctx, int32_t opening, int64_t n_act, const int32_t *active_idx,

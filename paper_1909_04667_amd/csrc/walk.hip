@@ -449,13 +449,17 @@ int select_active(tpm_ctx *c, int64_t n_act, const int32_t *idx) {
 
 // The geometric pass over a sparse set of an isolated system in FP64: thousands
 // of interactions for each target, and every share repeats the steps of the upper
-// tree, so shares stop paying early.  ms for 1, 2, 4 shares, random | densest set
-// (shared cursor or lanes by the census): Hernquist 2^20, 4 % 2.04 1.65 1.97 | 2.41 1.62
-// 1.26, 6 % 2.04 1.83 2.87 | 2.11 1.64 1.32, 7.5 % 2.05 2.23 3.25 | 2.10 1.72 1.45; 2^22, 2 %
-// 2.51 3.17 5.00 | 2.29 2.04 2.14, 4 % 3.73 5.33 9.42 | 2.68 3.00 3.37.
-// With a mesh the cutoff spans tens of length units, and lanes win from there on
-// (2^20, 64^3 mesh, lanes | shared cursor at the better of the two: 5 % random 2.44 | 3.48,
-// densest 2.45 | 2.38; 10 % 2.86 | 3.60, 3.05 | 3.25; 2^21, 9 % 3.71 | 5.54, 3.85 | 4.97).
+// tree, so in lanes, one share each, shares stop paying early.  ms for 1, 2, 4
+// shares, random | densest set (lanes | shared cursor): Hernquist 2^20, 4 % 2.04 1.65 1.97
+// | 2.41 1.62 1.26, 6 % 2.04 1.83 2.87 | 2.11 1.64 1.32, 7.5 % 2.05 2.23 3.25 | 2.10 1.72
+// 1.45; 2^22, 2 % 2.51 3.17 5.00 | 2.29 2.04 2.14, 4 % 3.73 5.33 9.42 | 2.68 3.00 3.37.  From a
+// twelfth of the particles on, random sets too are compact on the curve (768
+// particles for 64 targets) and take the shared cursor (10 % of 2^20: 2.96 2.57 2.13 |
+// 2.45 1.97 1.65).
+// With a mesh the cutoff spans tens of length units, and undivided lanes win from
+// there on whatever the set (2^20, 64^3 mesh, lanes | shared cursor at the better of the
+// two: 5 % random 2.44 | 3.48, densest 2.45 | 2.38; 10 % 2.86 | 3.60, 3.05 | 3.25; 2^21, 9 %
+// 3.71 | 5.54, 3.85 | 4.97).
 // With individual softening, whose interactions cost more, four shares pay as
 // elsewhere (2^20, 10 % 4.48 3.36 2.75 | 3.24 2.57 2.21).
 constexpr int64_t kGeoShares4 = 49152, kGeoShares2 = 98304;
@@ -548,7 +552,7 @@ static uint32_t shares_log(const tpm_ctx *c, int64_t n_act, int opening, Variant
     const bool fp32 = c->P.precision == TPM_FP32, rel = opening == TPM_OPEN_REL;
     if (v == kSplitWalk || (fp32 && !rel))
         return 0u;
-    if (sparse_geometric(c, n_act, opening))  // FP64
+    if (sparse_geometric(c, n_act, opening) && (c->P.pm_grid > 0 || 12 * n_act < c->n))  // FP64
         return n_act <= kGeoShares4 ? 2u : n_act <= kGeoShares2 ? 1u : 0u;
     if (t <= 65536 && fp32)
         return 3u;

@@ -596,7 +596,7 @@ def test_sparse_sets_group_or_lanes_identical(prec):
         assert torch.equal(acc.cpu(), full[:, sub])
 
 
-@pytest.mark.parametrize("k", [4097, 49152, 49153, 98304, 98305])
+@pytest.mark.parametrize("k", [4097, 33333, 33334, 49152, 49153, 98304, 98305])
 @pytest.mark.parametrize("prec,mesh", [("fp64", 0), ("fp64", 32), ("fp32", 32)])
 def test_sparse_sets_of_an_isolated_system(prec, mesh, k, monkeypatch):
     """Sparse sets of an isolated system: shared cursor or lanes by the census
