@@ -1310,7 +1310,7 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb) {
 
 // waves: wavefronts of a workgroup.
 __device__ __forceinline__ uint32_t wave_id(uint32_t waves = kBlock / 64) {
-    return xcd_block(blockIdx.x, gridDim.x) * waves + (threadIdx.x >> 6);
+    return (xcd_block(blockIdx.x, gridDim.x) * (waves * 64u) + threadIdx.x) >> 6;
 }
 
 // The lane walk in a periodic box keeps one contiguous eighth of the curve per
